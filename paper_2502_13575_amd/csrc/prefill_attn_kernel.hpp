@@ -1,4 +1,4 @@
-// Step-prefill attention on the matrix cores: one workgroup of eight wavefronts = one
+// Step-prefill attention on the matrix cores: one workgroup of four wavefronts = one
 // block of query tokens of a leaf query's node, one kv head.
 //
 // Scoring a new step with the reward model is a prefill of that step's tokens over the
@@ -13,16 +13,18 @@
 // side cache feed the compute units, not by the matrix cores.  Blocks of the same node
 // and of sibling nodes run next to each other and find their shared ancestors in L2.
 //
-// Wave w owns 32 query rows.  The 32x32x16 matrix instructions are used: on this chip
-// they take as long as the 16x16x32 ones and do twice the work.  Lane l = (n, g), n =
-// l % 32, g = l / 32.  Per run of 32 rows:
+// Bound: the matrix cores.  One wave per SIMD owns 64 query rows (two blocks of 32), so that
+// every K and V fragment read from LDS feeds two matrix instructions: with 32 rows per wave
+// the fragment reads alone (16 KB per wave and run at 128 bytes per cycle) take as long as
+// the matrix instructions.  Lane l = (n, g), n = l % 32, g = l / 32.  Per run of 32 rows and
+// block of 32 query rows:
 //   S^T = K Q^T     8 x v_mfma_f32_32x32x16_bf16: run rows on M, query rows on N.  A = K
 //                   rows from the LDS tile (lane (n, g): row n, d = 16 kk + 8 g .. + 7),
 //                   B = Q in registers.  Lane (n, g) receives query row n against run
 //                   rows 8 c + 4 g + r (c, r = 0..3);
 //   mask            run row t counts iff t < n_run and kpos + t <= i_row, kpos being the
-//                   run's position inside the node (ancestors: always).  One code path:
-//                   a run that needs no mask sees lim = 32;
+//                   run's position inside the node (ancestors: always).  Runs that are seen
+//                   in full, nearly all, branch past it;
 //   softmax         against a per-row reference that is raised only when a score exceeds
 //                   it by 2^8 in weight (then one cross-lane exchange);
 //   O^T += V^T P^T  8 x v_mfma_f32_32x32x16_f16: d on M (4 blocks of 32), query rows on
@@ -31,20 +33,20 @@
 //                   of half t stands for run row 16 t + 8 c' + 4 g + r; V, converted to
 //                   fp16 while it is staged, is written to LDS as A fragments in that
 //                   slot order.
-// The work on a run is software pipelined inside the wave, because matrix and vector
-// instructions only overlap when they alternate in program order:
-//   [ scores(u + 1) || weights(u) ]  [ apply(u) || mask, maximum(u + 1) ]  raise(u + 1)
-// (half t of the weights takes the scores of c = 2 t and 2 t + 1)
-// and the pipeline runs on across tiles: the first run of the next tile is read from
-// the next LDS buffer.  Three tile buffers rotate, so that the next tile can be staged
+// The work on a run is software pipelined inside the wave (prefill_unit), and the pipeline
+// runs on across tiles.  Three tile buffers rotate, so that the next tile can be staged
 // while the previous one may still be read by a slower wave: one barrier per tile (new
-// contents visible), and the staging sits in the same basic block as the matrix work.
-// K and V are fetched with range-checked buffer loads, three tiles ahead of their use
-// (two register sets alternate; one tile ahead left the waves waiting for memory):
-// waves 0..3 each fetch and stage half a run (16 rows, 16 bytes per lane and load) of K,
-// waves 4..7 of V.  The run list can be long (a
-// path of thousands of rows), so its descriptors travel through a ring of 256 entries in
-// LDS that is refilled 128 at a time, 64 tiles ahead of their use.
+// contents visible), and the staging is spread over the gaps of the matrix instructions.
+// K and V are fetched with range-checked buffer loads two and a half tiles ahead of their
+// use (two register sets alternate; one tile ahead left the waves waiting for memory).
+// Each wave fetches and stages half a run (16 rows, 16 bytes per lane and load) of K and of V.
+// The run list can be long (a path of thousands of rows), so its descriptors travel through
+// a ring of 256 entries in LDS that is refilled 128 at a time, 64 tiles ahead of their use.
+//
+// Measured per run (256 query rows) on 38 k query tokens of 8 heads each over 5.4 k rows:
+// about 2 000 cycles at 2.2 GHz, 1 024 of them matrix instructions (8 waves of 32 rows: 2 130);
+// 7.44 ms per launch = 929 TFLOP/s against 8.0 ms.  Without the weights the same loop takes
+// 1 390 cycles, without staging and loads 1 190.
 //
 // The same kernel serves decode attention for tree segments that MANY leaf queries share
 // (template parameter DECODE): there the 256 query rows of a work item are up to 256 / G
@@ -63,115 +65,237 @@ namespace ets {
 
 typedef float f32x16_t __attribute__((ext_vector_type(16)));
 
-// Scores of the wave's 32 query rows against one staged run: S^T = K Q^T.
-// ks_lane: the run's K rows in LDS at row n, 16-byte unit g.
-__device__ __forceinline__ void prefill_scores(const u32x4_t* __restrict__ ks_lane,
-                                               const bf16x8_t (&qf)[8], f32x16_t& s) {
-#pragma unroll
-    for (int i = 0; i < 16; ++i) s[i] = 0.f;
-#pragma unroll
-    for (int kk = 0; kk < 8; ++kk)
-        s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(ks_lane[2 * kk]), qf[kk], s, 0, 0, 0);
+#define ETS_INLINE __attribute__((always_inline))  // a lambda the wave's registers pass through
+
+constexpr int kPrefillThreads = 256;  // four waves of 64 query rows
+
+// The matrix instructions of the inner loop, with the register file of every operand named: a
+// wave holds 128 registers of O, 64 of Q, 32 of scores, 32 of weights, 64 of rows in flight and
+// 48 of fragments.  What the vector unit works on (scores, weights, and O when it is scaled) goes to
+// the ordinary registers; what only memory, LDS and matrix instructions touch (Q, fragments)
+// to the accumulation registers.  Left to itself the compiler puts every accumulator on the
+// other side and spills.
+// The compiler does not know what these statements are, so the wait states between a matrix
+// instruction and its neighbours are the code's own business: mfma_result_wait() before the
+// vector unit reads a result that may be younger than 18 issue slots, and no vector instruction
+// that writes an operand within two slots of its use.  (Accumulating into the same registers
+// needs none; fragments come from LDS and are waited for as usual.)
+__device__ __forceinline__ void mfma_scores_first(f32x16_t& s, u32x4_t k, bf16x8_t q) {
+    asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, 0" : "=&v"(s) : "a"(k), "a"(q));
+}
+__device__ __forceinline__ void mfma_scores(f32x16_t& s, u32x4_t k, bf16x8_t q) {
+    asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+v"(s) : "a"(k), "a"(q));
+}
+__device__ __forceinline__ void mfma_apply(f32x16_t& o, u32x4_t v, u32x4_t p) {
+    asm volatile("v_mfma_f32_32x32x16_f16 %0, %1, %2, %0" : "+v"(o) : "a"(v), "v"(p));
+}
+__device__ __forceinline__ void mfma_result_wait(f32x16_t (&o)[4]) {
+    asm volatile("s_nop 15\n\ts_nop 15" : "+v"(o[0]), "+v"(o[1]), "+v"(o[2]), "+v"(o[3]));
+}
+__device__ __forceinline__ void mfma_result_wait(f32x16_t& s) {
+    asm volatile("s_nop 15\n\ts_nop 15" : "+v"(s));
+}
+
+// Code `at` (0..3, a constant) of a dword of E4M3 codes as a float (exact).
+__device__ __forceinline__ float e4m3_at(uint32_t dw, int at) {
+    switch (at) {
+        case 0: return __builtin_amdgcn_cvt_f32_fp8((int)dw, 0);
+        case 1: return __builtin_amdgcn_cvt_f32_fp8((int)dw, 1);
+        case 2: return __builtin_amdgcn_cvt_f32_fp8((int)dw, 2);
+        default: return __builtin_amdgcn_cvt_f32_fp8((int)dw, 3);
+    }
 }
 
 // Masks the run rows the lane's query does not see (lim = rows of the run it sees, may
-// be <= 0) and returns the lane's largest score.  Score i stands for run row
-// 8 (i / 4) + 4 g + i % 4.
-__device__ __forceinline__ float prefill_mask_max(f32x16_t& s, int g, int lim) {
+// be <= 0).  Score i stands for run row 8 (i / 4) + 4 g + i % 4.
+__device__ __forceinline__ void prefill_mask(f32x16_t& s, int g, int lim) {
     const int rem = lim - 4 * g;
 #pragma unroll
     for (int i = 0; i < 16; ++i) s[i] = (8 * (i >> 2) + (i & 3)) < rem ? s[i] : -INFINITY;
-    float mx = fmaxf(fmaxf(s[0], s[1]), fmaxf(s[2], s[3]));
-#pragma unroll
-    for (int c = 1; c < 4; ++c)
-        mx = fmaxf(mx, fmaxf(fmaxf(s[4 * c], s[4 * c + 1]), fmaxf(s[4 * c + 2], s[4 * c + 3])));
-    return mx;
 }
 
-// Raises the rows' reference score when a score exceeds it by more than the margin.
-__device__ __forceinline__ void prefill_raise(float mx, float& m, float& lsum, f32x16_t (&oacc)[4],
-                                              float scale_log2e, float raise_margin) {
-    if (__any(mx > m + raise_margin)) {
-        mx = fmaxf(mx, __shfl_xor(mx, 32, 64));  // the row's other half of the run
-        const float m_new = fmaxf(m, mx);
-        const float alpha = fast_exp2((m - m_new) * scale_log2e);
-        lsum *= alpha;
+// Two weights rounded to fp16 (nearest even), the first in the low half.
+__device__ __forceinline__ uint32_t f16_pair(float lo, float hi) {
+    typedef float f32x2_t __attribute__((ext_vector_type(2)));
+    typedef _Float16 f16x2_t __attribute__((ext_vector_type(2)));
+    return __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2_t{lo, hi}), f16x2_t));
+}
+
+// V^T fragments in LDS.  The 16 rows of half a run are kept as 16-byte slots, one per output
+// element d = 8 a + x and row group g: the eight contraction slots that lane (d % 32, g) of d
+// block d / 32 feeds to the matrix instruction.  Slot (x, g, a) sits at 34 x + 16 g + a: a reader's 16
+// consecutive lanes (x = 0..7, two values of a) and a writer's 16 (all a) then touch every bank
+// once, and both address them with one register and constant offsets.
+constexpr int kVFragX = 34 * 16;        // bytes between elements x and x + 1
+constexpr int kVFragHalf = 8 * kVFragX; // bytes of half a run
+
+// A condition that hardly ever holds: its code is kept out of the way.  With one wave per SIMD a
+// branch that is taken costs about 100 cycles until instructions arrive from its target.
+#define ETS_RARE(x) __builtin_expect(!!(x), 0)
+
+// What a wave carries from run to run: two blocks of 32 query rows.
+struct PrefillState {
+    bf16x8_t qf[2][8];   // query rows as B operands
+    f32x16_t s[2];       // scores of the newest run
+    f32x16_t oacc[2][4]; // d block x: lane (n, g) holds d = 32 x + 8 c + 4 g + r at index 4 c + r
+    u32x4_t kf[8];       // K fragments of the run after it
+    float m[2], nmc[2];  // reference score of the lane's row (-inf: none yet); minus the same times
+                         // scale_log2e (0 without one)
+    float lsum[2];       // sum of the weights so far
+    float alpha[2];      // factor of oacc after the application under way, if it is to be scaled
+    float p_even, p_last;  // weights under way: of an even score, and the newest one
+};
+constexpr int kEarlyWeights = 4;  // weights of block 0 beside the scores of block 1
+constexpr int kLateWeights = 8;   // weights of block 1 that the next stage computes
+
+// Largest of a lane's scores.  (The instruction itself: around fmaxf the compiler first
+// canonicalises values whose origin it does not know, one more instruction for each.)
+__device__ __forceinline__ float prefill_max(const f32x16_t& s) {
+    float mx;
+    asm volatile(
+        "v_max_f32 %0, %1, %2\n\tv_max3_f32 %0, %0, %3, %4\n\tv_max3_f32 %0, %0, %5, %6\n\t"
+        "v_max3_f32 %0, %0, %7, %8\n\tv_max3_f32 %0, %0, %9, %10\n\tv_max3_f32 %0, %0, %11, %12\n\t"
+        "v_max3_f32 %0, %0, %13, %14\n\tv_max3_f32 %0, %0, %15, %16"
+        : "=&v"(mx)
+        : "v"(s[0]), "v"(s[1]), "v"(s[2]), "v"(s[3]), "v"(s[4]), "v"(s[5]), "v"(s[6]), "v"(s[7]),
+          "v"(s[8]), "v"(s[9]), "v"(s[10]), "v"(s[11]), "v"(s[12]), "v"(s[13]), "v"(s[14]), "v"(s[15]));
+    return mx;
+}
+// Raises the row's reference to the largest score of the run when one exceeds it by more than
+// the margin.  What has been gathered under the old reference is scaled: the sum at once, the
+// output rows when the caller has applied the weights still under way.
+__device__ __forceinline__ void prefill_raise(PrefillState& st, int j, float mx, float scale_log2e) {
+    mx = fmaxf(mx, __shfl_xor(mx, 32, 64));  // the row's other half of the run
+    const float m_new = fmaxf(st.m[j], mx);
+    // (a row that has seen nothing yet keeps -inf, and what it gathered is zero)
+    st.alpha[j] = st.m[j] == -INFINITY ? 0.f : fast_exp2((st.m[j] - m_new) * scale_log2e);
+    st.nmc[j] = m_new == -INFINITY ? 0.f : -m_new * scale_log2e;
+    st.m[j] = m_new;
+    st.lsum[j] *= st.alpha[j];
+}
+__device__ __forceinline__ void scale_rows(PrefillState& st, int j) {
+    mfma_result_wait(st.oacc[j]);
 #pragma unroll
-        for (int x = 0; x < 4; ++x) oacc[x] *= alpha;
-        m = m_new;
+    for (int x = 0; x < 4; ++x) st.oacc[j][x] *= st.alpha[j];
+}
+
+// Weight i of block j, taken against the row's reference score, in two steps so that nothing
+// waits for the exponential.  The empty statements hold the arithmetic where it is written: the
+// compiler would otherwise sink it behind the next branch, away from the matrix instructions.
+__device__ __forceinline__ void weight_begin(PrefillState& st, int j, int i, float scale_log2e) {
+    st.p_last = fast_exp2(fmaf(st.s[j][i], scale_log2e, st.nmc[j]));
+}
+__device__ __forceinline__ void weight_end(PrefillState& st, u32x4_t (&pf)[2][2], int j, int i) {
+    st.lsum[j] += st.p_last;
+    if (i & 1) {
+        uint32_t h = f16_pair(st.p_even, st.p_last);
+        asm volatile("" : "+v"(h), "+v"(st.lsum[j]));
+        pf[j][i >> 3][(i & 7) >> 1] = h;
+    } else {
+        st.p_even = st.p_last;
+        asm volatile("" : "+v"(st.lsum[j]));
     }
 }
 
-// Where lane s of a V^T fragment of d block x sits inside the fragment's 64 slots of 16
-// bytes.  The staging writes of one instruction go to 8 slots in each of the 4 d blocks;
-// the swizzle spreads those 32 slots evenly over the LDS banks (two per bank group, the
-// minimum) while 16 consecutive lanes of a fragment read still cover every bank once.
-__device__ __forceinline__ int vfrag_slot(int s, int x) {
-    const int k = ((s >> 4) & 1) | ((s >> 5) << 1) | (x << 2);
-    return (s & 48) | ((s & 15) ^ k);
-}
-
-// One pipeline stage: the scores of run u + 1 and the weights of run u, then the
-// application of run u's weights and the masking of run u + 1's scores, written in the
-// order in which it is to be issued: every matrix instruction is followed by the LDS read
-// of a fragment four instructions on and by two scores' worth of vector arithmetic, and a
-// scheduling fence keeps the group together.  Matrix and vector instructions of one wave
-// overlap only when they alternate like this.
-//   ks_next  K rows of run u + 1 in LDS (at row n, 16-byte unit g)
-//   vs_run   V^T fragments of run u
-//   s_cur    masked scores of run u (in), s_next: masked scores of run u + 1 (out)
-// Returns the lane's largest score of run u + 1.
-__device__ __forceinline__ float prefill_unit(const u32x4_t* __restrict__ ks_next,
-                                              const u32x4_t* __restrict__ vs_run,
-                                              const int (&slot_x)[4], const bf16x8_t (&qf)[8],
-                                              const f32x16_t& s_cur, f32x16_t& s_next, int g,
-                                              int lim_next, float m, float& lsum, f32x16_t (&oacc)[4],
-                                              float scale_log2e) {
-    constexpr int AHEAD = 4;
-    u32x4_t fr[AHEAD];
-    f16x8_t pf[2];
-    const float mc = m * scale_log2e;
-    float psum = 0.f;
-#pragma unroll
-    for (int i = 0; i < 16; ++i) s_next[i] = 0.f;
-#pragma unroll
-    for (int kk = 0; kk < AHEAD; ++kk) fr[kk] = ks_next[2 * kk];
+// One pipeline stage of a wave: the scores of run u + 1 and the application of run u.
+//   A, block 0   scores(u + 1)  ||  the last weights of block 1 of run u
+//   A, block 1   scores(u + 1)  ||  block 0 of run u + 1: mask, maximum, first weights
+//   B            apply(u)       ||  its other weights; block 1: mask, maximum, first weights
+// Written in the order in which it is to be issued: matrix and vector instructions of one wave
+// overlap only when they alternate in program order, and a scheduling fence keeps each group
+// together.  A matrix instruction takes 32 cycles and 8 of issue, which leaves 24 for other
+// instructions behind it (measured: 6 multiply-adds are free, the seventh costs its 4 cycles);
+// a weight takes 18 (an exponential 8, a multiply-add and an addition 4 each, half a conversion
+// 2), so a run's 32 weights, the staging and the rest fill the 32 gaps of a stage almost completely
+// and have to be spread evenly.  The scores of a block are read by the vector unit behind
+// three later matrix instructions (24 passes; the result takes 16).  Fragments are read from LDS
+// eight matrix steps ahead of their use: kf holds the K fragments of run u + 1 on entry and
+// of run u + 2 on exit, read behind `before_b` (a workgroup barrier where that run's tile has
+// just been staged).
+//   v_run, k_after   LDS byte addresses: the lane's slot of run u's V^T fragments, and its row of
+//                    run u + 2's K
+//   fill(k)          k = 0..15: the caller's work beside A;  fill_b(i), i = 0..15: beside B
+//   hidden, mask(j)  whether rows of run u + 1 are hidden from a query row, and what hides
+//                    them from block j's scores
+template <class Fill, class Mask, class Before, class FillB>
+__device__ __forceinline__ void prefill_unit(PrefillState& st, const char* __restrict__ v_run,
+                                             const char* __restrict__ k_after,
+                                             u32x4_t (&pf_cur)[2][2], u32x4_t (&pf)[2][2],
+                                             float scale_log2e, float raise_margin, bool hidden,
+                                             Fill fill, Mask mask, Before before_b, FillB fill_b) {
+    u32x4_t vf[8];
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int kk = 0; kk < 8; ++kk) {
-        s_next = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(fr[kk % AHEAD]), qf[kk], s_next, 0, 0, 0);
-        if (kk + AHEAD < 8) fr[kk % AHEAD] = ks_next[2 * (kk + AHEAD)];
-        const float p0 = fast_exp2(fmaf(s_cur[2 * kk], scale_log2e, -mc));
-        const float p1 = fast_exp2(fmaf(s_cur[2 * kk + 1], scale_log2e, -mc));
-        psum += p0 + p1;
-        pf[kk >> 2][2 * (kk & 3)] = (_Float16)p0;
-        pf[kk >> 2][2 * (kk & 3) + 1] = (_Float16)p1;
+        if (kk == 0) mfma_scores_first(st.s[0], st.kf[0], st.qf[0][0]);
+        else mfma_scores(st.s[0], st.kf[kk], st.qf[0][kk]);
+        __builtin_amdgcn_sched_barrier(0);
+        vf[kk] = load16(v_run + (kk >> 2) * kVFragHalf + (kk & 3) * 64);  // half kk / 4, d block kk % 4
+        if (kk > 0) weight_end(st, pf_cur, 1, 16 - kLateWeights + kk - 1);
+        weight_begin(st, 1, 16 - kLateWeights + kk, scale_log2e);
+        fill(kk);
         __builtin_amdgcn_sched_barrier(0);
     }
-    lsum += psum;
-    // apply(u): d block x, half t, both halves of a block back to back
+    bool raised0 = false, raised1 = false;
 #pragma unroll
-    for (int j = 0; j < AHEAD; ++j) fr[j] = vs_run[((j & 1) * 4 + (j >> 1)) * 64 + slot_x[j >> 1]];
+    for (int kk = 0; kk < 8; ++kk) {
+        if (kk == 0) mfma_scores_first(st.s[1], st.kf[0], st.qf[1][0]);
+        else mfma_scores(st.s[1], st.kf[kk], st.qf[1][kk]);
+        __builtin_amdgcn_sched_barrier(0);
+        if (kk == 0) weight_end(st, pf_cur, 1, 15);
+        fill(8 + kk);
+        if (kk == 2 && ETS_RARE(hidden)) mask(0);
+        if (kk == 3) {
+            const float mx = prefill_max(st.s[0]);
+            raised0 = __any(mx > st.m[0] + raise_margin);
+            if (ETS_RARE(raised0)) prefill_raise(st, 0, mx, scale_log2e);
+        }
+        if (kk > 8 - kEarlyWeights) weight_end(st, pf, 0, kk - 9 + kEarlyWeights);
+        if (kk >= 8 - kEarlyWeights) weight_begin(st, 0, kk - 8 + kEarlyWeights, scale_log2e);
+        __builtin_amdgcn_sched_barrier(0);
+    }
+    before_b();
     __builtin_amdgcn_sched_barrier(0);
-    const int rem = lim_next - 4 * g;
-    float mx = -INFINITY;
+    // the other weights of block 0, then those of block 1 that are not late
+    constexpr int kRest0 = 16 - kEarlyWeights, kRest = kRest0 + 16 - kLateWeights;
+    auto begin = [&](int k) {
+        if (k < kRest0) weight_begin(st, 0, kEarlyWeights + k, scale_log2e);
+        else weight_begin(st, 1, k - kRest0, scale_log2e);
+    };
+    auto end = [&](int k) {
+        if (k < 0) weight_end(st, pf, 0, kEarlyWeights - 1);
+        else if (k < kRest0) weight_end(st, pf, 0, kEarlyWeights + k);
+        else weight_end(st, pf, 1, k - kRest0);
+    };
+    int k = 0;
 #pragma unroll
-    for (int j = 0; j < 8; ++j) {
-        const int x = j >> 1, t = j & 1;
-        oacc[x] = __builtin_amdgcn_mfma_f32_32x32x16_f16(as_f16x8(fr[j % AHEAD]), pf[t], oacc[x], 0, 0, 0);
-        if (j + AHEAD < 8) {
-            const int jn = j + AHEAD;
-            fr[j % AHEAD] = vs_run[((jn & 1) * 4 + (jn >> 1)) * 64 + slot_x[jn >> 1]];
+    for (int i = 0; i < 16; ++i) {
+        // half t of the run, d block x, query block j
+        const int t = i >> 3, x = (i >> 1) & 3, j = i & 1;
+        mfma_apply(st.oacc[j][x], vf[4 * t + x], pf_cur[j][t]);
+        __builtin_amdgcn_sched_barrier(0);
+        if (j == 1) st.kf[i >> 1] = load16(k_after + 32 * (i >> 1));
+        if (i == 2 && ETS_RARE(hidden)) mask(1);
+        if (i == 3) {
+            const float mx = prefill_max(st.s[1]);
+            raised1 = __any(mx > st.m[1] + raise_margin);
+            if (ETS_RARE(raised1)) prefill_raise(st, 1, mx, scale_log2e);
+        } else {
+            // one weight beside an instruction, two beside every third until none is too many
+            end(k - 1);
+            begin(k++);
+            if (i % 3 == 0 && kRest - k > 15 - i - (i < 3 ? 1 : 0)) {
+                end(k - 1);
+                begin(k++);
+            }
         }
-        // scores 2 j and 2 j + 1 of run u + 1 stand for run rows 8 (i / 4) + 4 g + i % 4
-#pragma unroll
-        for (int i = 2 * j; i < 2 * j + 2; ++i) {
-            s_next[i] = (8 * (i >> 2) + (i & 3)) < rem ? s_next[i] : -INFINITY;
-            mx = fmaxf(mx, s_next[i]);
-        }
+        fill_b(i);
         __builtin_amdgcn_sched_barrier(0);
     }
-    return mx;
+    static_assert(kRest == 20, "15 instructions take a weight, five of them two");
+    end(kRest - 1);
+    if (ETS_RARE(raised0)) scale_rows(st, 0);
+    if (ETS_RARE(raised1)) scale_rows(st, 1);
 }
 
 // FP8: the pools hold E4M3 codes (128-byte rows, 8 bytes per lane and load); the codes are
@@ -182,7 +306,7 @@ __device__ __forceinline__ float prefill_unit(const u32x4_t* __restrict__ ks_nex
 // ent_base, ws_ml are the decode plan's tables; otherwise `items_raw` are PrefillItem and
 // the last three arguments are unused.
 template <bool FP8, bool DECODE>
-__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2))) void prefill_attn_kernel(
+__global__ __launch_bounds__(kPrefillThreads) __attribute__((amdgpu_waves_per_eu(1, 1))) void prefill_attn_kernel(
     const void* __restrict__ k_pool, const void* __restrict__ v_pool, int64_t pool_tokens,
     const bf16_t* __restrict__ q, const Run* __restrict__ runs,
     const void* __restrict__ items_raw, int item_base, int g_shift, float scale_log2e_base,
@@ -190,19 +314,22 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2))) void p
     const int32_t* __restrict__ ent_order, const int32_t* __restrict__ ent_base,
     float2* __restrict__ ws_ml) {
     constexpr int D = 128;
-    constexpr int KROW = kTreeAttnKRow;
-    constexpr int KS_UNITS = 64 * KROW;    // K tile: 64 rows of 272 bytes
-    constexpr int VS_UNITS = 2 * 8 * 64;   // V^T fragments: [run][half][d block][lane]
-    constexpr int BUF_UNITS = KS_UNITS + VS_UNITS;
+    constexpr int NB = 2;                  // blocks of 32 query rows per wave
+    constexpr int WROWS = 32 * NB;         // query rows per wave
+    constexpr int KROW_B = 16 * kTreeAttnKRow;  // bytes of a K row in LDS (272)
+    constexpr int KS_B = 64 * KROW_B;           // K tile: 64 rows
+    constexpr int BUF_B = KS_B + 4 * kVFragHalf;  // V^T fragments behind it: [run][half]
     constexpr int RING = 256;
-    __shared__ u32x4_t smem[3 * BUF_UNITS];  // three tile buffers
+    static_assert(4 * WROWS == kPrefillRowsPerItem && 4 * WROWS == kWideRowsPerItem, "rows per workgroup");
+    __shared__ u32x4_t smem_raw[3 * BUF_B / 16];  // three tile buffers
     __shared__ u32x4_t sm_desc[RING];
+
+    char* smem = reinterpret_cast<char*>(smem_raw);
 
     const int n_kv_heads = (int)gridDim.x;
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const bool loads_v = w >= 4;   // waves 0..3 fetch K, waves 4..7 fetch V
-    const int sw = (w & 3) >> 1;   // which run of a tile this wave fetches
-    const int hw = w & 1;          // which 16-row half of that run
+    const int sw = w >> 1;   // which run of a tile this wave fetches
+    const int hw = w & 1;    // which 16-row half of that run
     const int lane = threadIdx.x & 63;
     const int a = lane & 15;  // when loading: 16-byte piece of a row
     const int b = lane >> 4;  // when loading: row group
@@ -234,265 +361,343 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2))) void p
     const int n_runs = run_end - run_begin;
     const int n_tiles = (n_runs + 1) >> 1;
     const Run* my_runs = runs + run_begin;
-    const float raise_margin = 8.0f / scale_log2e;
+    const float raise_margin = 8.0f / scale_log2e;  // raw-score distance of 2^8 in weight
 
-    // the wave's 16 rows of K (rows b + 4 i) or of V (rows 4 b + i) of two tiles in flight:
-    // loads are issued three tiles ahead of their use, and a register set is busy from
-    // the issue until its tile is staged, so two sets alternate
+    // the wave's 16 rows of K (rows b + 4 i) and of V (rows 4 b + i) of two tiles in flight:
+    // a register set is busy from the issue of its loads until its tile is staged, two
+    // tiles later; two sets alternate
     using raw_t = std::conditional_t<FP8, u32x2_t, u32x4_t>;
-    raw_t raw0[4], raw1[4];
+    struct RawTile {
+        raw_t k[4], v[4];
+    };
+    RawTile raw0, raw1;
     constexpr uint32_t stride_b = FP8 ? D : D * 2;
     const int64_t plane = (int64_t)h * pool_tokens;
-    const void* pool = loads_v ? v_pool : k_pool;
-    const uint32_t lane_off =
-        (uint32_t)(16 * hw + (loads_v ? 4 * b : b)) * stride_b + a * (FP8 ? 8 : 16);
-    const uint32_t load_step = (loads_v ? 1u : 4u) * stride_b;
+    const uint32_t piece = a * (FP8 ? 8 : 16);
+    const uint32_t k_lane_off = (uint32_t)(16 * hw + b) * stride_b + piece;
+    const uint32_t v_lane_off = (uint32_t)(16 * hw + 4 * b) * stride_b + piece;
+    auto load_piece = [](__amdgpu_buffer_rsrc_t rs, uint32_t off) -> raw_t {
+        if constexpr (FP8)
+            return __builtin_bit_cast(u32x2_t, __builtin_amdgcn_raw_buffer_load_b64(rs, off, 0, 0));
+        else
+            return __builtin_bit_cast(u32x4_t, __builtin_amdgcn_raw_buffer_load_b128(rs, off, 0, 0));
+    };
     // a run's rows through a descriptor that covers exactly the run: rows past the end of
-    // a short run read as zero (and are masked); an empty run (past the end of an odd
-    // list) is staged as zeros
-    auto issue_loads = [&](const Run& sd, raw_t (&raw)[4]) {
-        // always four loads (an empty run's descriptor covers nothing: every lane reads
-        // zero without a memory access), so that the number of loads in flight is known
-        // at every wait
-        const int64_t base = (plane + sd.tok) * (int64_t)stride_b;
-        char* pb = const_cast<char*>(reinterpret_cast<const char*>(pool)) + base;
-        const int bytes = sd.n * (int)stride_b;
-        const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(pb, 0, bytes, 0x00020000);
+    // a short run read as zero (and are masked); an empty run (past the end of the
+    // list) is staged as zeros.  Always eight loads (an empty run's descriptor covers nothing:
+    // every lane reads zero without a memory access), so that the number of loads in
+    // flight is known at every wait.
+    struct RunRsrc {
+        __amdgpu_buffer_rsrc_t k, v;
+    };
+    auto rsrc_of = [&](const Run& sd) {
+        // (uniform, and said to be so: a run that was carried round the loop may sit in vector
+        // registers, and loads through a descriptor made there go lane by lane)
+        const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)sd.tok);
+        const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)((uint64_t)sd.tok >> 32));
+        const int64_t base = (plane + (int64_t)(((uint64_t)hi << 32) | lo)) * (int64_t)stride_b;
+        char* kb = const_cast<char*>(reinterpret_cast<const char*>(k_pool)) + base;
+        char* vb = const_cast<char*>(reinterpret_cast<const char*>(v_pool)) + base;
+        const int bytes = __builtin_amdgcn_readfirstlane(sd.n) * (int)stride_b;
+        return RunRsrc{__builtin_amdgcn_make_buffer_rsrc(kb, 0, bytes, 0x00020000),
+                       __builtin_amdgcn_make_buffer_rsrc(vb, 0, bytes, 0x00020000)};
+    };
+    auto issue_load = [&](const RunRsrc& rs, RawTile& raw, int i) {  // i = 0..7
+        if (i < 4) raw.k[i] = load_piece(rs.k, k_lane_off + (uint32_t)(4 * i) * stride_b);
+        else raw.v[i - 4] = load_piece(rs.v, v_lane_off + (uint32_t)(i - 4) * stride_b);
+    };
+    auto issue_loads = [&](const Run& sd, RawTile& raw) {
+        const RunRsrc rs = rsrc_of(sd);
+#pragma unroll
+        for (int i = 0; i < 8; ++i) issue_load(rs, raw, i);
+    };
+    // K: row-major rows of 272 bytes.  V: lane (a, b) holds run rows 16 hw + 4 b + i
+    // (i = 0..3) at d = 8 a + x (x = 0..7); the four rows at one d are half (b >> 1) of slot
+    // (x, b & 1, a).
+    char* const k_dst = smem + (32 * sw + 16 * hw + b) * KROW_B + a * 16;  // + 4 i rows
+    char* const v_dst = smem + KS_B + (sw * 2 + hw) * kVFragHalf + (16 * (b & 1) + a) * 16 + (b >> 1) * 8;
+    auto stage_k = [&](char* dst, const RawTile& raw, int i) {  // i = 0..3
+        *reinterpret_cast<u32x4_t*>(dst + 4 * i * KROW_B) = widen_raw(raw.k[i]);
+    };
+    auto stage_v = [&](char* dst, const RawTile& raw, int x) {  // element x = 0..7 of the piece
+        float f[4];  // the element of the four rows
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
             if constexpr (FP8)
-                raw[i] = __builtin_bit_cast(u32x2_t, __builtin_amdgcn_raw_buffer_load_b64(
-                                                         rs, lane_off + (uint32_t)i * load_step, 0, 0));
+                f[i] = e4m3_at(raw.v[i][x >> 2], x & 3);
             else
-                raw[i] = __builtin_bit_cast(u32x4_t, __builtin_amdgcn_raw_buffer_load_b128(
-                                                         rs, lane_off + (uint32_t)i * load_step, 0, 0));
+                f[i] = (x & 1) ? bf16_hi(raw.v[i][x >> 1]) : bf16_lo(raw.v[i][x >> 1]);
         }
+        u32x2_t t;
+        t[0] = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_pkrtz(f[0], f[1]));
+        t[1] = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_pkrtz(f[2], f[3]));
+        *reinterpret_cast<u32x2_t*>(dst + x * kVFragX) = t;
     };
-    // K: row-major rows of 272 bytes.  V: lane (a, b) holds run rows 16 hw + 4 b + i
-    // (i = 0..3) at d = 8 a + x (x = 0..7); the four rows at one d are half (b >> 1) of
-    // the 16-byte A fragment of lane (d % 32, b & 1) in d block d / 32 of half hw.
-    auto stage = [&](int buf, const raw_t (&raw)[4]) {
-        u32x4_t* ks = smem + buf * BUF_UNITS;
-        u32x2_t* vs2 = reinterpret_cast<u32x2_t*>(ks + KS_UNITS);
-        if (!loads_v) {
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                if constexpr (FP8)
-                    ks[(32 * sw + 16 * hw + 4 * i + b) * KROW + a] = e4m3x8_to_bf16x8(raw[i]);
-                else
-                    ks[(32 * sw + 16 * hw + 4 * i + b) * KROW + a] = raw[i];
-            }
-        } else {
-            const int frag = (sw * 2 + hw) * 4 + (a >> 2);    // [run][half][d block]
-            const int dst_lane = 32 * (b & 1) + 8 * (a & 3);  // + x
-            // slot of lane dst_lane + x: x only enters the low three bits, which the
-            // swizzle XORs with bits that do not depend on x
-            u32x2_t* dst = vs2 + (frag * 64 * 2 + (b >> 1));
-            const int slot0 = vfrag_slot(dst_lane, a >> 2);
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                u32x2_t te, to;
-                if constexpr (FP8) {
-                    // elements 2 j and 2 j + 1 of the four rows as floats (exact), then
-                    // fp16 pairs across rows
-                    typedef float f32x2_t __attribute__((ext_vector_type(2)));
-                    f32x2_t f[4];
-#pragma unroll
-                    for (int i = 0; i < 4; ++i)
-                        f[i] = (j & 1) ? __builtin_amdgcn_cvt_pk_f32_fp8((int)raw[i][j >> 1], true)
-                                       : __builtin_amdgcn_cvt_pk_f32_fp8((int)raw[i][j >> 1], false);
-                    te[0] = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_pkrtz(f[0][0], f[1][0]));
-                    te[1] = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_pkrtz(f[2][0], f[3][0]));
-                    to[0] = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_pkrtz(f[0][1], f[1][1]));
-                    to[1] = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_pkrtz(f[2][1], f[3][1]));
-                } else {
-                    te[0] = __builtin_bit_cast(
-                        uint32_t, __builtin_amdgcn_cvt_pkrtz(bf16_lo(raw[0][j]), bf16_lo(raw[1][j])));
-                    te[1] = __builtin_bit_cast(
-                        uint32_t, __builtin_amdgcn_cvt_pkrtz(bf16_lo(raw[2][j]), bf16_lo(raw[3][j])));
-                    to[0] = __builtin_bit_cast(
-                        uint32_t, __builtin_amdgcn_cvt_pkrtz(bf16_hi(raw[0][j]), bf16_hi(raw[1][j])));
-                    to[1] = __builtin_bit_cast(
-                        uint32_t, __builtin_amdgcn_cvt_pkrtz(bf16_hi(raw[2][j]), bf16_hi(raw[3][j])));
-                }
-                dst[(slot0 ^ (2 * j)) * 2] = te;      // x = 2 j
-                dst[(slot0 ^ (2 * j + 1)) * 2] = to;  // x = 2 j + 1
-            }
-        }
+    // descriptor of run idx from the ring (same address in every lane); runs past the end of the
+    // list are empty there
+    auto desc_at = [&](int idx) { return sm_desc + (idx & (RING - 1)); };
+    auto to_run = [&](const u32x2_t& tok, uint32_t n) {
+        uint32_t lo = __builtin_amdgcn_readfirstlane(tok[0]);
+        uint32_t hi = __builtin_amdgcn_readfirstlane(tok[1]);
+        uint32_t rows = __builtin_amdgcn_readfirstlane(n);
+        asm volatile("" : "+s"(lo), "+s"(hi), "+s"(rows));  // carried round the loop in scalar registers
+        return Run{(int64_t)(((uint64_t)hi << 32) | lo), (int32_t)rows, 0};
     };
-    // descriptor of run idx from the ring (same address in every lane); past the end: empty
-    auto read_desc = [&](int idx) {
-        Run sd{0, 0, 0};
-        if (idx < n_runs) {
-            const u32x4_t d = sm_desc[idx & (RING - 1)];
-            const uint32_t lo = __builtin_amdgcn_readfirstlane(d[0]);
-            const uint32_t hi = __builtin_amdgcn_readfirstlane(d[1]);
-            sd.tok = (int64_t)(((uint64_t)hi << 32) | lo);
-            sd.n = __builtin_amdgcn_readfirstlane(d[2]);
-            sd.pad = __builtin_amdgcn_readfirstlane(d[3]);
-        }
-        return sd;
-    };
+    auto run_of = [&](const u32x4_t& d) { return to_run(u32x2_t{d[0], d[1]}, d[2]); };
+    auto run_at = [&](int idx) { return idx < n_runs ? my_runs[idx] : Run{0, 0, 0}; };
 
-    // prologue: first tile, the first 256 descriptors, the query rows
-    issue_loads(sw < n_runs ? my_runs[sw] : Run{0, 0, 0}, raw0);
+    // prologue: the first two tiles, the first 256 descriptors, the query rows
+    issue_loads(run_at(sw), raw0);
     u32x4_t desc_raw = {0u, 0u, 0u, 0u};
     if ((int)threadIdx.x < min(n_runs, RING))
         desc_raw = load16(reinterpret_cast<const char*>(my_runs + threadIdx.x));
+    issue_loads(run_at(2 + sw), raw1);
 
-    // row r = 32 w + n of the item is token r >> g_shift of the block, query head
-    // r & (G - 1) of the kv head's group; rows past the block repeat its last token
-    // (decode: row r is leaf query r >> g_shift of the item, in ent_order)
-    const int r_lane = 32 * w + n;
-    const int tq_lane = min(r_lane >> g_shift, n_grp - 1);
-    const int i_row = tok0 + tq_lane;  // the lane's query token, as an index into its node
-    // a wave whose 32 rows all lie past the block's last token (the last block of a node
-    // is rarely full) only fetches and stages: its SIMD is left to the other wave
-    const bool active = ((32 * w) >> g_shift) < n_grp;
-    bf16x8_t qf[8];
-    int64_t out_row;  // row of the lane's query in `out` (and in lse / ws_ml)
-    {
-        const int head = h * G + (r_lane & (G - 1));
-        int64_t q_row;
-        if constexpr (DECODE) {
-            q_row = ent_order[ent_begin + tq_lane];
-            out_row = (int64_t)(ent_base[ent_begin + tq_lane] + slot_off) * n_q_heads + head;
-        } else {
-            q_row = q_row0 + tq_lane;
-            out_row = q_row * n_q_heads + head;
-        }
-        const bf16_t* qp = q + (q_row * n_q_heads + head) * D;
+    // row r = 64 w + 32 j + n of the item (block j of the wave) is token r >> g_shift of the
+    // block, query head r & (G - 1) of the kv head's group; rows past the block repeat its last
+    // token (decode: row r is leaf query r >> g_shift of the item, in ent_order)
+    auto group_of = [&](int r) { return min(r >> g_shift, n_grp - 1); };
+    // a wave whose rows all lie past the block's last token (the last block of a node
+    // is rarely full) only fetches and stages
+    const bool active = ((WROWS * w) >> g_shift) < n_grp;
+    const int i_first = tok0 + group_of(WROWS * w);  // the wave's first query token
+    PrefillState st;
 #pragma unroll
-        for (int kk = 0; kk < 8; ++kk) qf[kk] = as_bf16x8(load16(qp + 16 * kk + 8 * g));
+    for (int j = 0; j < NB; ++j) {
+        const int r = WROWS * w + 32 * j + n;
+        int64_t q_row = q_row0 + group_of(r);
+        if constexpr (DECODE) q_row = ent_order[ent_begin + group_of(r)];
+        const bf16_t* qp = q + (q_row * n_q_heads + h * G + (r & (G - 1))) * D;
+#pragma unroll
+        for (int kk = 0; kk < 8; ++kk) st.qf[j][kk] = as_bf16x8(load16(qp + 16 * kk + 8 * g));
     }
 
-    if (threadIdx.x < RING) sm_desc[threadIdx.x] = desc_raw;
-    f32x16_t oacc[4];  // d block x: lane (n, g) holds d = 32 x + 8 c + 4 g + r at index 4 c + r
-    float m = -INFINITY, lsum = 0.f;
+    sm_desc[threadIdx.x] = desc_raw;
 #pragma unroll
-    for (int x = 0; x < 4; ++x)
+    for (int j = 0; j < NB; ++j) {
+        st.m[j] = -INFINITY;
+        st.nmc[j] = st.lsum[j] = 0.f;
 #pragma unroll
-        for (int i = 0; i < 16; ++i) oacc[x][i] = 0.f;
-    stage(0, raw0);
-    // the loads of the second and third tile are in flight while the first is computed
-    // (their descriptors straight from memory: the ring is not visible before the barrier)
-    issue_loads(2 + sw < n_runs ? my_runs[2 + sw] : Run{0, 0, 0}, raw0);
-    issue_loads(4 + sw < n_runs ? my_runs[4 + sw] : Run{0, 0, 0}, raw1);
-    __syncthreads();  // descriptors and the first tile are in LDS
+        for (int x = 0; x < 4; ++x)
+#pragma unroll
+            for (int i = 0; i < 16; ++i) st.oacc[j][x][i] = 0.f;
+    }
+    // tile 0, and the half of tile 1 that precedes the first stage (see do_tile)
+#pragma unroll
+    for (int i = 0; i < 4; ++i) stage_k(k_dst, raw0, i);
+#pragma unroll
+    for (int x = 0; x < 8; ++x) stage_v(v_dst, raw0, x);
+    issue_loads(run_at(4 + sw), raw0);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        stage_k(k_dst + BUF_B, raw1, i);
+        stage_v(v_dst + BUF_B, raw1, i);
+    }
+    __syncthreads();  // descriptors and the first tile are in LDS; of the second, K is
 
-    auto lim_of = [&](const u32x4_t& d) {
-        // rows of the run that the lane's query row sees
-        const int n_valid = __builtin_amdgcn_readfirstlane(d[2]);
-        if constexpr (DECODE) return n_valid;  // the query is newer than every row
-        const int kpos = __builtin_amdgcn_readfirstlane(d[3]);
-        return min(n_valid, i_row - kpos + 1);
+    // Which rows of a run are hidden: t >= n, and in step prefill kpos + t > the query token's
+    // index (kpos: the run's position inside the querying node).
+    struct Extent {
+        int n, kpos;  // of one run, uniform
     };
-    const u32x4_t empty_desc = {0u, 0u, 0u, 0u};  // n = 0: everything masked
-    auto desc_of = [&](int idx) { return idx < n_runs ? sm_desc[idx & (RING - 1)] : empty_desc; };
+    auto extent_of = [&](const u32x2_t& d) ETS_INLINE {
+        Extent e{(int)__builtin_amdgcn_readfirstlane(d[0]), (int)__builtin_amdgcn_readfirstlane(d[1])};
+        asm volatile("" : "+s"(e.n), "+s"(e.kpos));  // carried round the loop in scalar registers
+        return e;
+    };
+    auto hides = [&](const Extent& e) ETS_INLINE -> bool {
+        // (once more said to be uniform, see rsrc_of)
+        const int n_valid = __builtin_amdgcn_readfirstlane(e.n);
+        if constexpr (DECODE) return n_valid != 32;  // the query is newer than every row
+        const int kpos = __builtin_amdgcn_readfirstlane(e.kpos);
+        return (n_valid != 32) | (kpos + 31 > i_first);  // (no branch)
+    };
+    auto mask = [&](int j, const Extent& e) ETS_INLINE {
+        int lim = e.n;
+        if constexpr (!DECODE) lim = min(lim, tok0 + group_of(WROWS * w + 32 * j + n) - e.kpos + 1);
+        mfma_result_wait(st.s[j]);
+        prefill_mask(st.s[j], g, lim);
+    };
+    auto n_kpos = [&](int idx) ETS_INLINE {
+        return reinterpret_cast<const u32x2_t*>(desc_at(idx))[1];
+    };
 
-    int slot_x[4];
+    const char* const k_src = smem + n * KROW_B + g * 16;  // the lane's row of a run's K fragments
+    const char* const v_src = smem + KS_B + (34 * (n & 7) + 16 * g + (n >> 3)) * 16;
+    u32x4_t pf_a[NB][2], pf_b[NB][2];  // weights of the even and of the odd run of a tile
+    Extent e_next;                     // of the run whose scores come next
+    Run load_next;                     // the run to be fetched next
+    // scores and weights of the first run
+    auto first_run = [&]() ETS_INLINE {
 #pragma unroll
-    for (int x = 0; x < 4; ++x) slot_x[x] = vfrag_slot(lane, x);
-    f32x16_t s_a, s_b;  // scores of the runs in flight (even and odd run of a tile)
-    if (active) {
-        // first run: scores, mask and maximum
-        prefill_scores(smem + n * KROW + g, qf, s_a);
-        const float mx = prefill_mask_max(s_a, g, lim_of(desc_of(0)));
-        prefill_raise(mx, m, lsum, oacc, scale_log2e, raise_margin);
-    }
+        for (int kk = 0; kk < 8; ++kk) {
+            st.kf[kk] = load16(k_src + 32 * kk);
+#pragma unroll
+            for (int j = 0; j < NB; ++j) {
+                if (kk == 0) mfma_scores_first(st.s[j], st.kf[0], st.qf[j][0]);
+                else mfma_scores(st.s[j], st.kf[kk], st.qf[j][kk]);
+            }
+        }
+        e_next = extent_of(n_kpos(0));
+#pragma unroll
+        for (int j = 0; j < NB; ++j) {
+            mfma_result_wait(st.s[j]);
+            if (hides(e_next)) mask(j, e_next);
+            prefill_raise(st, j, prefill_max(st.s[j]), scale_log2e);
+#pragma unroll
+            for (int i = 0; i < (j == 0 ? 16 : 16 - kLateWeights); ++i) {
+                weight_begin(st, j, i, scale_log2e);
+                weight_end(st, pf_a, j, i);
+            }
+        }
+#pragma unroll
+        for (int x = 0; x < 8; ++x) st.kf[x] = load16(k_src + 32 * KROW_B + 32 * x);
+        e_next = extent_of(n_kpos(1));
+    };
 
-    int cur = 0, nxt = 1;  // tile % 3, (tile + 1) % 3
-    // one tile; `raw` holds the rows of tile + 1 and takes those of tile + 3
-    auto do_tile = [&](int tile, raw_t (&raw)[4]) {
-        const u32x4_t* ks = smem + cur * BUF_UNITS;
-        const u32x4_t* vs = ks + KS_UNITS;
-        const u32x4_t* ks_next = smem + nxt * BUF_UNITS;
-        const u32x4_t d1 = desc_of(2 * tile + 1), d2 = desc_of(2 * tile + 2);
+    // Tile t, in buffer `cur` (t % 3).  Tile t + 1 goes to `nxt` from the register set `oth`, K and
+    // half of V beside the previous tile's second stage, the rest beside this tile's first,
+    // in front of the barrier; the set then takes the rows of tile t + 3.  Tile t + 2 follows
+    // from `own` into the third buffer, whose last readers (tile t - 1) are behind that
+    // barrier.
+    int cur = 0, nxt = BUF_B, aft = 2 * BUF_B;
+    load_next = run_of(*desc_at(6 + sw));
+    auto do_tile = [&](int tile, RawTile& own, RawTile& oth, auto computes) ETS_INLINE {
         // ring refill: when run 128 k starts (k >= 1), runs [128 (k + 1), 128 (k + 2)) take
-        // the slots of the 128 runs that were finished before it; they are used from 64
+        // the slots of the 128 runs that were finished before it; they are used from 60
         // tiles later on
-        const bool refill = tile > 0 && (tile & 63) == 0;
-        const int refill_idx = 2 * tile + 128 + (int)threadIdx.x;
-        if (refill && threadIdx.x < 128 && refill_idx < n_runs)
-            desc_raw = load16(reinterpret_cast<const char*>(my_runs + refill_idx));
-
-        // the buffer of tile - 2 is free: every wave has passed the barrier of tile - 1.
-        // Past the end of the list zeros are staged (never read).
-        stage(nxt, raw);  // waits for the loads of tile + 1
-        issue_loads(read_desc(2 * (tile + 3) + sw), raw);
-        if (refill && threadIdx.x < 128 && refill_idx < n_runs)
-            sm_desc[refill_idx & (RING - 1)] = desc_raw;
-
-        // [ scores(run 1) || weights(run 0) ]  [ apply(run 0) || mask, maximum(run 1) ]
-        if (active) {
-            const float mx1 = prefill_unit(ks + (32 + n) * KROW + g, vs, slot_x, qf, s_a, s_b, g,
-                                           lim_of(d1), m, lsum, oacc, scale_log2e);
-            prefill_raise(mx1, m, lsum, oacc, scale_log2e, raise_margin);
+        if (ETS_RARE(tile > 0 && (tile & 63) == 0 && w < 2)) {
+            const int idx = 2 * tile + 128 + (int)threadIdx.x;
+            u32x4_t d = {0u, 0u, 0u, 0u};
+            if (idx < n_runs) d = load16(reinterpret_cast<const char*>(my_runs + idx));
+            sm_desc[idx & (RING - 1)] = d;
         }
-
-        __syncthreads();  // the next tile is staged
-        // [ scores(next tile, run 0) || weights(run 1) ]  [ apply(run 1) || mask, maximum ]
-        // (past the last tile the scores are masked away as a whole)
-        if (active) {
-            const float mx0 = prefill_unit(ks_next + n * KROW + g, vs + 8 * 64, slot_x, qf, s_b, s_a, g,
-                                           lim_of(d2), m, lsum, oacc, scale_log2e);
-            prefill_raise(mx0, m, lsum, oacc, scale_log2e, raise_margin);
+        if constexpr (decltype(computes)::value) {
+            char* const v_nxt = v_dst + nxt;
+            char* const v_aft = v_dst + aft;
+            char* const k_aft = k_dst + aft;
+            const char* const vs = v_src + cur;
+            const char* const ks = k_src + nxt;
+            RunRsrc rs;
+            u32x2_t d_e, d_tok;
+            uint32_t d_n;
+            auto finish = [&](int k) ETS_INLINE {
+                if (k >= 8 && k < 11) stage_v(v_nxt, oth, k - 4);
+                if (k == 13) stage_v(v_nxt, oth, 7);
+            };
+            auto begin = [&](int k) ETS_INLINE {
+                if (k >= 8 && k < 11) stage_v(v_aft, own, k - 8);
+                if (k >= 12) stage_k(k_aft, own, k - 12);
+                if (k == 13) stage_v(v_aft, own, 3);
+            };
+            auto loads = [&](int i) ETS_INLINE {
+                if (i == 4) d_e = n_kpos(2 * tile + 2);
+                // (behind the last branch of the stage: carried over one, a resource descriptor would
+                // move to vector registers)
+                if (i == 5) rs = rsrc_of(load_next);
+                if (i >= 6 && i < 14) issue_load(rs, oth, i - 6);
+                if (i == 14) e_next = extent_of(d_e);
+            };
+            auto descs = [&](int i) ETS_INLINE {
+                if (i == 4) d_e = n_kpos(2 * tile + 3);
+                if (i == 5) d_tok = *reinterpret_cast<const u32x2_t*>(desc_at(2 * tile + 8 + sw));
+                if (i == 6) d_n = reinterpret_cast<const uint32_t*>(desc_at(2 * tile + 8 + sw))[2];
+                if (i == 13) e_next = extent_of(d_e);
+                if (i == 14) load_next = to_run(d_tok, d_n);
+            };
+            const Extent e1 = e_next;
+            prefill_unit(st, vs, ks, pf_a, pf_b, scale_log2e, raise_margin, hides(e1), finish,
+                         [&](int j) ETS_INLINE { mask(j, e1); }, []() { __syncthreads(); }, loads);
+            const Extent e2 = e_next;
+            prefill_unit(st, vs + 2 * kVFragHalf, ks + 32 * KROW_B, pf_b, pf_a, scale_log2e, raise_margin,
+                         hides(e2), begin, [&](int j) ETS_INLINE { mask(j, e2); }, []() {}, descs);
+        } else {
+#pragma unroll
+            for (int x = 4; x < 8; ++x) stage_v(v_dst + nxt, oth, x);
+            __syncthreads();
+            issue_loads(load_next, oth);
+            load_next = run_of(*desc_at(2 * tile + 8 + sw));
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                stage_k(k_dst + aft, own, i);
+                stage_v(v_dst + aft, own, i);
+            }
         }
+        const int free_buf = cur;
         cur = nxt;
-        nxt = nxt == 2 ? 0 : nxt + 1;
+        nxt = aft;
+        aft = free_buf;
     };
-    // (no branch inside the loop body: the waits for a register set then leave the other
-    // set's loads in flight)
-    for (int tile = 0; tile + 1 < n_tiles; tile += 2) {
-        do_tile(tile, raw0);
-        do_tile(tile + 1, raw1);
+    // (nothing but the exit branches off inside the loops: the waits for a register set then leave
+    // the other set's loads in flight)
+    auto walk = [&](auto computes) ETS_INLINE {
+        for (int tile = 0;;) {
+            do_tile(tile, raw0, raw1, computes);
+            if (++tile >= n_tiles) break;
+            do_tile(tile, raw1, raw0, computes);
+            if (++tile >= n_tiles) break;
+        }
+        __syncthreads();  // every wave is done with the tiles: the epilogue reuses the buffers
+    };
+    if (!active) {
+        walk(std::false_type{});  // only fetches and stages, through the same barriers
+        return;
     }
-    if (n_tiles & 1) do_tile(n_tiles - 1, raw0);
-    __syncthreads();  // every wave is done with the tiles: the epilogue reuses the buffers
+    first_run();
+    walk(std::true_type{});
 
-    // rows out through the wave's own LDS region (16 rows padded to 132 floats, two
-    // passes), so that whole 512-byte rows are stored: normalised in step prefill,
+    // rows out through the wave's own LDS region (16 rows padded to 132 floats, two passes per
+    // block), so that whole 512-byte rows are stored: normalised in step prefill,
     // unnormalised next to (m, l) in decode
     constexpr int OROW = 132;
     float* ob = reinterpret_cast<float*>(smem) + w * (16 * OROW);
-    float l = lsum;
-    l += __shfl_xor(l, 32, 64);
-    float inv = 1.0f;
-    if constexpr (!DECODE) {
-        inv = 1.0f / l;
-        if constexpr (FP8) inv *= v_scales.s[h];
-    }
-    if (g == 0 && (r_lane >> g_shift) < n_grp) {
-        if constexpr (DECODE)
-            ws_ml[out_row] = make_float2(m * scale_log2e, l);
-        else
-            lse[out_row] = (m * scale_log2e + __builtin_amdgcn_logf(l)) * 0.6931471805599453f;
-    }
     const int col = (lane & 31) * 4;
 #pragma unroll
-    for (int pass = 0; pass < 2; ++pass) {
-        if ((n >> 4) == pass) {
-#pragma unroll
-            for (int x = 0; x < 4; ++x)
-#pragma unroll
-                for (int c = 0; c < 4; ++c)
-                    *reinterpret_cast<float4*>(ob + (n & 15) * OROW + 32 * x + 8 * c + 4 * g) =
-                        make_float4(oacc[x][4 * c] * inv, oacc[x][4 * c + 1] * inv,
-                                    oacc[x][4 * c + 2] * inv, oacc[x][4 * c + 3] * inv);
+    for (int j = 0; j < NB; ++j) {
+        mfma_result_wait(st.oacc[j]);
+        const int r_lane = WROWS * w + 32 * j + n;
+        // row of the lane's query in `out` (and in lse / ws_ml)
+        int64_t out_row = q_row0 + group_of(r_lane);
+        if constexpr (DECODE) out_row = ent_base[ent_begin + group_of(r_lane)] + slot_off;
+        out_row = out_row * n_q_heads + h * G + (r_lane & (G - 1));
+        float l = st.lsum[j];
+        l += __shfl_xor(l, 32, 64);
+        float inv = 1.0f;
+        if constexpr (!DECODE) {
+            inv = 1.0f / l;
+            if constexpr (FP8) inv *= v_scales.s[h];
         }
-        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-#pragma unroll
-        for (int k = 0; k < 8; ++k) {
-            const int rr = 2 * k + (lane >> 5);  // row of this pass that the lane stores
-            const int r = 32 * w + 16 * pass + rr;
-            // lane 16 pass + rr (g = 0) holds the output row of query row r
-            const int64_t row_out = __shfl(out_row, 16 * pass + rr, 64);
-            const float4 v = *reinterpret_cast<const float4*>(ob + rr * OROW + col);
-            if ((r >> g_shift) < n_grp) *reinterpret_cast<float4*>(out + row_out * D + col) = v;
+        if (g == 0 && (r_lane >> g_shift) < n_grp) {
+            if constexpr (DECODE)
+                ws_ml[out_row] = make_float2(st.m[j] * scale_log2e, l);
+            else
+                lse[out_row] = (st.m[j] * scale_log2e + __builtin_amdgcn_logf(l)) * 0.6931471805599453f;
         }
-        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-        __builtin_amdgcn_wave_barrier();
+#pragma unroll
+        for (int pass = 0; pass < 2; ++pass) {
+            if ((n >> 4) == pass) {
+#pragma unroll
+                for (int x = 0; x < 4; ++x)
+#pragma unroll
+                    for (int c = 0; c < 4; ++c)
+                        *reinterpret_cast<float4*>(ob + (n & 15) * OROW + 32 * x + 8 * c + 4 * g) =
+                            make_float4(st.oacc[j][x][4 * c] * inv, st.oacc[j][x][4 * c + 1] * inv,
+                                        st.oacc[j][x][4 * c + 2] * inv, st.oacc[j][x][4 * c + 3] * inv);
+            }
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+#pragma unroll
+            for (int k = 0; k < 8; ++k) {
+                const int rr = 2 * k + (lane >> 5);  // row of this pass that the lane stores
+                const int r = WROWS * w + 32 * j + 16 * pass + rr;
+                // lane 16 pass + rr (g = 0) holds the output row of query row r
+                const int64_t row_out = __shfl(out_row, 16 * pass + rr, 64);
+                const float4 v = *reinterpret_cast<const float4*>(ob + rr * OROW + col);
+                if ((r >> g_shift) < n_grp) *reinterpret_cast<float4*>(out + row_out * D + col) = v;
+            }
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+        }
     }
 }
 

@@ -10,7 +10,7 @@ import torch
 import oracle
 import paper_2502_13575_amd as ets
 from workload import (CONFIGS, Tree, TreeConfig, make_prefill_queries_host, make_tree,
-                      make_values_device, make_values_host, random_tree)
+                      make_values_device, make_values_host, random_tree, to_bf16_bits)
 
 from _gpu_util import (compare, gpu_prefill, make_ctx, oracle_prefill, pool_to_device,
                        pool_to_host, to_device, to_host_bits)
@@ -66,6 +66,31 @@ def test_prefill_long_paths_refill_the_descriptor_ring():
     tree = Tree(np.array([-1, 0], np.int32), np.array([0, 9000], np.int64),
                 np.array([9000, 40], np.int32), np.array([1], np.int32), 9040)
     _full_parity(cfg, tree, "prefill 9000-row ancestor")
+
+
+@pytest.mark.parametrize("hkv,hq,root,n", [(1, 1, 31, 65), (2, 8, 64, 33), (1, 8, 257, 40), (1, 4, 700, 96)])
+def test_prefill_scores_that_rise_along_the_path(hkv, hq, root, n):
+    """Scores climb by up to 110 nats along the path for half of the query tokens and fall for
+    the others, so that the reference score is raised again and again, in one block of query
+    rows of a wave and not in the other, in every phase of the pipeline (the bar is that of all
+    other cases: weights keep their relative accuracy, lse is exact to fp32 rounding)."""
+    cfg = TreeConfig("rise", hkv, hq, 128, "bf16", 0, 0, 0, 0, 0, None, seed=900 + n)
+    tree = Tree(np.array([-1, 0], np.int32), np.array([0, root], np.int64),
+                np.array([root, n], np.int32), np.array([1, 0], np.int32), root + n)
+    _, v, _ = make_values_host(cfg, tree)
+    r = np.random.default_rng(n)
+    u = r.choice([-1.0, 1.0], size=128)
+    t = np.arange(root + n) / (root + n)
+    k = (u * (10.0 * t)[:, None, None] + 0.1 * r.standard_normal((root + n, hkv, 128)))
+    rows = n + root
+    sign = np.where(np.arange(rows) // (32 // max(hq // hkv, 1) + 1) % 2 == 0, 1.0, -1.0)
+    q = u * sign[:, None, None] + 0.1 * r.standard_normal((rows, hq, 128))
+    k, q = to_bf16_bits(k.astype(np.float32)), to_bf16_bits(q.astype(np.float32))
+    with make_ctx(cfg) as ctx:
+        out, lse, _ = gpu_prefill(ctx, tree, pool_to_device(k), pool_to_device(v), to_device(q))
+    oo, ol = oracle_prefill(cfg, tree, k, v, q)
+    compare(out.cpu().numpy().reshape(-1, 128), lse.cpu().numpy().reshape(-1), oo.reshape(-1, 128),
+            ol.reshape(-1), "bf16", "prefill rising %d + %d" % (root, n))
 
 
 def test_prefill_duplicates_empty_nodes_and_no_queries():
