@@ -121,12 +121,17 @@ __device__ __forceinline__ uint32_t f16_pair(float lo, float hi) {
     return __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2_t{lo, hi}), f16x2_t));
 }
 
+// K rows in LDS: 16 units of 16 bytes and one of padding (a fragment read takes one unit of 32
+// rows: 17 n visits every bank group once whichever sixteen rows meet).
+constexpr int kPrefillKRow = 17;
 // V^T fragments in LDS.  The 16 rows of half a run are kept as 16-byte slots, one per output
 // element d = 8 a + x and row group g: the eight contraction slots that lane (d % 32, g) of d
-// block d / 32 feeds to the matrix instruction.  Slot (x, g, a) sits at 34 x + 16 g + a: a reader's 16
-// consecutive lanes (x = 0..7, two values of a) and a writer's 16 (all a) then touch every bank
-// once, and both address them with one register and constant offsets.
-constexpr int kVFragX = 34 * 16;        // bytes between elements x and x + 1
+// block d / 32 feeds to the matrix instruction.  Slot (x, g, a) sits at 36 x + 16 g + a: a writer's
+// 16 lanes (all a) and the sixteen lanes of a read that meet ({0..3, 12..15, 20..27} or {4..11,
+// 16..19, 28..31} of 8 a + x) then touch every bank group once (34 x + .. takes 256 cycles
+// for 32 reads of four waves instead of 160), and both address them with one register and
+// constant offsets.
+constexpr int kVFragX = 36 * 16;        // bytes between elements x and x + 1
 constexpr int kVFragHalf = 8 * kVFragX; // bytes of half a run
 
 // A condition that hardly ever holds: its code is kept out of the way.  With one wave per SIMD a
@@ -316,7 +321,7 @@ __global__ __launch_bounds__(kPrefillThreads) __attribute__((amdgpu_waves_per_eu
     constexpr int D = 128;
     constexpr int NB = 2;                  // blocks of 32 query rows per wave
     constexpr int WROWS = 32 * NB;         // query rows per wave
-    constexpr int KROW_B = 16 * kTreeAttnKRow;  // bytes of a K row in LDS (272)
+    constexpr int KROW_B = 16 * kPrefillKRow;  // bytes of a K row in LDS (272)
     constexpr int KS_B = 64 * KROW_B;           // K tile: 64 rows
     constexpr int BUF_B = KS_B + 4 * kVFragHalf;  // V^T fragments behind it: [run][half]
     constexpr int RING = 256;
@@ -523,7 +528,7 @@ __global__ __launch_bounds__(kPrefillThreads) __attribute__((amdgpu_waves_per_eu
     };
 
     const char* const k_src = smem + n * KROW_B + g * 16;  // the lane's row of a run's K fragments
-    const char* const v_src = smem + KS_B + (34 * (n & 7) + 16 * g + (n >> 3)) * 16;
+    const char* const v_src = smem + KS_B + (n & 7) * kVFragX + (16 * g + (n >> 3)) * 16;
     u32x4_t pf_a[NB][2], pf_b[NB][2];  // weights of the even and of the odd run of a tile
     Extent e_next;                     // of the run whose scores come next
     Run load_next;                     // the run to be fetched next

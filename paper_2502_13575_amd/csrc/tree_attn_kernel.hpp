@@ -111,16 +111,19 @@ __device__ __forceinline__ std::conditional_t<FP8, u32x2_t, u32x4_t> load_row_pi
 }
 
 static_assert(kTreeAttnRowsPerItem == 64, "4 waves x 16 rows");
-constexpr int kTreeAttnKRow = 17;         // 16-byte units per padded K row in LDS (272 bytes)
 
-// Geometry by head_dim D (128 or 64): a K row in LDS is D / 8 16-byte units plus one of
-// padding; the score product contracts over D in D / 32 matrix instructions; the output
+// Geometry by head_dim D (128 or 64): a K row in LDS is D / 8 16-byte units plus two of
+// padding (see k_row_units); the score product contracts over D in D / 32 matrix instructions; the output
 // has D / 16 blocks of 16 rows of V^T (fragments).
+// A K fragment read takes unit 4 kk + b of row a in lane (a, b).  The LDS serves a 16-byte read
+// sixteen lanes at a time, in the groups {0..3, 12..15, 20..27}, {4..11, 16..19, 28..31} and the
+// same in the upper half of the wave: two values of b meet in a group, so that rows must
+// take even and b odd steps through the 16 bank groups.  Two units of padding give that: 32
+// such reads of four waves in 160 cycles, against 256 with one unit (where a + b collides).
 template <int D>
 constexpr int k_row_units() {
-    return D / 8 + 1;
+    return D / 8 + 2;
 }
-static_assert(k_row_units<128>() == kTreeAttnKRow, "the step-prefill kernel stages K the same way");
 
 // One step of a row-parallel item: 32 staged tokens (V already fp16) against one block
 // of 16 query rows.
@@ -276,6 +279,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void t
     constexpr int NKL = 16 / RPL;          // K loads per 16 tokens
     constexpr int KS_UNITS = 64 * KROW;    // K tile: 64 padded rows
     constexpr int VS_UNITS = 2 * NX * 64;  // V^T fragments: [step][x][lane]
+    // a wave's own region (small items, and the way out of every item's partial rows)
+    constexpr int WAVE_UNITS = 16 * KROW + NX * 32;
+    static_assert(4 * WAVE_UNITS <= KS_UNITS + VS_UNITS, "four regions");
     // K tile, then V^T fragments; the K part is reused for the token-parallel fold
     __shared__ u32x4_t smem[KS_UNITS + VS_UNITS];
     __shared__ float sm_m[4][16];
@@ -411,7 +417,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void t
         ws_ml, 0, FUSED ? (int)(uint32_t)(tail.n_ws_rows * 8) : 0, 0x00020000);
     auto store_partial = [&](const f32x4_t (&oacc)[NX], float m, float l, int32_t out_row) {
         constexpr int OROW = D + 4;
-        float* ob = reinterpret_cast<float*>(smem) + w * (16 * OROW);
+        static_assert(16 * OROW * 4 <= WAVE_UNITS * 16, "16 rows");
+        float* ob = reinterpret_cast<float*>(smem + w * WAVE_UNITS);
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
             float* p = ob + a * OROW + (D / 4) * b + (D / 16) * i;
@@ -544,7 +551,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void t
         // in flight while the current one is computed; no fold, no workgroup barrier.
         const uint32_t k_off0 = (uint32_t)rb * stride_b + pa * piece_b;       // K row rb (+ RPL i)
         const uint32_t v_off0 = (uint32_t)(4 * b) * stride_b + va * piece_b;  // V row 4 b (+ i)
-        u32x4_t* ksw = smem + w * (16 * KROW + NX * 32);
+        u32x4_t* ksw = smem + w * WAVE_UNITS;
         u32x2_t* vsw = reinterpret_cast<u32x2_t*>(ksw + 16 * KROW);
         auto unit_rows = [&](int u, int64_t& tok) {
             // steps 0 and 1 stand in the unit table; the others: uniform, a scalar load
