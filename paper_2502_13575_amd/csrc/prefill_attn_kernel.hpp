@@ -3,7 +3,8 @@
 //
 // Scoring a new step with the reward model is a prefill of that step's tokens over the
 // tree of cached steps: query token i of the node sees every row of the node's strict
-// ancestors and rows 0..i of the node itself.  A workgroup takes 256 query rows
+// ancestors and rows 0..i of the node itself.  A workgroup takes 256 query rows, or 128 in
+// launches of few items (template parameter NB: blocks of 32 rows per wave; below, NB = 2)
 // (256 / G consecutive tokens x the G query heads of the kv head), walks the ancestors'
 // rows and then the node's own rows up to its last token, 64 rows (two runs of at most
 // 32) at a time through LDS, and keeps the running softmax of its rows in registers:
@@ -13,10 +14,10 @@
 // side cache feed the compute units, not by the matrix cores.  Blocks of the same node
 // and of sibling nodes run next to each other and find their shared ancestors in L2.
 //
-// Bound: the matrix cores.  One wave per SIMD owns 64 query rows (two blocks of 32), so that
-// every K and V fragment read from LDS feeds two matrix instructions: with 32 rows per wave
-// the fragment reads alone (16 KB per wave and run at 128 bytes per cycle) take as long as
-// the matrix instructions.  Lane l = (n, g), n = l % 32, g = l / 32.  Per run of 32 rows and
+// Bound: the issue of instructions next to the matrix cores.  One wave per SIMD owns 64 query
+// rows (two blocks of 32), so that every K and V fragment read from LDS feeds two matrix
+// instructions: with 32 rows per wave, eight waves read 128 KB per run, 640 of the 1 024
+// cycles that the matrix instructions take even without a bank conflict.  Lane l = (n, g), n = l % 32, g = l / 32.  Per run of 32 rows and
 // block of 32 query rows:
 //   S^T = K Q^T     8 x v_mfma_f32_32x32x16_bf16: run rows on M, query rows on N.  A = K
 //                   rows from the LDS tile (lane (n, g): row n, d = 16 kk + 8 g .. + 7),
@@ -138,16 +139,17 @@ constexpr int kVFragHalf = 8 * kVFragX; // bytes of half a run
 // branch that is taken costs about 100 cycles until instructions arrive from its target.
 #define ETS_RARE(x) __builtin_expect(!!(x), 0)
 
-// What a wave carries from run to run: two blocks of 32 query rows.
+// What a wave carries from run to run: NB blocks of 32 query rows.
+template <int NB>
 struct PrefillState {
-    bf16x8_t qf[2][8];   // query rows as B operands
-    f32x16_t s[2];       // scores of the newest run
-    f32x16_t oacc[2][4]; // d block x: lane (n, g) holds d = 32 x + 8 c + 4 g + r at index 4 c + r
-    u32x4_t kf[8];       // K fragments of the run after it
-    float m[2], nmc[2];  // reference score of the lane's row (-inf: none yet); minus the same times
+    bf16x8_t qf[NB][8];   // query rows as B operands
+    f32x16_t s[2];        // NB = 2: scores of the newest run, per block; NB = 1: of two runs in turn
+    f32x16_t oacc[NB][4]; // d block x: lane (n, g) holds d = 32 x + 8 c + 4 g + r at index 4 c + r
+    u32x4_t kf[8];        // K fragments of the run after it
+    float m[NB], nmc[NB];  // reference score of the lane's row (-inf: none yet); minus the same times
                          // scale_log2e (0 without one)
-    float lsum[2];       // sum of the weights so far
-    float alpha[2];      // factor of oacc after the application under way, if it is to be scaled
+    float lsum[NB];       // sum of the weights so far
+    float alpha[NB];      // factor of oacc after the application under way, if it is to be scaled
     float p_even, p_last;  // weights under way: of an even score, and the newest one
 };
 constexpr int kEarlyWeights = 4;  // weights of block 0 beside the scores of block 1
@@ -169,7 +171,8 @@ __device__ __forceinline__ float prefill_max(const f32x16_t& s) {
 // Raises the row's reference to the largest score of the run when one exceeds it by more than
 // the margin.  What has been gathered under the old reference is scaled: the sum at once, the
 // output rows when the caller has applied the weights still under way.
-__device__ __forceinline__ void prefill_raise(PrefillState& st, int j, float mx, float scale_log2e) {
+template <int NB>
+__device__ __forceinline__ void prefill_raise(PrefillState<NB>& st, int j, float mx, float scale_log2e) {
     mx = fmaxf(mx, __shfl_xor(mx, 32, 64));  // the row's other half of the run
     const float m_new = fmaxf(st.m[j], mx);
     // (a row that has seen nothing yet keeps -inf, and what it gathered is zero)
@@ -178,7 +181,8 @@ __device__ __forceinline__ void prefill_raise(PrefillState& st, int j, float mx,
     st.m[j] = m_new;
     st.lsum[j] *= st.alpha[j];
 }
-__device__ __forceinline__ void scale_rows(PrefillState& st, int j) {
+template <int NB>
+__device__ __forceinline__ void scale_rows(PrefillState<NB>& st, int j) {
     mfma_result_wait(st.oacc[j]);
 #pragma unroll
     for (int x = 0; x < 4; ++x) st.oacc[j][x] *= st.alpha[j];
@@ -187,10 +191,13 @@ __device__ __forceinline__ void scale_rows(PrefillState& st, int j) {
 // Weight i of block j, taken against the row's reference score, in two steps so that nothing
 // waits for the exponential.  The empty statements hold the arithmetic where it is written: the
 // compiler would otherwise sink it behind the next branch, away from the matrix instructions.
-__device__ __forceinline__ void weight_begin(PrefillState& st, int j, int i, float scale_log2e) {
-    st.p_last = fast_exp2(fmaf(st.s[j][i], scale_log2e, st.nmc[j]));
+template <int NB>
+__device__ __forceinline__ void weight_begin(PrefillState<NB>& st, const f32x16_t& s, int j, int i,
+                                             float scale_log2e) {
+    st.p_last = fast_exp2(fmaf(s[i], scale_log2e, st.nmc[j]));
 }
-__device__ __forceinline__ void weight_end(PrefillState& st, u32x4_t (&pf)[2][2], int j, int i) {
+template <int NB>
+__device__ __forceinline__ void weight_end(PrefillState<NB>& st, u32x4_t (&pf)[2][2], int j, int i) {
     st.lsum[j] += st.p_last;
     if (i & 1) {
         uint32_t h = f16_pair(st.p_even, st.p_last);
@@ -220,10 +227,10 @@ __device__ __forceinline__ void weight_end(PrefillState& st, u32x4_t (&pf)[2][2]
 //   v_run, k_after   LDS byte addresses: the lane's slot of run u's V^T fragments, and its row of
 //                    run u + 2's K
 //   fill(k)          k = 0..15: the caller's work beside A;  fill_b(i), i = 0..15: beside B
-//   hidden, mask(j)  whether rows of run u + 1 are hidden from a query row, and what hides
-//                    them from block j's scores
+//   hidden, mask(s, j)  whether rows of run u + 1 are hidden from a query row, and what hides
+//                    them from block j's scores s
 template <class Fill, class Mask, class Before, class FillB>
-__device__ __forceinline__ void prefill_unit(PrefillState& st, const char* __restrict__ v_run,
+__device__ __forceinline__ void prefill_unit(PrefillState<2>& st, const char* __restrict__ v_run,
                                              const char* __restrict__ k_after,
                                              u32x4_t (&pf_cur)[2][2], u32x4_t (&pf)[2][2],
                                              float scale_log2e, float raise_margin, bool hidden,
@@ -237,7 +244,7 @@ __device__ __forceinline__ void prefill_unit(PrefillState& st, const char* __res
         __builtin_amdgcn_sched_barrier(0);
         vf[kk] = load16(v_run + (kk >> 2) * kVFragHalf + (kk & 3) * 64);  // half kk / 4, d block kk % 4
         if (kk > 0) weight_end(st, pf_cur, 1, 16 - kLateWeights + kk - 1);
-        weight_begin(st, 1, 16 - kLateWeights + kk, scale_log2e);
+        weight_begin(st, st.s[1], 1, 16 - kLateWeights + kk, scale_log2e);
         fill(kk);
         __builtin_amdgcn_sched_barrier(0);
     }
@@ -249,14 +256,14 @@ __device__ __forceinline__ void prefill_unit(PrefillState& st, const char* __res
         __builtin_amdgcn_sched_barrier(0);
         if (kk == 0) weight_end(st, pf_cur, 1, 15);
         fill(8 + kk);
-        if (kk == 2 && ETS_RARE(hidden)) mask(0);
+        if (kk == 2 && ETS_RARE(hidden)) mask(st.s[0], 0);
         if (kk == 3) {
             const float mx = prefill_max(st.s[0]);
             raised0 = __any(mx > st.m[0] + raise_margin);
             if (ETS_RARE(raised0)) prefill_raise(st, 0, mx, scale_log2e);
         }
         if (kk > 8 - kEarlyWeights) weight_end(st, pf, 0, kk - 9 + kEarlyWeights);
-        if (kk >= 8 - kEarlyWeights) weight_begin(st, 0, kk - 8 + kEarlyWeights, scale_log2e);
+        if (kk >= 8 - kEarlyWeights) weight_begin(st, st.s[0], 0, kk - 8 + kEarlyWeights, scale_log2e);
         __builtin_amdgcn_sched_barrier(0);
     }
     before_b();
@@ -264,8 +271,8 @@ __device__ __forceinline__ void prefill_unit(PrefillState& st, const char* __res
     // the other weights of block 0, then those of block 1 that are not late
     constexpr int kRest0 = 16 - kEarlyWeights, kRest = kRest0 + 16 - kLateWeights;
     auto begin = [&](int k) {
-        if (k < kRest0) weight_begin(st, 0, kEarlyWeights + k, scale_log2e);
-        else weight_begin(st, 1, k - kRest0, scale_log2e);
+        if (k < kRest0) weight_begin(st, st.s[0], 0, kEarlyWeights + k, scale_log2e);
+        else weight_begin(st, st.s[1], 1, k - kRest0, scale_log2e);
     };
     auto end = [&](int k) {
         if (k < 0) weight_end(st, pf, 0, kEarlyWeights - 1);
@@ -280,7 +287,7 @@ __device__ __forceinline__ void prefill_unit(PrefillState& st, const char* __res
         mfma_apply(st.oacc[j][x], vf[4 * t + x], pf_cur[j][t]);
         __builtin_amdgcn_sched_barrier(0);
         if (j == 1) st.kf[i >> 1] = load16(k_after + 32 * (i >> 1));
-        if (i == 2 && ETS_RARE(hidden)) mask(1);
+        if (i == 2 && ETS_RARE(hidden)) mask(st.s[1], 1);
         if (i == 3) {
             const float mx = prefill_max(st.s[1]);
             raised1 = __any(mx > st.m[1] + raise_margin);
@@ -303,6 +310,55 @@ __device__ __forceinline__ void prefill_unit(PrefillState& st, const char* __res
     if (ETS_RARE(raised1)) scale_rows(st, 1);
 }
 
+// The same for one block of 32 query rows per wave (small launches, see build_prefill_plan).  The
+// scores alternate between st.s[ODD] (run u, complete) and st.s[1 - ODD] (run u + 1):
+//   A   scores(u + 1)  ||  weights of run u
+//   B   apply(u)       ||  staging and loads; mask and maximum of run u + 1
+template <int ODD, class Fill, class Mask, class Before, class FillB>
+__device__ __forceinline__ void prefill_unit1(PrefillState<1>& st, const char* __restrict__ v_run,
+                                              const char* __restrict__ k_after, u32x4_t (&pf)[2][2],
+                                              float scale_log2e, float raise_margin, bool hidden,
+                                              Fill fill, Mask mask, Before before_b, FillB fill_b) {
+    u32x4_t vf[8];
+    f32x16_t& s_cur = st.s[ODD];
+    f32x16_t& s_next = st.s[1 - ODD];
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int kk = 0; kk < 8; ++kk) {
+        if (kk == 0) mfma_scores_first(s_next, st.kf[0], st.qf[0][0]);
+        else mfma_scores(s_next, st.kf[kk], st.qf[0][kk]);
+        __builtin_amdgcn_sched_barrier(0);
+        vf[kk] = load16(v_run + (kk >> 2) * kVFragHalf + (kk & 3) * 64);
+        if (kk > 0) weight_end(st, pf, 0, 2 * kk - 1);
+        weight_begin(st, s_cur, 0, 2 * kk, scale_log2e);
+        weight_end(st, pf, 0, 2 * kk);
+        weight_begin(st, s_cur, 0, 2 * kk + 1, scale_log2e);
+        fill(2 * kk);
+        fill(2 * kk + 1);
+        __builtin_amdgcn_sched_barrier(0);
+    }
+    weight_end(st, pf, 0, 15);
+    before_b();
+    __builtin_amdgcn_sched_barrier(0);
+    bool raised = false;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+        mfma_apply(st.oacc[0][i & 3], vf[i], pf[0][i >> 2]);
+        __builtin_amdgcn_sched_barrier(0);
+        st.kf[i] = load16(k_after + 32 * i);
+        if (i == 2 && ETS_RARE(hidden)) mask(s_next, 0);
+        if (i == 3) {
+            const float mx = prefill_max(s_next);
+            raised = __any(mx > st.m[0] + raise_margin);
+            if (ETS_RARE(raised)) prefill_raise(st, 0, mx, scale_log2e);
+        }
+        fill_b(2 * i);
+        fill_b(2 * i + 1);
+        __builtin_amdgcn_sched_barrier(0);
+    }
+    if (ETS_RARE(raised)) scale_rows(st, 0);
+}
+
 // FP8: the pools hold E4M3 codes (128-byte rows, 8 bytes per lane and load); the codes are
 // widened while the tile is staged (K to bf16, V straight to the fp16 fragments), the kv
 // head's K scale enters the score scale and its V scale multiplies the normalised rows.
@@ -310,7 +366,7 @@ __device__ __forceinline__ void prefill_unit(PrefillState& st, const char* __res
 // 256 / G of them), `out` is the partial workspace ws_o, `lse` is unused, and ent_order,
 // ent_base, ws_ml are the decode plan's tables; otherwise `items_raw` are PrefillItem and
 // the last three arguments are unused.
-template <bool FP8, bool DECODE>
+template <bool FP8, bool DECODE, int NB>
 __global__ __launch_bounds__(kPrefillThreads) __attribute__((amdgpu_waves_per_eu(1, 1))) void prefill_attn_kernel(
     const void* __restrict__ k_pool, const void* __restrict__ v_pool, int64_t pool_tokens,
     const bf16_t* __restrict__ q, const Run* __restrict__ runs,
@@ -319,13 +375,13 @@ __global__ __launch_bounds__(kPrefillThreads) __attribute__((amdgpu_waves_per_eu
     const int32_t* __restrict__ ent_order, const int32_t* __restrict__ ent_base,
     float2* __restrict__ ws_ml) {
     constexpr int D = 128;
-    constexpr int NB = 2;                  // blocks of 32 query rows per wave
     constexpr int WROWS = 32 * NB;         // query rows per wave
     constexpr int KROW_B = 16 * kPrefillKRow;  // bytes of a K row in LDS (272)
     constexpr int KS_B = 64 * KROW_B;           // K tile: 64 rows
     constexpr int BUF_B = KS_B + 4 * kVFragHalf;  // V^T fragments behind it: [run][half]
     constexpr int RING = 256;
-    static_assert(4 * WROWS == kPrefillRowsPerItem && 4 * WROWS == kWideRowsPerItem, "rows per workgroup");
+    static_assert(!DECODE || 4 * WROWS == kWideRowsPerItem, "rows per workgroup");
+    static_assert(4 * WROWS == (NB == 2 ? kPrefillRowsPerItem : kPrefillRowsSmall), "rows per workgroup");
     __shared__ u32x4_t smem_raw[3 * BUF_B / 16];  // three tile buffers
     __shared__ u32x4_t sm_desc[RING];
 
@@ -466,7 +522,7 @@ __global__ __launch_bounds__(kPrefillThreads) __attribute__((amdgpu_waves_per_eu
     // is rarely full) only fetches and stages
     const bool active = ((WROWS * w) >> g_shift) < n_grp;
     const int i_first = tok0 + group_of(WROWS * w);  // the wave's first query token
-    PrefillState st;
+    PrefillState<NB> st;
 #pragma unroll
     for (int j = 0; j < NB; ++j) {
         const int r = WROWS * w + 32 * j + n;
@@ -517,11 +573,11 @@ __global__ __launch_bounds__(kPrefillThreads) __attribute__((amdgpu_waves_per_eu
         const int kpos = __builtin_amdgcn_readfirstlane(e.kpos);
         return (n_valid != 32) | (kpos + 31 > i_first);  // (no branch)
     };
-    auto mask = [&](int j, const Extent& e) ETS_INLINE {
+    auto mask = [&](f32x16_t& s, int j, const Extent& e) ETS_INLINE {
         int lim = e.n;
         if constexpr (!DECODE) lim = min(lim, tok0 + group_of(WROWS * w + 32 * j + n) - e.kpos + 1);
-        mfma_result_wait(st.s[j]);
-        prefill_mask(st.s[j], g, lim);
+        mfma_result_wait(s);
+        prefill_mask(s, g, lim);
     };
     auto n_kpos = [&](int idx) ETS_INLINE {
         return reinterpret_cast<const u32x2_t*>(desc_at(idx))[1];
@@ -529,7 +585,7 @@ __global__ __launch_bounds__(kPrefillThreads) __attribute__((amdgpu_waves_per_eu
 
     const char* const k_src = smem + n * KROW_B + g * 16;  // the lane's row of a run's K fragments
     const char* const v_src = smem + KS_B + (n & 7) * kVFragX + (16 * g + (n >> 3)) * 16;
-    u32x4_t pf_a[NB][2], pf_b[NB][2];  // weights of the even and of the odd run of a tile
+    u32x4_t pf_a[2][2], pf_b[2][2];    // weights of the even and of the odd run of a tile
     Extent e_next;                     // of the run whose scores come next
     Run load_next;                     // the run to be fetched next
     // scores and weights of the first run
@@ -547,11 +603,12 @@ __global__ __launch_bounds__(kPrefillThreads) __attribute__((amdgpu_waves_per_eu
 #pragma unroll
         for (int j = 0; j < NB; ++j) {
             mfma_result_wait(st.s[j]);
-            if (hides(e_next)) mask(j, e_next);
+            if (hides(e_next)) mask(st.s[j], j, e_next);
             prefill_raise(st, j, prefill_max(st.s[j]), scale_log2e);
+            // (with one block the weights belong to the first stage)
 #pragma unroll
-            for (int i = 0; i < (j == 0 ? 16 : 16 - kLateWeights); ++i) {
-                weight_begin(st, j, i, scale_log2e);
+            for (int i = 0; NB == 2 && i < (j == 0 ? 16 : 16 - kLateWeights); ++i) {
+                weight_begin(st, st.s[j], j, i, scale_log2e);
                 weight_end(st, pf_a, j, i);
             }
         }
@@ -611,11 +668,21 @@ __global__ __launch_bounds__(kPrefillThreads) __attribute__((amdgpu_waves_per_eu
                 if (i == 14) load_next = to_run(d_tok, d_n);
             };
             const Extent e1 = e_next;
-            prefill_unit(st, vs, ks, pf_a, pf_b, scale_log2e, raise_margin, hides(e1), finish,
-                         [&](int j) ETS_INLINE { mask(j, e1); }, []() { __syncthreads(); }, loads);
+            auto mask1 = [&](f32x16_t& s, int j) ETS_INLINE { mask(s, j, e1); };
+            if constexpr (NB == 2)
+                prefill_unit(st, vs, ks, pf_a, pf_b, scale_log2e, raise_margin, hides(e1), finish, mask1,
+                             []() { __syncthreads(); }, loads);
+            else
+                prefill_unit1<0>(st, vs, ks, pf_a, scale_log2e, raise_margin, hides(e1), finish, mask1,
+                                 []() { __syncthreads(); }, loads);
             const Extent e2 = e_next;
-            prefill_unit(st, vs + 2 * kVFragHalf, ks + 32 * KROW_B, pf_b, pf_a, scale_log2e, raise_margin,
-                         hides(e2), begin, [&](int j) ETS_INLINE { mask(j, e2); }, []() {}, descs);
+            auto mask2 = [&](f32x16_t& s, int j) ETS_INLINE { mask(s, j, e2); };
+            if constexpr (NB == 2)
+                prefill_unit(st, vs + 2 * kVFragHalf, ks + 32 * KROW_B, pf_b, pf_a, scale_log2e,
+                             raise_margin, hides(e2), begin, mask2, []() {}, descs);
+            else
+                prefill_unit1<1>(st, vs + 2 * kVFragHalf, ks + 32 * KROW_B, pf_b, scale_log2e,
+                                 raise_margin, hides(e2), begin, mask2, []() {}, descs);
         } else {
 #pragma unroll
             for (int x = 4; x < 8; ++x) stage_v(v_dst + nxt, oth, x);

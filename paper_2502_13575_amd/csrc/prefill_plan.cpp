@@ -1,7 +1,7 @@
 // Planner of step-prefill attention: per distinct leaf node one run list (ancestors'
 // rows merged where they are contiguous in the pool and cut into pieces of at most 32,
 // then the node's own rows in pieces of 32 counted from its first row), per leaf query
-// blocks of 128 / G query tokens.  Leaf queries are taken in depth-first order of their
+// blocks of rows_per_item / G query tokens.  Leaf queries are taken in depth-first order of their
 // nodes, so that workgroups that run at the same time walk the same ancestors.
 #include "prefill_plan.h"
 
@@ -31,7 +31,6 @@ ets_status build(const ets_shape& shape, const ets_tree& tree, PrefillPlan& p,
                  int64_t kv_elem_bytes) {
     const int32_t N = tree.n_nodes, L = tree.n_leaves;
     const int32_t G = shape.n_q_heads / shape.n_kv_heads;
-    const int32_t tq = kPrefillRowsPerItem / G;  // query tokens per item
     p.parent.assign(tree.parent, tree.parent + N);
     p.tok_offset.assign(tree.tok_offset, tree.tok_offset + N);
     p.n_tokens.assign(tree.n_tokens, tree.n_tokens + N);
@@ -41,6 +40,20 @@ ets_status build(const ets_shape& shape, const ets_tree& tree, PrefillPlan& p,
     p.q_ptr.assign((size_t)L + 1, 0);
     p.item_begin.assign((size_t)L, 0);
     for (int32_t l = 0; l < L; ++l) p.q_ptr[l + 1] = p.q_ptr[l] + p.n_tokens[p.leaf_node[l]];
+
+    // Items of 256 rows need the fewest bytes and instructions per row (512 long ragged items,
+    // 8 heads per kv head: 7.9 ms per launch against 9.4 with 128 rows).  But one workgroup is
+    // resident per compute unit, so a launch of so few items that compute units stay empty
+    // lasts as long as one item, and 128 rows are walked in 0.6 of the time of 256: 16 steps
+    // of 64 tokens (128 items of 256 rows, or 256 of 128) take 28.5 us instead of 38.3.
+    int64_t n_large = 0;
+    for (int32_t l = 0; l < L; ++l)
+        n_large += (p.n_tokens[p.leaf_node[l]] + (int64_t)(kPrefillRowsPerItem / G) - 1) /
+                   (kPrefillRowsPerItem / G);
+    constexpr int64_t kComputeUnits = 256;
+    const int32_t rows = n_large * shape.n_kv_heads <= kComputeUnits ? kPrefillRowsSmall
+                                                                     : kPrefillRowsPerItem;
+    const int32_t tq = rows / G;  // query tokens per item
 
     // depth-first position of every node: children (larger ids) in id order
     std::vector<int32_t> first_child(N, -1), next_sibling(N, -1), last_child(N, -1), roots;
@@ -77,7 +90,7 @@ ets_status build(const ets_shape& shape, const ets_tree& tree, PrefillPlan& p,
     st = ets_prefill_stats{};
     st.n_leaves = L;
     st.n_q_rows = p.q_ptr[L];
-    st.rows_per_item = kPrefillRowsPerItem;
+    st.rows_per_item = rows;
     std::vector<char> live(N, 0);
 
     std::vector<int32_t> chain;
@@ -213,7 +226,7 @@ bool check_prefill_plan(const PrefillPlan& p, const ets_shape& shape, PlanCheck&
     for (const PrefillItem& it : p.items) {
         out.items += 1;
         bad(it.run_begin < 0 || it.run_end < it.run_begin || it.run_end > n_runs);
-        bad(it.n_tok < 1 || it.n_tok * G > kPrefillRowsPerItem);
+        bad(it.n_tok < 1 || it.n_tok * G > p.stats.rows_per_item);
         bad(it.leaf < 0 || it.leaf >= p.stats.n_leaves);
         // query tokens past n_tok are clamped to the block's last one by the kernel
         bad(it.q_row0 < 0 || it.q_row0 + it.n_tok > p.stats.n_q_rows);

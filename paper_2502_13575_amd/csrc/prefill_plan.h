@@ -16,7 +16,10 @@ namespace ets {
 // run's first row; rows of ancestors carry kAncestorRun and are seen by every query.
 // Query token i sees row t of a run iff t < n and kpos + t <= i.
 constexpr int32_t kAncestorRun = -(1 << 30);
-constexpr int32_t kPrefillRowsPerItem = 256;  // query rows (tokens x heads per kv head)
+// Query rows (tokens x heads per kv head) of a work item: 256, or 128 when items of 256 would
+// not give every compute unit a workgroup (one is resident per compute unit).
+constexpr int32_t kPrefillRowsPerItem = 256;
+constexpr int32_t kPrefillRowsSmall = 128;
 
 // Work item of the prefill kernel: query tokens [tok0, tok0 + n_tok) of one leaf
 // query's node against runs [run_begin, run_end): the ancestors' rows, then the node's
@@ -25,7 +28,7 @@ struct PrefillItem {
     int32_t run_begin;
     int32_t run_end;
     int64_t q_row0;  // query row of token tok0
-    int32_t n_tok;   // 1 .. kPrefillRowsPerItem / G
+    int32_t n_tok;   // 1 .. stats.rows_per_item / G
     int32_t tok0;
     int32_t leaf;    // leaf query index
     int32_t pad;

@@ -68,29 +68,38 @@ def test_prefill_long_paths_refill_the_descriptor_ring():
     _full_parity(cfg, tree, "prefill 9000-row ancestor")
 
 
-@pytest.mark.parametrize("hkv,hq,root,n", [(1, 1, 31, 65), (2, 8, 64, 33), (1, 8, 257, 40), (1, 4, 700, 96)])
-def test_prefill_scores_that_rise_along_the_path(hkv, hq, root, n):
+@pytest.mark.parametrize("hkv,hq,root,n,copies", [
+    (1, 1, 31, 65, 1), (2, 8, 64, 33, 1), (1, 8, 257, 40, 1), (1, 4, 700, 96, 1),
+    # enough blocks that work items hold 256 query rows instead of 128
+    (8, 8, 45, 257, 20), (8, 16, 33, 129, 20), (8, 32, 64, 64, 17), (8, 32, 31, 65, 20), (8, 64, 257, 33, 20)])
+def test_prefill_scores_that_rise_along_the_path(hkv, hq, root, n, copies):
     """Scores climb by up to 110 nats along the path for half of the query tokens and fall for
     the others, so that the reference score is raised again and again, in one block of query
     rows of a wave and not in the other, in every phase of the pipeline (the bar is that of all
     other cases: weights keep their relative accuracy, lse is exact to fp32 rounding)."""
     cfg = TreeConfig("rise", hkv, hq, 128, "bf16", 0, 0, 0, 0, 0, None, seed=900 + n)
     tree = Tree(np.array([-1, 0], np.int32), np.array([0, root], np.int64),
-                np.array([root, n], np.int32), np.array([1, 0], np.int32), root + n)
+                np.array([root, n], np.int32), np.array([1, 0] * copies, np.int32), root + n)
     _, v, _ = make_values_host(cfg, tree)
     r = np.random.default_rng(n)
     u = r.choice([-1.0, 1.0], size=128)
     t = np.arange(root + n) / (root + n)
     k = (u * (10.0 * t)[:, None, None] + 0.1 * r.standard_normal((root + n, hkv, 128)))
-    rows = n + root
+    rows = (n + root) * copies
     sign = np.where(np.arange(rows) // (32 // max(hq // hkv, 1) + 1) % 2 == 0, 1.0, -1.0)
     q = u * sign[:, None, None] + 0.1 * r.standard_normal((rows, hq, 128))
     k, q = to_bf16_bits(k.astype(np.float32)), to_bf16_bits(q.astype(np.float32))
     with make_ctx(cfg) as ctx:
-        out, lse, _ = gpu_prefill(ctx, tree, pool_to_device(k), pool_to_device(v), to_device(q))
-    oo, ol = oracle_prefill(cfg, tree, k, v, q)
-    compare(out.cpu().numpy().reshape(-1, 128), lse.cpu().numpy().reshape(-1), oo.reshape(-1, 128),
-            ol.reshape(-1), "bf16", "prefill rising %d + %d" % (root, n))
+        out, lse, st = gpu_prefill(ctx, tree, pool_to_device(k), pool_to_device(v), to_device(q))
+    assert st.rows_per_item == (128 if copies == 1 else 256)
+    # every (token, head) of the first and of the last pair of leaf queries
+    pick = [x for l in sorted({0, 1, 2 * copies - 2, 2 * copies - 1})
+            for x in ((l, i, h) for i in range([n, root][l % 2]) for h in range(hq))]
+    sl, stok, sh = (np.array(x, np.int32) for x in zip(*pick))
+    oo, ol = oracle_prefill(cfg, tree, k, v, q, rows=(sl, stok, sh))
+    at = oracle.prefill_q_ptr(tree.n_tokens, tree.leaf_node)[sl] + stok
+    compare(out.cpu().numpy()[at, sh], lse.cpu().numpy()[at, sh], oo, ol, "bf16",
+            "prefill rising %d + %d" % (root, n))
 
 
 def test_prefill_duplicates_empty_nodes_and_no_queries():
