@@ -79,7 +79,7 @@ struct AdvEntry {
 // Geometry of the matrix-core kernel that the planner and the launch code rely on.
 constexpr int kTreeAttnRowsPerItem = 64;  // query rows one work item serves at most
 constexpr int kTreeAttnMaxSteps = 256;    // steps per work item that takes a workgroup
-constexpr int kWideRowsPerItem = 256;     // query rows per work item of the wide kernel (8 waves x 32)
+constexpr int kWideRowsPerItem = 256;     // query rows per work item of the wide kernel (4 waves x 64)
 // Both per-entry tables (ent_order, ent_base) end in this many zero entries on the device:
 // a wave fetches the entries of its 16 query rows with one 16-entry scalar load, which may
 // run up to 15 entries past the item's last entry (see check_plan).

@@ -45,9 +45,11 @@
 // a ring of 256 entries in LDS that is refilled 128 at a time, 64 tiles ahead of their use.
 //
 // Measured per run (256 query rows) on 38 k query tokens of 8 heads each over 5.4 k rows:
-// about 2 000 cycles at 2.2 GHz, 1 024 of them matrix instructions (8 waves of 32 rows: 2 130);
-// 7.44 ms per launch = 929 TFLOP/s against 8.0 ms.  Without the weights the same loop takes
-// 1 390 cycles, without staging and loads 1 190.
+// 2 000 cycles at 2.2 GHz, 1 024 of them matrix instructions (eight waves of 32 rows: 2 130);
+// 7.8 ms per launch against 8.4 on the same card, 930 TFLOP/s at best.  Without the weights
+// the same loop takes 1 390 cycles, without staging and loads too 1 190; 1 350 cycles are
+// instruction issue.  512 steps of up to 512 tokens over 13 k rows: 32.5 ms = 978 TFLOP/s
+// (36.5 before).  128 rows per workgroup: 1 350 cycles per run.
 //
 // The same kernel serves decode attention for tree segments that MANY leaf queries share
 // (template parameter DECODE): there the 256 query rows of a work item are up to 256 / G
