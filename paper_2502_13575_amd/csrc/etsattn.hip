@@ -372,8 +372,8 @@ void mark(ets_ctx* c, int which, hipStream_t stream) {
 template <int D, int G>
 void launch_merge_dg(ets_ctx* c, const LaunchArgs& a) {
     const int n_leaves = (int)c->plan.stats.n_leaves;
-    const int64_t pairs = (int64_t)n_leaves * c->shape.n_kv_heads;  // one wave each
-    const unsigned grid = (unsigned)((pairs + 3) / 4);
+    // one wave per (leaf query, kv head), four leaf queries of one kv head to a workgroup
+    const unsigned grid = (unsigned)((n_leaves + (int64_t)3) / 4 * c->shape.n_kv_heads);
     hipLaunchKernelGGL((merge_kernel<D, G>), dim3(grid), dim3(256), 0, a.stream, c->d_part_base,
                        n_leaves, c->shape.n_kv_heads, a.ws_o, a.ws_ml, a.out, c->out_bf16 ? 1 : 0,
                        a.lse, c->v_scales);

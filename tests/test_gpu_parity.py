@@ -276,6 +276,27 @@ def test_long_chain_of_one_token_nodes(d):
             oo.reshape(-1, d), ol.reshape(-1), "bf16", "chain")
 
 
+@pytest.mark.parametrize("hkv,hq,d,n", [(8, 32, 128, 21), (3, 3, 128, 18), (5, 40, 128, 19), (1, 2, 64, 9),
+                                        (8, 8, 64, 20), (8, 64, 128, 1)])
+def test_merge_of_every_partial_count(hkv, hq, d, n):
+    """A path with a leaf query at each of its n nodes: leaf i has at least i + 1 partials (every
+    remainder of the merge's batches and rounds), leaf counts off and on a multiple of the four
+    of a workgroup, kv head counts other than the eight XCDs."""
+    from workload import Tree
+    n_tok = np.full(n, 130, np.int32)
+    tree = Tree(np.arange(-1, n - 1, dtype=np.int32), np.arange(n, dtype=np.int64) * 130, n_tok,
+                np.arange(n, dtype=np.int32), n * 130)
+    cfg = TreeConfig("merge", hkv, hq, d, "bf16", 0, 0, 0, 0, 0, None, seed=53 + n)
+    k, v, q = make_values_host(cfg, tree)
+    oo, ol = oracle_full(cfg, tree, k, v, q)
+    print("case merge", hkv, hq, d, n, flush=True)
+    with make_ctx(cfg) as ctx:
+        out, lse, st = gpu_attn(ctx, tree, pool_to_device(k), pool_to_device(v), to_device(q))
+    assert st.n_partials >= n * (n + 1) // 2
+    compare(out.cpu().numpy().reshape(-1, d), lse.cpu().numpy().reshape(-1),
+            oo.reshape(-1, d), ol.reshape(-1), "bf16", "merge")
+
+
 @pytest.mark.parametrize("name,opts,steps", [("c2_w16", {}, 40), ("c2_w16", {"mfma": 0}, 6),
                                              ("c2_w16", {"fuse_merge": 1}, 40),
                                              ("c2_w16", {"head_dim": 64}, 40),
