@@ -97,8 +97,8 @@ __device__ __forceinline__ void merge_leaf_heads(int lane, int64_t leaf, int h, 
     // Rows in flight per lane and batch: inside the attention kernel registers are scarce; in the
     // merge launch most leaf queries have 5 to 10 partials, and a batch of eight saves them a round
     // trip (whole calls against batches of four, us: 16 leaves 13.54 -> 13.40, 64 leaves 1 % less,
-    // 512 leaves unchanged).  With 16 floats a lane (8 query heads of 128) eight rows would take
-    // 128 registers: four.
+    // 512 leaves unchanged).  With 16 floats a lane (8 query heads of 128) eight rows take 300
+    // registers, one wave per SIMD: 256 leaves 144 -> 143, 16 searches no faster; four.
     constexpr int UNROLL = COHERENT ? (EPL >= 8 ? 2 : 4) : (EPL >= 16 ? 4 : 8);
     const int g_row = lane / LPH;
     auto load_rows = [&](Piece (&v)[UNROLL][EPL / VEC], int64_t base, int k, int cn) {
