@@ -102,6 +102,36 @@ def test_prefill_scores_that_rise_along_the_path(hkv, hq, root, n, copies):
             "prefill rising %d + %d" % (root, n))
 
 
+@pytest.mark.parametrize("n,copies", [(16, 1), (32, 64)])  # work items of 128 and of 256 query rows
+def test_prefill_sum_of_many_equal_weights(n, copies):
+    """300 runs of rows that all have the same weight, another one for every query row: what an
+    addition loses is then the same throughout a binade of the sum and does not average out.
+    lse in closed form.  Bound in units of 2^-24: one rounding per run of the row's sum and eight
+    inside a run; 15 for the weight itself (its argument reaches 6 in three roundings, times
+    ln 2, and one ulp of the exponential); 26 for the logarithm (1 ulp at 12.3) and lse's rounding."""
+    hkv, hq, runs = 8, 64, 300
+    cfg = TreeConfig("sum", hkv, hq, 128, "bf16", 0, 0, 0, 0, 0, None, seed=1)
+    root = 32 * runs
+    tree = Tree(np.array([-1, 0], np.int32), np.array([0, root], np.int64),
+                np.array([root, n], np.int32), np.full(copies, 1, np.int32), root + n)
+    k = np.zeros((root + n, hkv, 128), np.float32)
+    k[1:, :, 0] = -1.0        # row 0 scores 0, all others minus the query's first element
+    rows = n * copies
+    q = np.zeros((rows, hq, 128), np.float32)
+    q[:, :, 0] = np.geomspace(1.2, 44.0, rows * hq).reshape(rows, hq)
+    q = to_bf16_bits(q)
+    a = (q[:, :, 0].astype(np.uint32) << 16).view(np.float32).astype(np.float64)
+    t = root + np.arange(rows) % n   # rows seen besides row 0
+    want = np.log1p(t[:, None] * np.exp(-a / np.sqrt(128.0)))
+    kd = pool_to_device(to_bf16_bits(k))
+    with make_ctx(cfg) as ctx:
+        _, lse, st = gpu_prefill(ctx, tree, kd, torch.zeros_like(kd), to_device(q))
+    assert st.rows_per_item == (128 if copies == 1 else 256)
+    worst = np.abs(lse.cpu().numpy() - want).max()
+    print("case sum of equal weights", n, copies, "lse max-abs %.3g" % worst, flush=True)
+    assert worst <= (runs + 1 + 8 + 15 + 26) * 2.0 ** -24
+
+
 def test_prefill_duplicates_empty_nodes_and_no_queries():
     cfg = TreeConfig("dup", 2, 8, 128, "bf16", 0, 0, 0, 0, 0, None, seed=33)
     tree = Tree(np.array([-1, 0, 0, 2], np.int32), np.array([0, 20, 0, 60], np.int64),
