@@ -27,6 +27,18 @@ ets_status check(const ets_tree& t) {
     return ETS_OK;
 }
 
+// Query rows per work item.  One workgroup is resident per compute unit, so a launch takes as many
+// rounds as its workgroups fill the compute units, and a round costs the cycles that an item of
+// that size spends on a run of 32 rows.  Calls of steps below a path of 960 rows, 8 kv heads x 4
+// query heads, us with 128 / 256 rows per item: 16 steps of 64 tokens 28.4 / 37.2 (one round
+// either way); 16 steps of 65, 96, 128 tokens 48.5 / 37.1, 50.3 / 37.8, 53.8 / 43.3 (two rounds
+// against one); 24 steps of 30 to 100 tokens 49.6 / 66.9 (two each); 256 steps of 16 tokens 177 /
+// 248 (the same items, each of at most 128 rows), of 48 tokens 390 / 305.
+constexpr int64_t kComputeUnits = 256, kPrefillRunSmall = 1350, kPrefillRunLarge = 2008;
+int64_t rounds_cost(int64_t workgroups, int64_t cycles_per_run) {
+    return (workgroups + kComputeUnits - 1) / kComputeUnits * cycles_per_run;
+}
+
 ets_status build(const ets_shape& shape, const ets_tree& tree, PrefillPlan& p,
                  int64_t kv_elem_bytes) {
     const int32_t N = tree.n_nodes, L = tree.n_leaves;
@@ -41,18 +53,16 @@ ets_status build(const ets_shape& shape, const ets_tree& tree, PrefillPlan& p,
     p.item_begin.assign((size_t)L, 0);
     for (int32_t l = 0; l < L; ++l) p.q_ptr[l + 1] = p.q_ptr[l] + p.n_tokens[p.leaf_node[l]];
 
-    // Items of 256 rows need the fewest bytes and instructions per row (512 long ragged items,
-    // 8 heads per kv head: 7.9 ms per launch against 9.4 with 128 rows).  But one workgroup is
-    // resident per compute unit, so a launch of so few items that compute units stay empty
-    // lasts as long as one item, and 128 rows are walked in 0.6 of the time of 256: 16 steps
-    // of 64 tokens (128 items of 256 rows, or 256 of 128) take 28.5 us instead of 38.3.
-    int64_t n_large = 0;
-    for (int32_t l = 0; l < L; ++l)
-        n_large += (p.n_tokens[p.leaf_node[l]] + (int64_t)(kPrefillRowsPerItem / G) - 1) /
-                   (kPrefillRowsPerItem / G);
-    constexpr int64_t kComputeUnits = 256;
-    const int32_t rows = n_large * shape.n_kv_heads <= kComputeUnits ? kPrefillRowsSmall
-                                                                     : kPrefillRowsPerItem;
+    int64_t n_large = 0, n_small = 0;
+    for (int32_t l = 0; l < L; ++l) {
+        const int64_t q_rows = (int64_t)p.n_tokens[p.leaf_node[l]] * G;
+        n_large += (q_rows + kPrefillRowsPerItem - 1) / kPrefillRowsPerItem;
+        n_small += (q_rows + kPrefillRowsSmall - 1) / kPrefillRowsSmall;
+    }
+    const int32_t rows = rounds_cost(n_small * shape.n_kv_heads, kPrefillRunSmall) <
+                                 rounds_cost(n_large * shape.n_kv_heads, kPrefillRunLarge)
+                             ? kPrefillRowsSmall
+                             : kPrefillRowsPerItem;
     const int32_t tq = rows / G;  // query tokens per item
 
     // depth-first position of every node: children (larger ids) in id order

@@ -16,8 +16,8 @@ namespace ets {
 // run's first row; rows of ancestors carry kAncestorRun and are seen by every query.
 // Query token i sees row t of a run iff t < n and kpos + t <= i.
 constexpr int32_t kAncestorRun = -(1 << 30);
-// Query rows (tokens x heads per kv head) of a work item: 256, or 128 when items of 256 would
-// not give every compute unit a workgroup (one is resident per compute unit).
+// Query rows (tokens x heads per kv head) of a work item: 256, or 128 where that takes less time
+// (see rounds_cost in prefill_plan.cpp).
 constexpr int32_t kPrefillRowsPerItem = 256;
 constexpr int32_t kPrefillRowsSmall = 128;
 

@@ -59,6 +59,27 @@ def test_prefill_plan_on_configs(name):
         assert st.unique_kv_bytes == st.unique_tokens * 2 * cfg.n_kv_heads * 128 * 2
 
 
+@pytest.mark.parametrize("steps,tokens,hkv,hq,rows", [
+    # one round of workgroups over the 256 compute units either way: the shorter items
+    (16, 64, 8, 32, 128), (1, 500, 8, 32, 128), (1, 1, 1, 1, 128),
+    # items of 256 rows fit one round, of 128 rows two
+    (16, 65, 8, 32, 256), (16, 128, 8, 32, 256), (32, 64, 8, 32, 256), (17, 32, 8, 64, 256),
+    # two rounds of either; two against three
+    (20, 65, 8, 32, 128), (24, 65, 8, 32, 256),
+    # steps of at most 128 rows are one item either way, however many there are
+    (64, 16, 8, 8, 128), (256, 32, 8, 32, 128), (256, 4, 8, 64, 128),
+    # many steps of more rows
+    (256, 48, 8, 32, 256), (512, 256, 8, 32, 256)])
+def test_prefill_rows_per_item(steps, tokens, hkv, hq, rows):
+    n = np.full(steps + 1, tokens, np.int32)
+    t = Tree(np.array([-1] + [0] * steps, np.int32), np.arange(steps + 1, dtype=np.int64) * tokens, n,
+             np.arange(1, steps + 1, dtype=np.int32), (steps + 1) * tokens)
+    with _ctx(hkv, hq) as ctx:
+        st = ctx.plan_prefill(t.parent, t.tok_offset, t.n_tokens, t.leaf_node)
+        assert st.rows_per_item == rows
+        assert st.n_items == steps * -(-tokens * hq // hkv // rows)
+
+
 def test_prefill_closed_form_counts():
     # root of 40 rows, two children of 70 and 5 rows, leaf queries on both children and
     # on the root itself
