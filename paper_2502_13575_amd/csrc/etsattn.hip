@@ -250,14 +250,14 @@ void launch_wide_attn(const ets_ctx* c, const LaunchArgs& a) {
     for (int64_t y0 = 0; y0 < n_items; y0 += 65535) {
         const unsigned ny = (unsigned)std::min<int64_t>(65535, n_items - y0);
         if (c->kv_format == ETS_KV_FP8_E4M3)
-            hipLaunchKernelGGL((prefill_attn_kernel<true, true, 2>),
+            hipLaunchKernelGGL((prefill_attn_kernel<true, true>),
                                dim3((unsigned)c->shape.n_kv_heads, ny), dim3(kPrefillThreads), 0, a.stream, a.k,
                                a.v, a.pool_tokens, static_cast<const bf16_t*>(a.q), c->d_runs,
                                c->d_wide, (int)y0, g_shift, c->scale * 1.4426950408889634f,
                                c->k_scales, c->v_scales, a.ws_o, nullptr, c->d_ent_order,
                                c->d_ent_base, a.ws_ml);
         else
-            hipLaunchKernelGGL((prefill_attn_kernel<false, true, 2>),
+            hipLaunchKernelGGL((prefill_attn_kernel<false, true>),
                                dim3((unsigned)c->shape.n_kv_heads, ny), dim3(kPrefillThreads), 0, a.stream, a.k,
                                a.v, a.pool_tokens, static_cast<const bf16_t*>(a.q), c->d_runs,
                                c->d_wide, (int)y0, g_shift, c->scale * 1.4426950408889634f,
@@ -859,10 +859,8 @@ ets_status ets_tree_prefill_attn(ets_ctx* ctx, const void* k_pool, const void* v
     // grid: x = kv head, y = item, at most 65535 items per launch
     for (int64_t y0 = 0; y0 < st.n_items; y0 += 65535) {
         const unsigned ny = (unsigned)std::min<int64_t>(65535, st.n_items - y0);
-        const bool small = st.rows_per_item == kPrefillRowsSmall;
-        auto kernel = ctx->kv_format == ETS_KV_FP8_E4M3
-                          ? (small ? prefill_attn_kernel<true, false, 1> : prefill_attn_kernel<true, false, 2>)
-                          : (small ? prefill_attn_kernel<false, false, 1> : prefill_attn_kernel<false, false, 2>);
+        auto kernel = ctx->kv_format == ETS_KV_FP8_E4M3 ? prefill_attn_kernel<true, false>
+                                                        : prefill_attn_kernel<false, false>;
         hipLaunchKernelGGL(kernel, dim3((unsigned)ctx->shape.n_kv_heads, ny), dim3(kPrefillThreads), 0,
                            stream, k_pool, v_pool, pool_tokens, static_cast<const bf16_t*>(q),
                            ctx->d_pre_runs, ctx->d_pre_items, (int)y0, g_shift,

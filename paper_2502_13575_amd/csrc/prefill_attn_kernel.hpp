@@ -3,11 +3,12 @@
 //
 // Scoring a new step with the reward model is a prefill of that step's tokens over the
 // tree of cached steps: query token i of the node sees every row of the node's strict
-// ancestors and rows 0..i of the node itself.  A workgroup takes 256 query rows, or 128 in
-// launches of few items (template parameter NB: blocks of 32 rows per wave; below, NB = 2)
-// (256 / G consecutive tokens x the G query heads of the kv head), walks the ancestors'
-// rows and then the node's own rows up to its last token, 64 rows (two runs of at most
-// 32) at a time through LDS, and keeps the running softmax of its rows in registers:
+// ancestors and rows 0..i of the node itself.  A workgroup takes up to 256 query rows
+// (256 / G consecutive tokens x the G query heads of the kv head) through its runs with 64 rows per
+// wave, or 32 where the item has at most 128 (template parameter NB: blocks of 32 rows per
+// wave; below, NB = 2): the ancestors' rows, then the node's own rows up to its last token, 64
+// rows (two runs of at most 32) at a time through LDS.  It keeps the running softmax of its rows
+// in registers:
 // there are no partial results and no merge, the normalised output leaves at the end.
 // Every K/V row a workgroup reads (512 bytes per kv head) meets 256 query rows, 256 flop
 // per byte: with 128 rows the walk was bound by the 5.8 TB/s at which L2 and the memory
@@ -17,8 +18,8 @@
 // Bound: the issue of instructions next to the matrix cores.  One wave per SIMD owns 64 query
 // rows (two blocks of 32), so that every K and V fragment read from LDS feeds two matrix
 // instructions: with 32 rows per wave, eight waves read 128 KB per run, 640 of the 1 024
-// cycles that the matrix instructions take even without a bank conflict.  Lane l = (n, g), n = l % 32, g = l / 32.  Per run of 32 rows and
-// block of 32 query rows:
+// cycles that the matrix instructions take even without a bank conflict.  Lane l = (n, g),
+// n = l % 32, g = l / 32.  Per run of 32 rows and block of 32 query rows:
 //   S^T = K Q^T     8 x v_mfma_f32_32x32x16_bf16: run rows on M, query rows on N.  A = K
 //                   rows from the LDS tile (lane (n, g): row n, d = 16 kk + 8 g .. + 7),
 //                   B = Q in registers.  Lane (n, g) receives query row n against run
@@ -374,33 +375,36 @@ __device__ __forceinline__ void prefill_unit1(PrefillState<1>& st, const char* _
     if (ETS_RARE(raised)) scale_rows(st, 0);
 }
 
-// FP8: the pools hold E4M3 codes (128-byte rows, 8 bytes per lane and load); the codes are
-// widened while the tile is staged (K to bf16, V straight to the fp16 fragments), the kv
-// head's K scale enters the score scale and its V scale multiplies the normalised rows.
-// DECODE: `items_raw` are CascadeItem (leaf queries ent_order[ent_begin .. + n_ent), at most
-// 256 / G of them), `out` is the partial workspace ws_o, `lse` is unused, and ent_order,
-// ent_base, ws_ml are the decode plan's tables; otherwise `items_raw` are PrefillItem and
-// the last three arguments are unused.
+// LDS of a workgroup: three tile buffers (K rows, behind them the V^T fragments [run][half]) and the
+// ring of run descriptors.
+constexpr int kPrefillKRowB = 16 * kPrefillKRow;  // bytes of a K row (272)
+constexpr int kPrefillKB = 64 * kPrefillKRowB;    // K tile: 64 rows
+constexpr int kPrefillBufB = kPrefillKB + 4 * kVFragHalf;
+constexpr int kPrefillRing = 256;
+
+// A work item, in the terms both modes share: its runs, and the number of row groups (query tokens,
+// or leaf queries) whose G heads make up its query rows.
+struct PrefillWork {
+    int run_begin, run_end, n_grp;
+    int tok0;           // step prefill: first query token, as an index into its node
+    int64_t q_row0;     // and its query row
+    int ent_begin;      // decode: first entry of its leaf queries
+    int slot_off;       // and the partial slot's offset in each
+};
+
+// The work item with 128 NB query rows (32 NB per wave), see prefill_attn_kernel.
 template <bool FP8, bool DECODE, int NB>
-__global__ __launch_bounds__(kPrefillThreads) __attribute__((amdgpu_waves_per_eu(1, 1))) void prefill_attn_kernel(
+__device__ __forceinline__ void prefill_item(
+    const PrefillWork& it, char* __restrict__ smem, u32x4_t* __restrict__ sm_desc,
     const void* __restrict__ k_pool, const void* __restrict__ v_pool, int64_t pool_tokens,
-    const bf16_t* __restrict__ q, const Run* __restrict__ runs,
-    const void* __restrict__ items_raw, int item_base, int g_shift, float scale_log2e_base,
-    HeadScales k_scales, HeadScales v_scales, float* __restrict__ out, float* __restrict__ lse,
-    const int32_t* __restrict__ ent_order, const int32_t* __restrict__ ent_base,
-    float2* __restrict__ ws_ml) {
+    const bf16_t* __restrict__ q, const Run* __restrict__ runs, int g_shift, float scale_log2e_base,
+    const HeadScales& k_scales, const HeadScales& v_scales, float* __restrict__ out,
+    float* __restrict__ lse, const int32_t* __restrict__ ent_order,
+    const int32_t* __restrict__ ent_base, float2* __restrict__ ws_ml) {
     constexpr int D = 128;
     constexpr int WROWS = 32 * NB;         // query rows per wave
-    constexpr int KROW_B = 16 * kPrefillKRow;  // bytes of a K row in LDS (272)
-    constexpr int KS_B = 64 * KROW_B;           // K tile: 64 rows
-    constexpr int BUF_B = KS_B + 4 * kVFragHalf;  // V^T fragments behind it: [run][half]
-    constexpr int RING = 256;
-    static_assert(!DECODE || 4 * WROWS == kWideRowsPerItem, "rows per workgroup");
+    constexpr int KROW_B = kPrefillKRowB, KS_B = kPrefillKB, BUF_B = kPrefillBufB, RING = kPrefillRing;
     static_assert(4 * WROWS == (NB == 2 ? kPrefillRowsPerItem : kPrefillRowsSmall), "rows per workgroup");
-    __shared__ u32x4_t smem_raw[3 * BUF_B / 16];  // three tile buffers
-    __shared__ u32x4_t sm_desc[RING];
-
-    char* smem = reinterpret_cast<char*>(smem_raw);
 
     const int n_kv_heads = (int)gridDim.x;
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -413,25 +417,9 @@ __global__ __launch_bounds__(kPrefillThreads) __attribute__((amdgpu_waves_per_eu
     const int g = lane >> 5;
     const int h = blockIdx.x;
     const float scale_log2e = FP8 ? scale_log2e_base * k_scales.s[h] : scale_log2e_base;
-    // the work item, in the terms both modes share: its runs, and the number of row
-    // groups (query tokens, or leaf queries) whose G heads make up its query rows
-    int run_begin, run_end, n_grp, tok0 = 0, ent_begin = 0, slot_off = 0;
-    int64_t q_row0 = 0;
-    if constexpr (DECODE) {
-        const CascadeItem it = static_cast<const CascadeItem*>(items_raw)[item_base + (int)blockIdx.y];
-        run_begin = it.run_begin;
-        run_end = it.run_end;
-        n_grp = it.n_ent;
-        ent_begin = it.ent_begin;
-        slot_off = it.slot_off;
-    } else {
-        const PrefillItem it = static_cast<const PrefillItem*>(items_raw)[item_base + (int)blockIdx.y];
-        run_begin = it.run_begin;
-        run_end = it.run_end;
-        n_grp = it.n_tok;
-        tok0 = it.tok0;
-        q_row0 = it.q_row0;
-    }
+    const int run_begin = it.run_begin, run_end = it.run_end, n_grp = it.n_grp, tok0 = it.tok0;
+    const int ent_begin = it.ent_begin, slot_off = it.slot_off;
+    const int64_t q_row0 = it.q_row0;
     const int G = 1 << g_shift;
     const int n_q_heads = n_kv_heads << g_shift;
     const int n_runs = run_end - run_begin;
@@ -786,6 +774,57 @@ __global__ __launch_bounds__(kPrefillThreads) __attribute__((amdgpu_waves_per_eu
             __builtin_amdgcn_wave_barrier();
         }
     }
+}
+
+// FP8: the pools hold E4M3 codes (128-byte rows, 8 bytes per lane and load); the codes are
+// widened while the tile is staged (K to bf16, V straight to the fp16 fragments), the kv
+// head's K scale enters the score scale and its V scale multiplies the normalised rows.
+// DECODE: `items_raw` are CascadeItem (leaf queries ent_order[ent_begin .. + n_ent), at most
+// 256 / G of them), `out` is the partial workspace ws_o, `lse` is unused, and ent_order,
+// ent_base, ws_ml are the decode plan's tables; otherwise `items_raw` are PrefillItem and
+// the last three arguments are unused.
+// An item of at most 128 query rows (the last block of a node, a short step, a segment of few leaf
+// queries) is walked with 32 rows per wave: 1 350 cycles per run instead of the 2 008 that a wave
+// of 64 rows takes however many of them are in use.  Calls against 64 rows per wave throughout, us:
+// 256 steps of 16 tokens, 4 heads per kv head, 248 -> 173; of 20 to 150 tokens 547 -> 516; of 32 to
+// 256 tokens, 1 head, 319 -> 298; 8 heads 1 484 -> 1 466; decode of 256 leaf queries with
+// segments of more than 16 query rows as wide items 183 -> 163.
+template <bool FP8, bool DECODE>
+__global__ __launch_bounds__(kPrefillThreads) __attribute__((amdgpu_waves_per_eu(1, 1))) void prefill_attn_kernel(
+    const void* __restrict__ k_pool, const void* __restrict__ v_pool, int64_t pool_tokens,
+    const bf16_t* __restrict__ q, const Run* __restrict__ runs,
+    const void* __restrict__ items_raw, int item_base, int g_shift, float scale_log2e_base,
+    HeadScales k_scales, HeadScales v_scales, float* __restrict__ out, float* __restrict__ lse,
+    const int32_t* __restrict__ ent_order, const int32_t* __restrict__ ent_base,
+    float2* __restrict__ ws_ml) {
+    static_assert(!DECODE || kPrefillRowsPerItem == kWideRowsPerItem, "rows per workgroup");
+    __shared__ u32x4_t smem[3 * kPrefillBufB / 16];
+    __shared__ u32x4_t sm_desc[kPrefillRing];
+    PrefillWork work{};
+    if constexpr (DECODE) {
+        const CascadeItem it = static_cast<const CascadeItem*>(items_raw)[item_base + (int)blockIdx.y];
+        work.run_begin = it.run_begin;
+        work.run_end = it.run_end;
+        work.n_grp = it.n_ent;
+        work.ent_begin = it.ent_begin;
+        work.slot_off = it.slot_off;
+    } else {
+        const PrefillItem it = static_cast<const PrefillItem*>(items_raw)[item_base + (int)blockIdx.y];
+        work.run_begin = it.run_begin;
+        work.run_end = it.run_end;
+        work.n_grp = it.n_tok;
+        work.tok0 = it.tok0;
+        work.q_row0 = it.q_row0;
+    }
+    char* const lds = reinterpret_cast<char*>(smem);
+    if (work.n_grp << g_shift <= kPrefillRowsSmall)
+        prefill_item<FP8, DECODE, 1>(work, lds, sm_desc, k_pool, v_pool, pool_tokens, q, runs, g_shift,
+                                     scale_log2e_base, k_scales, v_scales, out, lse, ent_order, ent_base,
+                                     ws_ml);
+    else
+        prefill_item<FP8, DECODE, 2>(work, lds, sm_desc, k_pool, v_pool, pool_tokens, q, runs, g_shift,
+                                     scale_log2e_base, k_scales, v_scales, out, lse, ent_order, ent_base,
+                                     ws_ml);
 }
 
 }  // namespace ets
