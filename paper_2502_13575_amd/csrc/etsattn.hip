@@ -374,7 +374,10 @@ void launch_merge_dg(ets_ctx* c, const LaunchArgs& a) {
     const int n_leaves = (int)c->plan.stats.n_leaves;
     // one wave per (leaf query, kv head), four leaf queries of one kv head to a workgroup
     const unsigned grid = (unsigned)((n_leaves + (int64_t)3) / 4 * c->shape.n_kv_heads);
-    hipLaunchKernelGGL((merge_kernel<D, G>), dim3(grid), dim3(256), 0, a.stream, c->d_part_base,
+    constexpr int kFew = D * G / 64 >= 16 ? kMergeBatch : kMergeBatchFewWaves;
+    const auto kernel = (int64_t)n_leaves * c->shape.n_kv_heads <= kMergeFewWaves
+                            ? merge_kernel<D, G, kFew> : merge_kernel<D, G, kMergeBatch>;
+    hipLaunchKernelGGL(kernel, dim3(grid), dim3(256), 0, a.stream, c->d_part_base,
                        n_leaves, c->shape.n_kv_heads, a.ws_o, a.ws_ml, a.out, c->out_bf16 ? 1 : 0,
                        a.lse, c->v_scales);
 }

@@ -49,7 +49,8 @@ constexpr int kDeviceScope = 16;
 // COHERENT: the partials were stored by other workgroups of this very launch, with
 // device-scope stores that had completed before their writer counted itself in; they are
 // read with device-scope loads (byte offsets into the workspace are below 2^32 then).
-template <int D, int G, bool COHERENT = false>
+// UNROLL: rows in flight per lane and batch.
+template <int D, int G, int UNROLL, bool COHERENT = false>
 __device__ __forceinline__ void merge_leaf_heads(int lane, int64_t leaf, int h, int p0, int p1,
                                                  int n_q_heads, const float* ws_o,
                                                  const float2* ws_ml, int64_t n_ws_rows, void* out,
@@ -94,12 +95,6 @@ __device__ __forceinline__ void merge_leaf_heads(int lane, int64_t leaf, int h, 
     // the first round's (m, l) pairs and the first batch of rows go out together, before
     // anything is reduced (a leaf rarely has more partials than one round holds), so that a
     // typical leaf costs two or three memory round trips.
-    // Rows in flight per lane and batch: inside the attention kernel registers are scarce; in the
-    // merge launch most leaf queries have 5 to 10 partials, and a batch of eight saves them a round
-    // trip (whole calls against batches of four, us: 16 leaves 13.54 -> 13.40, 64 leaves 1 % less,
-    // 512 leaves unchanged).  With 16 floats a lane (8 query heads of 128) eight rows take 300
-    // registers, one wave per SIMD: 256 leaves 144 -> 143, 16 searches no faster; four.
-    constexpr int UNROLL = COHERENT ? (EPL >= 8 ? 2 : 4) : (EPL >= 16 ? 4 : 8);
     const int g_row = lane / LPH;
     auto load_rows = [&](Piece (&v)[UNROLL][EPL / VEC], int64_t base, int k, int cn) {
 #pragma unroll
@@ -203,6 +198,12 @@ __device__ __forceinline__ void merge_leaf_heads(int lane, int64_t leaf, int h, 
             empty ? -INFINITY : (ms + __builtin_amdgcn_logf(ls)) * 0.6931471805599453f;
 }
 
+// Rows in flight where the attention kernel merges, whose registers are scarce.
+template <int D, int G>
+constexpr int fused_merge_batch() {
+    return D * G / 64 >= 8 ? 2 : 4;
+}
+
 // Workgroup b takes four leaf queries of kv head b % n_kv_heads.  Workgroups go to the eight XCDs
 // in turn, in the attention kernel (grid x = kv head) as here, so with eight kv heads a head's
 // partials are merged behind the L2 they were written through; with other counts the mapping is
@@ -211,7 +212,18 @@ __device__ __forceinline__ void merge_leaf_heads(int lane, int64_t leaf, int h, 
 // 128, against four consecutive (leaf, head) pairs to a workgroup, us: 16 leaves 14.00 -> 13.54,
 // 64 leaves of one pruned step 59.1 -> 55.9, 16 searches of 256 leaves with 64 query heads
 // 2 057 -> 2 038; 64 to 512 leaves of one search within 0.6 %.
-template <int D, int G>
+//
+// Rows in flight (UNROLL): most leaf queries have 5 to 10 partials, and a batch of eight saves them
+// a round trip.  But with eight floats a lane it takes 166 registers instead of 96, three waves
+// per SIMD instead of five, and with four 95 instead of 63, which costs more once the chip has more
+// than a wave per SIMD to hold.  So eight up to 1 024 waves and four above.  The launch with batches
+// of four -> of eight, us, by (head_dim, query heads per kv head), 8 kv heads: 64 leaves (128, 4)
+// 7.2 -> 6.8, (64, 8) 7.2 -> 6.9; 100 leaves (128, 4) 7.0 -> 6.7, (64, 8) 7.8 -> 7.3, others the same;
+// 512 leaves (128, 4) 16.7 -> 17.8, (64, 8) 16.2 -> 16.9, (64, 4) 10.9 -> 11.6, (128, 2) 11.0 -> 11.8.
+// With 16 floats a lane (8 query heads of 128) eight rows take 300 registers: always four.
+constexpr int kMergeBatch = 4, kMergeBatchFewWaves = 8;
+constexpr int64_t kMergeFewWaves = 1024;  // four SIMDs on each of 256 compute units
+template <int D, int G, int UNROLL>
 __global__ __launch_bounds__(256) void merge_kernel(const int32_t* __restrict__ part_base,
                                                     int n_leaves, int n_kv_heads,
                                                     const float* __restrict__ ws_o,
@@ -224,7 +236,7 @@ __global__ __launch_bounds__(256) void merge_kernel(const int32_t* __restrict__ 
     const int h = (int)(blockIdx.x % (unsigned)n_kv_heads);
     const int leaf = (int)(blockIdx.x / (unsigned)n_kv_heads) * 4 + wave;
     if (leaf >= n_leaves) return;
-    merge_leaf_heads<D, G>(lane, leaf, h, part_base[leaf], part_base[leaf + 1], n_kv_heads * G, ws_o,
+    merge_leaf_heads<D, G, UNROLL>(lane, leaf, h, part_base[leaf], part_base[leaf + 1], n_kv_heads * G, ws_o,
                            ws_ml, 0, out, out_bf16 != 0, lse, v_scales.s[h]);
 }
 

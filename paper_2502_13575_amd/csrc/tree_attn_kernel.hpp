@@ -488,20 +488,24 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void t
                     const int m_p1 = m_p0 + __shfl(np, src, 64);
                     switch (g_shift) {
                         case 0:
-                            merge_leaf_heads<D, 1, true>(lane, m_leaf, h, m_p0, m_p1, n_q_heads, ws_o,
-                                                   ws_ml, tail.n_ws_rows, tail.out, tail.out_bf16 != 0, tail.lse, out_scale);
+                            merge_leaf_heads<D, 1, fused_merge_batch<D, 1>(), true>(
+                                lane, m_leaf, h, m_p0, m_p1, n_q_heads, ws_o, ws_ml, tail.n_ws_rows,
+                                tail.out, tail.out_bf16 != 0, tail.lse, out_scale);
                             break;
                         case 1:
-                            merge_leaf_heads<D, 2, true>(lane, m_leaf, h, m_p0, m_p1, n_q_heads, ws_o,
-                                                   ws_ml, tail.n_ws_rows, tail.out, tail.out_bf16 != 0, tail.lse, out_scale);
+                            merge_leaf_heads<D, 2, fused_merge_batch<D, 2>(), true>(
+                                lane, m_leaf, h, m_p0, m_p1, n_q_heads, ws_o, ws_ml, tail.n_ws_rows,
+                                tail.out, tail.out_bf16 != 0, tail.lse, out_scale);
                             break;
                         case 2:
-                            merge_leaf_heads<D, 4, true>(lane, m_leaf, h, m_p0, m_p1, n_q_heads, ws_o,
-                                                   ws_ml, tail.n_ws_rows, tail.out, tail.out_bf16 != 0, tail.lse, out_scale);
+                            merge_leaf_heads<D, 4, fused_merge_batch<D, 4>(), true>(
+                                lane, m_leaf, h, m_p0, m_p1, n_q_heads, ws_o, ws_ml, tail.n_ws_rows,
+                                tail.out, tail.out_bf16 != 0, tail.lse, out_scale);
                             break;
                         default:
-                            merge_leaf_heads<D, 8, true>(lane, m_leaf, h, m_p0, m_p1, n_q_heads, ws_o,
-                                                   ws_ml, tail.n_ws_rows, tail.out, tail.out_bf16 != 0, tail.lse, out_scale);
+                            merge_leaf_heads<D, 8, fused_merge_batch<D, 8>(), true>(
+                                lane, m_leaf, h, m_p0, m_p1, n_q_heads, ws_o, ws_ml, tail.n_ws_rows,
+                                tail.out, tail.out_bf16 != 0, tail.lse, out_scale);
                             break;
                     }
                     if (lane == 0) tail.arrived[(int64_t)m_leaf * n_kv_heads + h] = 0;

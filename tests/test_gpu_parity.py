@@ -297,6 +297,26 @@ def test_merge_of_every_partial_count(hkv, hq, d, n):
             oo.reshape(-1, d), ol.reshape(-1), "bf16", "merge")
 
 
+@pytest.mark.parametrize("hkv,hq,d,n,copies", [(8, 32, 128, 19, 7), (8, 64, 64, 18, 8), (2, 4, 128, 21, 25),
+                                               (5, 20, 64, 17, 13), (8, 8, 64, 19, 7)])
+def test_merge_of_every_partial_count_in_a_large_launch(hkv, hq, d, n, copies):
+    """As above with every leaf query repeated until the merge has more than the 1 024 waves up to
+    which it keeps eight rows in flight."""
+    from workload import Tree
+    tree = Tree(np.arange(-1, n - 1, dtype=np.int32), np.arange(n, dtype=np.int64) * 130,
+                np.full(n, 130, np.int32), np.tile(np.arange(n, dtype=np.int32), copies), n * 130)
+    assert n * copies * hkv > 1024
+    cfg = TreeConfig("merge", hkv, hq, d, "bf16", 0, 0, 0, 0, 0, None, seed=59 + n)
+    k, v, q = make_values_host(cfg, tree)
+    oo, ol = oracle_full(cfg, tree, k, v, q)
+    print("case merge", hkv, hq, d, n, copies, flush=True)
+    with make_ctx(cfg) as ctx:
+        out, lse, st = gpu_attn(ctx, tree, pool_to_device(k), pool_to_device(v), to_device(q))
+    assert st.n_partials >= copies * n
+    compare(out.cpu().numpy().reshape(-1, d), lse.cpu().numpy().reshape(-1),
+            oo.reshape(-1, d), ol.reshape(-1), "bf16", "merge")
+
+
 @pytest.mark.parametrize("name,opts,steps", [("c2_w16", {}, 40), ("c2_w16", {"mfma": 0}, 6),
                                              ("c2_w16", {"fuse_merge": 1}, 40),
                                              ("c2_w16", {"head_dim": 64}, 40),
