@@ -83,15 +83,22 @@ constexpr int kPrefillThreads = 256;  // four waves of 64 query rows
 // instruction and its neighbours are the code's own business: mfma_result_wait() before the
 // vector unit reads a result that may be younger than 18 issue slots, and no vector instruction
 // that writes an operand within two slots of its use.  (Accumulating into the same registers
-// needs none; fragments come from LDS and are waited for as usual.)
+// needs none; fragments come from LDS and are waited for as usual.)  Where a sequence of them starts,
+// behind code that may copy registers, the first one waits its two slots itself (0 to 0.4 % of a
+// call), and the rows are waited for where the loop is left.  Inside a sequence it rests on the
+// register allocator not placing a copy in front of an instruction, as is the case with the compiler
+// of ROCm 7.2.0; tests/test_matrix_wait_states.py follows every path of the built code.
 __device__ __forceinline__ void mfma_scores_first(f32x16_t& s, u32x4_t k, bf16x8_t q) {
-    asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, 0" : "=&v"(s) : "a"(k), "a"(q));
+    asm volatile("s_nop 1\n\tv_mfma_f32_32x32x16_bf16 %0, %1, %2, 0" : "=&v"(s) : "a"(k), "a"(q));
 }
 __device__ __forceinline__ void mfma_scores(f32x16_t& s, u32x4_t k, bf16x8_t q) {
     asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+v"(s) : "a"(k), "a"(q));
 }
 __device__ __forceinline__ void mfma_apply(f32x16_t& o, u32x4_t v, u32x4_t p) {
     asm volatile("v_mfma_f32_32x32x16_f16 %0, %1, %2, %0" : "+v"(o) : "a"(v), "v"(p));
+}
+__device__ __forceinline__ void mfma_apply_first(f32x16_t& o, u32x4_t v, u32x4_t p) {
+    asm volatile("s_nop 1\n\tv_mfma_f32_32x32x16_f16 %0, %1, %2, %0" : "+v"(o) : "a"(v), "v"(p));
 }
 __device__ __forceinline__ void mfma_result_wait(f32x16_t (&o)[4]) {
     asm volatile("s_nop 15\n\ts_nop 15" : "+v"(o[0]), "+v"(o[1]), "+v"(o[2]), "+v"(o[3]));
@@ -300,7 +307,8 @@ __device__ __forceinline__ void prefill_unit(PrefillState<2>& st, const char* __
     for (int i = 0; i < 16; ++i) {
         // half t of the run, d block x, query block j
         const int t = i >> 3, x = (i >> 1) & 3, j = i & 1;
-        mfma_apply(st.oacc[j][x], vf[4 * t + x], pf_cur[j][t]);
+        if (i == 0) mfma_apply_first(st.oacc[j][x], vf[4 * t + x], pf_cur[j][t]);
+        else mfma_apply(st.oacc[j][x], vf[4 * t + x], pf_cur[j][t]);
         __builtin_amdgcn_sched_barrier(0);
         if (j == 1) st.kf[i >> 1] = load16(k_after + 32 * (i >> 1));
         if (i == 2 && ETS_RARE(hidden)) mask(st.s[1], 1);
@@ -359,7 +367,8 @@ __device__ __forceinline__ void prefill_unit1(PrefillState<1>& st, const char* _
     bool raised = false;
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
-        mfma_apply(st.oacc[0][i & 3], vf[i], pf[0][i >> 2]);
+        if (i == 0) mfma_apply_first(st.oacc[0][i & 3], vf[i], pf[0][i >> 2]);
+        else mfma_apply(st.oacc[0][i & 3], vf[i], pf[0][i >> 2]);
         __builtin_amdgcn_sched_barrier(0);
         st.kf[i] = load16(k_after + 32 * i);
         if (i == 2 && ETS_RARE(hidden)) mask(s_next, 0);
@@ -712,6 +721,10 @@ __device__ __forceinline__ void prefill_item(
             do_tile(tile, raw1, raw0, computes);
             if (++tile >= n_tiles) break;
         }
+        // (here, where the loop is left, so that no copy of the rows comes before it)
+        if constexpr (decltype(computes)::value)
+#pragma unroll
+            for (int j = 0; j < NB; ++j) mfma_result_wait(st.oacc[j]);
         __syncthreads();  // every wave is done with the tiles: the epilogue reuses the buffers
     };
     if (!active) {
@@ -729,7 +742,6 @@ __device__ __forceinline__ void prefill_item(
     const int col = (lane & 31) * 4;
 #pragma unroll
     for (int j = 0; j < NB; ++j) {
-        mfma_result_wait(st.oacc[j]);
         const int r_lane = WROWS * w + 32 * j + n;
         // row of the lane's query in `out` (and in lse / ws_ml)
         int64_t out_row = q_row0 + group_of(r_lane);
