@@ -585,10 +585,10 @@ __device__ __forceinline__ void prefill_item(
         const int kpos = __builtin_amdgcn_readfirstlane(e.kpos);
         return (n_valid != 32) | (kpos + 31 > i_first);  // (no branch)
     };
+    // (three matrix instructions, 24 issue slots, stand between a block's scores and its mask)
     auto mask = [&](f32x16_t& s, int j, const Extent& e) ETS_INLINE {
         int lim = e.n;
         if constexpr (!DECODE) lim = min(lim, tok0 + group_of(WROWS * w + 32 * j + n) - e.kpos + 1);
-        mfma_result_wait(s);
         prefill_mask(s, g, lim);
     };
     auto n_kpos = [&](int idx) ETS_INLINE {
