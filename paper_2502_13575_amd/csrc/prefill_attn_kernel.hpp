@@ -24,9 +24,11 @@
 //                   rows from the LDS tile (lane (n, g): row n, d = 16 kk + 8 g .. + 7),
 //                   B = Q in registers.  Lane (n, g) receives query row n against run
 //                   rows 8 c + 4 g + r (c, r = 0..3);
-//   mask            run row t counts iff t < n_run and kpos + t <= i_row, kpos being the
-//                   run's position inside the node (ancestors: always).  Runs that are seen
-//                   in full, nearly all, branch past it;
+//   hide            rows past the end of a short run (t >= n_run) get -3.4e38 from one more matrix
+//                   instruction, in every run alike: with steps of some forty tokens every second
+//                   run is a short one;
+//   mask            rows of the querying node: row t counts iff kpos + t <= i_row, kpos being
+//                   the run's position inside the node.  Runs that are seen in full branch past it;
 //   softmax         against a per-row reference that is raised only when a score exceeds
 //                   it by 2^8 in weight (then one cross-lane exchange);
 //   O^T += V^T P^T  8 x v_mfma_f32_32x32x16_f16: d on M (4 blocks of 32), query rows on
@@ -93,6 +95,10 @@ __device__ __forceinline__ void mfma_scores_first(f32x16_t& s, u32x4_t k, bf16x8
 }
 __device__ __forceinline__ void mfma_scores(f32x16_t& s, u32x4_t k, bf16x8_t q) {
     asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+v"(s) : "a"(k), "a"(q));
+}
+// s += rows x low, see `missing` in prefill_item.
+__device__ __forceinline__ void mfma_hide(f32x16_t& s, u32x2_t rows, u32x2_t low) {
+    asm volatile("s_nop 1\n\tv_mfma_f32_32x32x8_bf16 %0, %1, %2, %0" : "+v"(s) : "v"(rows), "a"(low));
 }
 __device__ __forceinline__ void mfma_apply(f32x16_t& o, u32x4_t v, u32x4_t p) {
     asm volatile("v_mfma_f32_32x32x16_f16 %0, %1, %2, %0" : "+v"(o) : "a"(v), "v"(p));
@@ -250,14 +256,16 @@ __device__ __forceinline__ void weight_end(PrefillState<NB>& st, u32x4_t (&pf)[2
 //   v_run, k_after   LDS byte addresses: the lane's slot of run u's V^T fragments, and its row of
 //                    run u + 2's K
 //   fill(k)          k = 0..15: the caller's work beside A;  fill_b(i), i = 0..15: beside B
-//   hidden, mask(s, j)  whether rows of run u + 1 are hidden from a query row, and what hides
+//   missing, low     operands of mfma_hide for run u + 1
+//   hidden, mask(s, j)  whether rows of run u + 1 are newer than a query token, and what hides
 //                    them from block j's scores s
 template <class Fill, class Mask, class Before, class FillB>
 __device__ __forceinline__ void prefill_unit(PrefillState<2>& st, const char* __restrict__ v_run,
                                              const char* __restrict__ k_after,
                                              u32x4_t (&pf_cur)[2][2], u32x4_t (&pf)[2][2],
-                                             float scale_log2e, float raise_margin, bool hidden,
-                                             Fill fill, Mask mask, Before before_b, FillB fill_b) {
+                                             float scale_log2e, float raise_margin, u32x2_t missing,
+                                             u32x2_t low, bool hidden, Fill fill, Mask mask,
+                                             Before before_b, FillB fill_b) {
     u32x4_t vf[8];
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
@@ -271,6 +279,7 @@ __device__ __forceinline__ void prefill_unit(PrefillState<2>& st, const char* __
         fill(kk);
         __builtin_amdgcn_sched_barrier(0);
     }
+    mfma_hide(st.s[0], missing, low);
     bool raised0 = false, raised1 = false;
 #pragma unroll
     for (int kk = 0; kk < 8; ++kk) {
@@ -289,6 +298,7 @@ __device__ __forceinline__ void prefill_unit(PrefillState<2>& st, const char* __
         if (kk >= 8 - kEarlyWeights) weight_begin(st, st.s[0], 0, kk - 8 + kEarlyWeights, scale_log2e);
         __builtin_amdgcn_sched_barrier(0);
     }
+    mfma_hide(st.s[1], missing, low);
     before_b();
     __builtin_amdgcn_sched_barrier(0);
     // the other weights of block 0, then those of block 1 that are not late
@@ -341,8 +351,9 @@ __device__ __forceinline__ void prefill_unit(PrefillState<2>& st, const char* __
 template <int ODD, class Fill, class Mask, class Before, class FillB>
 __device__ __forceinline__ void prefill_unit1(PrefillState<1>& st, const char* __restrict__ v_run,
                                               const char* __restrict__ k_after, u32x4_t (&pf)[2][2],
-                                              float scale_log2e, float raise_margin, bool hidden,
-                                              Fill fill, Mask mask, Before before_b, FillB fill_b) {
+                                              float scale_log2e, float raise_margin, u32x2_t missing,
+                                              u32x2_t low, bool hidden, Fill fill, Mask mask,
+                                              Before before_b, FillB fill_b) {
     u32x4_t vf[8];
     f32x16_t& s_cur = st.s[ODD];
     f32x16_t& s_next = st.s[1 - ODD];
@@ -361,6 +372,7 @@ __device__ __forceinline__ void prefill_unit1(PrefillState<1>& st, const char* _
         fill(2 * kk + 1);
         __builtin_amdgcn_sched_barrier(0);
     }
+    mfma_hide(s_next, missing, low);
     weight_end(st, pf, 0, 15);
     before_b();
     __builtin_amdgcn_sched_barrier(0);
@@ -456,7 +468,7 @@ __device__ __forceinline__ void prefill_item(
             return __builtin_bit_cast(u32x4_t, __builtin_amdgcn_raw_buffer_load_b128(rs, off, 0, 0));
     };
     // a run's rows through a descriptor that covers exactly the run: rows past the end of
-    // a short run read as zero (and are masked); an empty run (past the end of the
+    // a short run read as zero (and are hidden); an empty run (past the end of the
     // list) is staged as zeros.  Always eight loads (an empty run's descriptor covers nothing:
     // every lane reads zero without a memory access), so that the number of loads in
     // flight is known at every wait.
@@ -568,7 +580,7 @@ __device__ __forceinline__ void prefill_item(
     }
     __syncthreads();  // descriptors and the first tile are in LDS; of the second, K is
 
-    // Which rows of a run are hidden: t >= n, and in step prefill kpos + t > the query token's
+    // Which rows of a run do not count: t >= n, and in step prefill kpos + t > the query token's
     // index (kpos: the run's position inside the querying node).
     struct Extent {
         int n, kpos;  // of one run, uniform
@@ -579,17 +591,27 @@ __device__ __forceinline__ void prefill_item(
         return e;
     };
     auto hides = [&](const Extent& e) ETS_INLINE -> bool {
+        if constexpr (DECODE) return false;  // the query is newer than every row
         // (once more said to be uniform, see rsrc_of)
-        const int n_valid = __builtin_amdgcn_readfirstlane(e.n);
-        if constexpr (DECODE) return n_valid != 32;  // the query is newer than every row
         const int kpos = __builtin_amdgcn_readfirstlane(e.kpos);
-        return (n_valid != 32) | (kpos + 31 > i_first);  // (no branch)
+        return kpos + 31 > i_first;
     };
     // (three matrix instructions, 24 issue slots, stand between a block's scores and its mask)
     auto mask = [&](f32x16_t& s, int j, const Extent& e) ETS_INLINE {
-        int lim = e.n;
-        if constexpr (!DECODE) lim = min(lim, tok0 + group_of(WROWS * w + 32 * j + n) - e.kpos + 1);
-        prefill_mask(s, g, lim);
+        prefill_mask(s, g, tok0 + group_of(WROWS * w + 32 * j + n) - e.kpos + 1);
+    };
+    // Rows past the end of a short run: they read as zero and score zero, and an outer product of
+    // one contraction slot adds -3.4e38 to them, for every run alike.  `missing`: A operand,
+    // 1 in the slot for those rows; `low`: B operand, the number in every column.  (A compare per
+    // score behind a branch took 2 to 9 % more on steps of 25 to 150 tokens, 262 steps of 24..80
+    // tokens over 4 kv heads 587 us -> 533; where all runs are full the instruction costs 0 to 1 %.)
+    const int row_or_none = g == 0 ? n : -1;
+    u32x2_t low = {g == 0 ? 0xFF7Fu : 0u, 0u};
+    asm volatile("" : "+a"(low));
+    auto missing_of = [&](const Extent& e) ETS_INLINE {
+        u32x2_t r = {row_or_none >= __builtin_amdgcn_readfirstlane(e.n) ? 0x3F80u : 0u, 0u};
+        asm volatile("" : "+v"(r));  // (here, not next to the matrix instruction)
+        return r;
     };
     auto n_kpos = [&](int idx) ETS_INLINE {
         return reinterpret_cast<const u32x2_t*>(desc_at(idx))[1];
@@ -614,6 +636,7 @@ __device__ __forceinline__ void prefill_item(
         e_next = extent_of(n_kpos(0));
 #pragma unroll
         for (int j = 0; j < NB; ++j) {
+            mfma_hide(st.s[j], missing_of(e_next), low);
             mfma_result_wait(st.s[j]);
             if (hides(e_next)) mask(st.s[j], j, e_next);
             prefill_raise(st, j, prefill_max(st.s[j]), scale_log2e);
@@ -682,19 +705,19 @@ __device__ __forceinline__ void prefill_item(
             const Extent e1 = e_next;
             auto mask1 = [&](f32x16_t& s, int j) ETS_INLINE { mask(s, j, e1); };
             if constexpr (NB == 2)
-                prefill_unit(st, vs, ks, pf_a, pf_b, scale_log2e, raise_margin, hides(e1), finish, mask1,
-                             []() { __syncthreads(); }, loads);
+                prefill_unit(st, vs, ks, pf_a, pf_b, scale_log2e, raise_margin, missing_of(e1), low,
+                             hides(e1), finish, mask1, []() { __syncthreads(); }, loads);
             else
-                prefill_unit1<0>(st, vs, ks, pf_a, scale_log2e, raise_margin, hides(e1), finish, mask1,
-                                 []() { __syncthreads(); }, loads);
+                prefill_unit1<0>(st, vs, ks, pf_a, scale_log2e, raise_margin, missing_of(e1), low,
+                                 hides(e1), finish, mask1, []() { __syncthreads(); }, loads);
             const Extent e2 = e_next;
             auto mask2 = [&](f32x16_t& s, int j) ETS_INLINE { mask(s, j, e2); };
             if constexpr (NB == 2)
                 prefill_unit(st, vs + 2 * kVFragHalf, ks + 32 * KROW_B, pf_b, pf_a, scale_log2e,
-                             raise_margin, hides(e2), begin, mask2, []() {}, descs);
+                             raise_margin, missing_of(e2), low, hides(e2), begin, mask2, []() {}, descs);
             else
                 prefill_unit1<1>(st, vs + 2 * kVFragHalf, ks + 32 * KROW_B, pf_b, scale_log2e,
-                                 raise_margin, hides(e2), begin, mask2, []() {}, descs);
+                                 raise_margin, missing_of(e2), low, hides(e2), begin, mask2, []() {}, descs);
         } else {
 #pragma unroll
             for (int x = 4; x < 8; ++x) stage_v(v_dst + nxt, oth, x);
