@@ -80,6 +80,23 @@ def test_prefill_rows_per_item(steps, tokens, hkv, hq, rows):
         assert st.n_items == steps * -(-tokens * hq // hkv // rows)
 
 
+@pytest.mark.parametrize("lens,rows,n_items", [
+    # three rounds of 256-row items against four of 128 rows, but only 360 of the 544 are long
+    # and the others, of at most 64 rows, fit the gaps
+    ([20, 33] * 22 + [33], 256, 544),
+    # three rounds against four, 336 long and 336 of 64 rows in turn
+    ([40] * 42, 128, 1008)])
+def test_prefill_rows_per_item_when_rounds_are_partly_filled(lens, rows, n_items):
+    n = len(lens)
+    n_tok = np.array([640] + lens, np.int32)
+    off = np.concatenate([[0], np.cumsum(n_tok)[:-1]]).astype(np.int64)
+    t = Tree(np.array([-1] + [0] * n, np.int32), off, n_tok, np.arange(1, n + 1, dtype=np.int32),
+             int(n_tok.sum()))
+    with _ctx(8, 64) as ctx:
+        st = _check(ctx, t, tokens=[0, 19, 31, 32, 39])
+        assert st.rows_per_item == rows and st.n_items * 8 == n_items
+
+
 def test_prefill_closed_form_counts():
     # root of 40 rows, two children of 70 and 5 rows, leaf queries on both children and
     # on the root itself
