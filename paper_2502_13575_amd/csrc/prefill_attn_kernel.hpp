@@ -640,10 +640,18 @@ __device__ __forceinline__ void prefill_item(
             mfma_result_wait(st.s[j]);
             if (hides(e_next)) mask(st.s[j], j, e_next);
             prefill_raise(st, j, prefill_max(st.s[j]), scale_log2e);
-            // (with one block the weights belong to the first stage)
+            // (with one block the weights belong to the first stage; all exponentials ahead of the
+            // sums, so that they do not wait for one another)
+            const int n_weights = NB == 1 ? 0 : j == 0 ? 16 : 16 - kLateWeights;
+            float p[16];
 #pragma unroll
-            for (int i = 0; NB == 2 && i < (j == 0 ? 16 : 16 - kLateWeights); ++i) {
+            for (int i = 0; i < n_weights; ++i) {
                 weight_begin(st, st.s[j], j, i, scale_log2e);
+                p[i] = st.p_last;
+            }
+#pragma unroll
+            for (int i = 0; i < n_weights; ++i) {
+                st.p_last = p[i];
                 weight_end(st, pf_a, j, i);
             }
         }
@@ -757,11 +765,12 @@ __device__ __forceinline__ void prefill_item(
     first_run();
     walk(std::true_type{});
 
-    // rows out through the wave's own LDS region (16 rows padded to 132 floats, two passes per
-    // block), so that whole 512-byte rows are stored: normalised in step prefill,
-    // unnormalised next to (m, l) in decode
+    // rows out through the wave's own LDS region (a block's 32 rows padded to 132 floats), so that
+    // whole 512-byte rows are stored: normalised in step prefill, unnormalised next to (m, l) in
+    // decode
     constexpr int OROW = 132;
-    float* ob = reinterpret_cast<float*>(smem) + w * (16 * OROW);
+    static_assert(4 * 32 * OROW * 4 <= 3 * BUF_B, "four regions");
+    float* ob = reinterpret_cast<float*>(smem) + w * (32 * OROW);
     const int col = (lane & 31) * 4;
 #pragma unroll
     for (int j = 0; j < NB; ++j) {
@@ -784,30 +793,25 @@ __device__ __forceinline__ void prefill_item(
                 lse[out_row] = (st.m[j] * scale_log2e + __builtin_amdgcn_logf(l)) * 0.6931471805599453f;
         }
 #pragma unroll
-        for (int pass = 0; pass < 2; ++pass) {
-            if ((n >> 4) == pass) {
+        for (int x = 0; x < 4; ++x)
 #pragma unroll
-                for (int x = 0; x < 4; ++x)
+            for (int c = 0; c < 4; ++c)
+                *reinterpret_cast<float4*>(ob + n * OROW + 32 * x + 8 * c + 4 * g) =
+                    make_float4(st.oacc[j][x][4 * c] * inv, st.oacc[j][x][4 * c + 1] * inv,
+                                st.oacc[j][x][4 * c + 2] * inv, st.oacc[j][x][4 * c + 3] * inv);
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
 #pragma unroll
-                    for (int c = 0; c < 4; ++c)
-                        *reinterpret_cast<float4*>(ob + (n & 15) * OROW + 32 * x + 8 * c + 4 * g) =
-                            make_float4(st.oacc[j][x][4 * c] * inv, st.oacc[j][x][4 * c + 1] * inv,
-                                        st.oacc[j][x][4 * c + 2] * inv, st.oacc[j][x][4 * c + 3] * inv);
-            }
-            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-            __builtin_amdgcn_wave_barrier();
-#pragma unroll
-            for (int k = 0; k < 8; ++k) {
-                const int rr = 2 * k + (lane >> 5);  // row of this pass that the lane stores
-                const int r = WROWS * w + 32 * j + 16 * pass + rr;
-                // lane 16 pass + rr (g = 0) holds the output row of query row r
-                const int64_t row_out = __shfl(out_row, 16 * pass + rr, 64);
-                const float4 v = *reinterpret_cast<const float4*>(ob + rr * OROW + col);
-                if ((r >> g_shift) < n_grp) *reinterpret_cast<float4*>(out + row_out * D + col) = v;
-            }
-            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-            __builtin_amdgcn_wave_barrier();
+        for (int k = 0; k < 16; ++k) {
+            const int rr = 2 * k + (lane >> 5);  // row of the block that the lane stores
+            const int r = WROWS * w + 32 * j + rr;
+            int64_t row_out = (q_row0 + (r >> g_shift)) * n_q_heads + h * G + (r & (G - 1));
+            if constexpr (DECODE) row_out = __shfl(out_row, rr, 64);  // lane rr (g = 0) holds it
+            const float4 v = *reinterpret_cast<const float4*>(ob + rr * OROW + col);
+            if ((r >> g_shift) < n_grp) *reinterpret_cast<float4*>(out + row_out * D + col) = v;
         }
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
     }
 }
 
