@@ -113,16 +113,6 @@ __device__ __forceinline__ void mfma_result_wait(f32x16_t& s) {
     asm volatile("s_nop 15\n\ts_nop 15" : "+v"(s));
 }
 
-// Code `at` (0..3, a constant) of a dword of E4M3 codes as a float (exact).
-__device__ __forceinline__ float e4m3_at(uint32_t dw, int at) {
-    switch (at) {
-        case 0: return __builtin_amdgcn_cvt_f32_fp8((int)dw, 0);
-        case 1: return __builtin_amdgcn_cvt_f32_fp8((int)dw, 1);
-        case 2: return __builtin_amdgcn_cvt_f32_fp8((int)dw, 2);
-        default: return __builtin_amdgcn_cvt_f32_fp8((int)dw, 3);
-    }
-}
-
 // Masks the run rows the lane's query does not see (lim = rows of the run it sees, may
 // be <= 0).  Score i stands for run row 8 (i / 4) + 4 g + i % 4.
 __device__ __forceinline__ void prefill_mask(f32x16_t& s, int g, int lim) {
@@ -504,19 +494,31 @@ __device__ __forceinline__ void prefill_item(
     auto stage_k = [&](char* dst, const RawTile& raw, int i) {  // i = 0..3
         *reinterpret_cast<u32x4_t*>(dst + 4 * i * KROW_B) = widen_raw(raw.k[i]);
     };
-    auto stage_v = [&](char* dst, const RawTile& raw, int x) {  // element x = 0..7 of the piece
-        float f[4];  // the element of the four rows
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            if constexpr (FP8)
-                f[i] = e4m3_at(raw.v[i][x >> 2], x & 3);
-            else
-                f[i] = (x & 1) ? bf16_hi(raw.v[i][x >> 1]) : bf16_lo(raw.v[i][x >> 1]);
+    u32x2_t v_even = {0u, 0u}, v_odd = {0u, 0u};  // E4M3: two elements, of rows 0 and 1 so far
+    auto stage_v = [&](char* dst, const RawTile& raw, int x) {  // element x = 0..7 of the piece, in order
+        auto halves = [](float lo, float hi) {
+            return __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_pkrtz(lo, hi));
+        };
+        if constexpr (FP8) {
+            // one conversion yields two elements of a row: two rows of elements x and x + 1, then the
+            // other two and both stores
+            const int r = 2 * (x & 1);
+            const bool high = x & 2;
+            const auto lo = high ? __builtin_amdgcn_cvt_pk_f32_fp8((int)raw.v[r][x >> 2], true)
+                                 : __builtin_amdgcn_cvt_pk_f32_fp8((int)raw.v[r][x >> 2], false);
+            const auto hi = high ? __builtin_amdgcn_cvt_pk_f32_fp8((int)raw.v[r + 1][x >> 2], true)
+                                 : __builtin_amdgcn_cvt_pk_f32_fp8((int)raw.v[r + 1][x >> 2], false);
+            v_even[x & 1] = halves(lo[0], hi[0]);
+            v_odd[x & 1] = halves(lo[1], hi[1]);
+            if (x & 1) {
+                *reinterpret_cast<u32x2_t*>(dst + (x - 1) * kVFragX) = v_even;
+                *reinterpret_cast<u32x2_t*>(dst + x * kVFragX) = v_odd;
+            }
+        } else {
+            auto at = [&](int i) { return (x & 1) ? bf16_hi(raw.v[i][x >> 1]) : bf16_lo(raw.v[i][x >> 1]); };
+            *reinterpret_cast<u32x2_t*>(dst + x * kVFragX) =
+                u32x2_t{halves(at(0), at(1)), halves(at(2), at(3))};
         }
-        u32x2_t t;
-        t[0] = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_pkrtz(f[0], f[1]));
-        t[1] = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_pkrtz(f[2], f[3]));
-        *reinterpret_cast<u32x2_t*>(dst + x * kVFragX) = t;
     };
     // descriptor of run idx from the ring (same address in every lane); runs past the end of the
     // list are empty there
