@@ -397,7 +397,8 @@ typedef struct {
     int64_t n_q_rows;          /* query rows = sum of the leaf queries' node lengths      */
     int64_t n_items;           /* work items: blocks of rows_per_item / G query tokens    */
     int64_t n_runs;            /* entries of the run lists on the device                  */
-    int64_t rows_per_item;     /* query rows (tokens x heads of a kv head) per work item  */
+    int64_t rows_per_item;     /* query rows (tokens x heads of a kv head) of a full work
+                                * item: 256, or 128 where that takes less time            */
     int64_t unique_tokens;     /* rows of the nodes on some leaf query's chain, once      */
     int64_t unique_kv_bytes;   /* K plus V of those rows over all kv heads, one layer     */
     int64_t streamed_tokens;   /* rows walked, summed over the work items                 */

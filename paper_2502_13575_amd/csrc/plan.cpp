@@ -299,10 +299,12 @@ ets_status build(const ets_shape& shape, const PlanOptions& opt, const ets_tree&
     // attention launch of the configurations within 5 %.
     const int64_t t_tile = 2500, t_mem = t_tile, t_item = 7000, kTile = 64, kResident = 768;
     auto tile_cost = [&](int64_t) { return t_tile; };
-    // wide kernel: one workgroup per compute unit, about t_wide per 64-token tile of 256 rows.
-    // Off unless asked for: with the launch order merged, items of 64 rows measure 5-6 %
-    // faster on every shape, also with 8 query heads per kv head.  It does not merge, so
-    // a plan that uses it keeps the merge launch.
+    // wide kernel: one workgroup per compute unit, about t_wide per 64-token tile (1.8 us for items
+    // of more than 128 query rows, 1.2 for others).  Off unless asked for: without it a call takes
+    // 131 us on 256 leaves with 8 query heads per kv head against 142 to 159 for 512 to 16 rows,
+    // 368 on 512 leaves against 425 to 458, 2 056 on 16 searches against 2 129 to 2 213; over E4M3
+    // pools 290 on 512 leaves against 291 to 332.  It does not merge, so a plan that uses it keeps
+    // the merge launch.
     const int64_t wide_rows = opt.wide_rows >= 0 && shape.head_dim == 128 ? opt.wide_rows : 0;
     const int64_t ent_per_wide = std::max<int64_t>(1, kWideRowsPerItem / G);
     const int64_t t_wide = 1500;

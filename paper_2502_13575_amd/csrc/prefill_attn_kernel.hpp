@@ -45,14 +45,14 @@
 // use (two register sets alternate; one tile ahead left the waves waiting for memory).
 // Each wave fetches and stages half a run (16 rows, 16 bytes per lane and load) of K and of V.
 // The run list can be long (a path of thousands of rows), so its descriptors travel through
-// a ring of 256 entries in LDS that is refilled 128 at a time, 64 tiles ahead of their use.
+// a ring of 256 entries in LDS that is refilled 128 at a time: tile t reads descriptors up to
+// 2 t + 9, and a refill at tile t writes those from 2 t + 128 on, 60 tiles ahead of their use.
 //
-// Measured per run (256 query rows) on 38 k query tokens of 8 heads each over 5.4 k rows:
-// 2 000 cycles at 2.2 GHz, 1 024 of them matrix instructions (eight waves of 32 rows: 2 130);
-// 7.8 ms per launch against 8.4 on the same card, 930 TFLOP/s at best.  Without the weights
-// the same loop takes 1 390 cycles, without staging and loads too 1 190; 1 350 cycles are
-// instruction issue.  512 steps of up to 512 tokens over 13 k rows: 32.5 ms = 978 TFLOP/s
-// (36.5 before).  128 rows per workgroup: 1 350 cycles per run.
+// Measured against eight waves of 32 rows: 256 workgroups of 256 rows over one path of 16.8 k rows,
+// 526 runs: 529 us = 1.0 us per run (585), of 128 rows: 331 us = 0.63 us per run (355).  38 k query
+// tokens of 8 heads each over 5.4 k rows: 7.7 ms (8.5); 512 steps of up to 512 tokens over 13 k rows:
+// 32.6 ms = 976 TFLOP/s (36.0).  In that launch the matrix pipes are busy 55 % of the cycles; a
+// wave issues for 66 % of its time, waits to issue for 12 % and for data or at barriers for 22 %.
 //
 // The same kernel serves decode attention for tree segments that MANY leaf queries share
 // (template parameter DECODE): there the 256 query rows of a work item are up to 256 / G
@@ -73,7 +73,7 @@ typedef float f32x16_t __attribute__((ext_vector_type(16)));
 
 #define ETS_INLINE __attribute__((always_inline))  // a lambda the wave's registers pass through
 
-constexpr int kPrefillThreads = 256;  // four waves of 64 query rows
+constexpr int kPrefillThreads = 256;  // four waves of up to 64 query rows
 
 // The matrix instructions of the inner loop, with the register file of every operand named: a
 // wave holds 128 registers of O, 64 of Q, 32 of scores, 32 of weights, 64 of rows in flight and

@@ -31,9 +31,9 @@ ets_status check(const ets_tree& t) {
 
 // Query rows per work item.  One workgroup is resident per compute unit, so a launch takes as many
 // rounds as its workgroups fill the compute units, and a round costs the cycles that an item of
-// that size spends on a run of 32 rows.  (A block of at most 128 rows costs the same under
-// either size; among items of 256 rows it shortens no round that also holds a full one.)
-// Calls of steps below a path of 960 rows, 8 kv heads x 4 query heads, us with 128 / 256 rows per
+// that size spends on a run of 32 rows (526 runs in one round: 331 and 529 us).  (A block of at
+// most 128 rows costs the same under either size; among items of 256 rows it shortens no round
+// that also holds a full one.)  Calls of steps below a path of 960 rows, 8 kv heads x 4 query heads, us with 128 / 256 rows per
 // item: 16 steps of 64 tokens 28.4 / 37.2 (one round either way); 16 steps of 65, 96, 128 tokens
 // 48.5 / 37.1, 50.3 / 37.8, 53.8 / 43.3 (two rounds against one); 24 steps of 30 to 100 tokens
 // 49.6 / 66.9 (two each); 256 steps of 48 tokens 390 / 305 (16 against 8).
