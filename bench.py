@@ -22,8 +22,8 @@ MFMA_PEAK_TFLOPS = 2500.0       # MI355X dense bf16 / fp16 matrix-core peak, pub
 
 
 # sources whose change invalidates a stored counter reading, per kernel
-TRAFFIC_SOURCES = {"tree_attn": ("tree_attn_kernel.hpp", "plan.cpp"),
-                   "tree_attn_e4m3": ("tree_attn_kernel.hpp", "plan.cpp"),
+TRAFFIC_SOURCES = {"tree_attn": ("group_attn_kernel.hpp", "tree_attn_kernel.hpp", "plan.cpp"),
+                   "tree_attn_e4m3": ("group_attn_kernel.hpp", "tree_attn_kernel.hpp", "plan.cpp"),
                    "prefill_attn": ("prefill_attn_kernel.hpp", "prefill_plan.cpp")}
 
 

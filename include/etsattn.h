@@ -235,9 +235,10 @@ ets_status ets_plan_append_rows(const ets_ctx* ctx, int64_t* rows);
  *                    read once for all of them; below it every leaf reads the
  *                    segment itself (default 2; 0 = never share)
  *   "cascade_rows"   query rows (leaf queries x query heads per kv head) that one
- *                    work item of a shared segment serves: 16, 32 or 64
- *                    (default 64); a segment with more rows is read by several
- *                    items
+ *                    work item of a shared segment serves: 16, 32 or 64; a
+ *                    segment with more rows is read by several items (unset: 64, or
+ *                    128 where the planner gives the call to the kernel for that, which
+ *                    also reads a group's segments as one list)
  *   "wide_rows"      a shared segment with more query rows than this is read by the
  *                    wide kernel (256 query rows per work item, bound by the matrix
  *                    cores; head_dim 128) instead of by several items of "cascade_rows" rows each

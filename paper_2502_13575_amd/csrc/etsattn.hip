@@ -11,6 +11,7 @@
 #include "advance_kernel.hpp"
 #include "bench_kernels.hpp"
 #include "etsattn.h"
+#include "group_attn_kernel.hpp"
 #include "merge_kernel.hpp"
 #include "plan.h"
 #include "prefill_attn_kernel.hpp"
@@ -287,6 +288,15 @@ void launch_tree_attn(const ets_ctx* c, const LaunchArgs& a) {
     for (int64_t y0 = 0; y0 < n_wgs; y0 += 65535) {
         const unsigned ny = (unsigned)std::min<int64_t>(65535, n_wgs - y0);
         const bool fp8 = c->kv_format == ETS_KV_FP8_E4M3;
+        if (c->plan.groups) {
+            auto kernel = c->shape.head_dim == 64 ? (fp8 ? group_attn_kernel<true, 64> : group_attn_kernel<false, 64>)
+                                                  : (fp8 ? group_attn_kernel<true> : group_attn_kernel<false>);
+            hipLaunchKernelGGL(kernel, dim3((unsigned)c->shape.n_kv_heads, ny), dim3(256), 0, a.stream,
+                               a.k, a.v, a.pool_tokens, static_cast<const bf16_t*>(a.q), c->d_runs,
+                               c->d_units, (int)y0, c->d_ent_order, c->d_ent_base, g_shift,
+                               c->scale * 1.4426950408889634f, c->k_scales, a.ws_o, a.ws_ml);
+            continue;
+        }
         auto kernel =
             c->shape.head_dim == 64
                 ? (c->plan.fused ? (fp8 ? tree_attn_kernel<true, true, 64> : tree_attn_kernel<false, true, 64>)

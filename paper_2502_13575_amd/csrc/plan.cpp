@@ -25,10 +25,20 @@ struct Seg {
     int32_t ent_begin = 0;       // range in Plan::ent_order
     int32_t own_filled = 0;
     int32_t child_cursor = 0;
-    int32_t prefix = 0;          // partial slots used by the segments above
-    int32_t n_chunks = 0;
     bool cascade = false;
     bool wide = false;           // read by the wide kernel (many query rows)
+};
+
+// A list of nodes that the consecutive leaf queries ent_order[ent_begin .. + n_ent) read together:
+// one or more segments.  Its chunks take n_chunks partial slots of each of them, from `prefix` on.
+struct Shared {
+    int32_t ent_begin = 0, n_ent = 0;
+    std::vector<int32_t> nodes;
+    int64_t tokens = 0;
+    int32_t prefix = 0, n_chunks = 0;
+    int32_t above = -1;          // the shared list before it on the way from the root
+    bool wide = false;
+    bool sole = true;            // nobody else reads these nodes
 };
 
 struct Chunk {
@@ -141,7 +151,11 @@ bool fill_unit_steps(const Plan& p, UnitSlot& u, int wave, const std::vector<cha
 
 // The table the matrix-core kernel starts from (see UnitSlot), and the slots whose copies
 // of steps an advance has to refresh.
-void build_units(Plan& p) {
+int32_t unit_kind(const Plan& p, int32_t code, const CascadeItem& it, int64_t G) {
+    return code < 0 ? 1 : p.groups && it.n_ent * G <= 16 ? 2 : 0;
+}
+
+void build_units(Plan& p, int64_t G) {
     const size_t n_units = p.wg_map.size();
     p.units.assign(4 * n_units, UnitSlot{});  // zero: n_ent = 0, nothing to do
     p.adv_slots.clear();
@@ -155,7 +169,7 @@ void build_units(Plan& p) {
             if (idx >= n_items) continue;
             UnitSlot& u = p.units[4 * y + (size_t)w];
             u.item = p.cascade_items[(size_t)idx];
-            u.item.wave_item = code < 0 ? 1 : 0;
+            u.item.wave_item = unit_kind(p, code, u.item, G);
             if (fill_unit_steps(p, u, w, &grows)) p.adv_slots.push_back((int32_t)(4 * y + (size_t)w));
         }
     }
@@ -164,6 +178,33 @@ void build_units(Plan& p) {
 // After an advance: the unit table's copies follow the step lists.
 void refresh_units(Plan& p) {
     for (int32_t slot : p.adv_slots) fill_unit_steps(p, p.units[(size_t)slot], slot & 3, nullptr);
+}
+
+// Cuts the leaf queries (in depth-first order) into groups of at most `room` consecutive ones, with
+// the fewest tokens for the groups to read: the sum over the groups of the shared rows above any of
+// their leaf queries.  What two neighbours have in common is read once if they share a group and
+// twice if a boundary stands between them, so a boundary costs the rows above both (`common[i]`:
+// above leaf queries i - 1 and i).  Returns the first leaf query of every group, and the end.
+std::vector<int32_t> group_leaves(const std::vector<int64_t>& common, int32_t room) {
+    constexpr int64_t kGroupTokens = 32;  // and a group of its own costs about the start of an item
+    const int32_t L = (int32_t)common.size();
+    std::vector<int64_t> cost((size_t)L + 1, 0);
+    std::vector<int32_t> from((size_t)L + 1, 0);
+    for (int32_t j = 1; j <= L; ++j) {
+        cost[j] = std::numeric_limits<int64_t>::max();
+        for (int32_t i = std::max(0, j - room); i < j; ++i) {
+            const int64_t c = cost[i] + common[i] + kGroupTokens;
+            if (c < cost[j]) {
+                cost[j] = c;
+                from[j] = i;
+            }
+        }
+    }
+    std::vector<int32_t> bounds;
+    for (int32_t j = L; j > 0; j = from[j]) bounds.push_back(j);
+    bounds.push_back(0);
+    std::reverse(bounds.begin(), bounds.end());
+    return bounds;
 }
 
 ets_status validate(const ets_tree& t) {
@@ -245,6 +286,7 @@ ets_status build(const ets_shape& shape, const PlanOptions& opt, const ets_tree&
     p.ent_order.assign(L, 0);
     p.part_base.assign((size_t)L + 1, 0);
     p.max_cascade_ent = 0;
+    p.groups = false;
     p.adv.clear();
     p.adv_in_place = true;
     p.advances = 0;
@@ -291,14 +333,7 @@ ets_status build(const ets_shape& shape, const PlanOptions& opt, const ets_tree&
     p.piece = (int32_t)piece;
     auto grow_end_of = [&](int32_t node) { return p.tok_offset[node] + p.n_tokens[node]; };
     const int64_t partial_bytes = 2 * (int64_t)shape.n_q_heads * (shape.head_dim + 2) * 4;
-    const int64_t ent_per_item = std::max<int64_t>(1, opt.cascade_rows / G);
-    // cost model in nanoseconds: a resident workgroup needs about t_tile per tile of 64
-    // tokens whether it waits on memory (few rows) or computes (many rows), and t_item to
-    // start and to store its partial results; 768 workgroups are resident (three per
-    // compute unit).  Measured: 2.1-2.7 us per tile, 6.5-8.5 us per item; the sum predicts the
-    // attention launch of the configurations within 5 %.
-    const int64_t t_tile = 2500, t_mem = t_tile, t_item = 7000, kTile = 64, kResident = 768;
-    auto tile_cost = [&](int64_t) { return t_tile; };
+    constexpr int64_t kTile = 64;
     // wide kernel: one workgroup per compute unit, about t_wide per 64-token tile (1.8 us for items
     // of more than 128 query rows, 1.2 for others).  Off unless asked for: without it a call takes
     // 131 us on 256 leaves with 8 query heads per kv head against 142 to 159 for 512 to 16 rows,
@@ -308,8 +343,7 @@ ets_status build(const ets_shape& shape, const PlanOptions& opt, const ets_tree&
     const int64_t wide_rows = opt.wide_rows >= 0 && shape.head_dim == 128 ? opt.wide_rows : 0;
     const int64_t ent_per_wide = std::max<int64_t>(1, kWideRowsPerItem / G);
     const int64_t t_wide = 1500;
-    int64_t own_total = 0, work_ns = 0, wide_work_ns = 0;
-    int64_t items_est = L;  // one item per leaf query for what it reads itself, plus:
+    bool any_wide = false;
     for (Seg& sg : segs) {
         sg.cascade = cascade_ok && sg.cnt >= 2 && sg.cnt >= opt.cascade_min_leaves &&
                      sg.tokens > 0 &&
@@ -318,24 +352,168 @@ ets_status build(const ets_shape& shape, const PlanOptions& opt, const ets_tree&
         // system: items of 64 rows would stream it rows / 64 times through the compute
         // units.  The wide kernel takes 256 rows per item.
         sg.wide = sg.cascade && wide_rows > 0 && sg.cnt * G > wide_rows;
-        if (sg.wide) {
-            st.cascade_tokens += sg.tokens;
-            st.wide_tokens += sg.tokens;
-            wide_work_ns += ceil_div(sg.tokens, kTile) * ceil_div(sg.cnt, ent_per_wide) * t_wide *
-                            shape.n_kv_heads;
-        } else if (sg.cascade) {
-            st.cascade_tokens += sg.tokens;
-            for (int64_t e0 = 0; e0 < sg.cnt; e0 += ent_per_item) {
-                work_ns += ceil_div(sg.tokens, kTile) *
-                           tile_cost(std::min(ent_per_item, sg.cnt - e0) * G) * shape.n_kv_heads;
-                items_est += 1;
+        any_wide = any_wide || sg.wide;
+        if (sg.cascade) st.cascade_tokens += sg.tokens;
+        if (sg.wide) st.wide_tokens += sg.tokens;
+    }
+    // Which kernel.  The group kernel applies a tile to 128 query rows in about 1.0 us of a compute unit,
+    // where two items of 64 rows of the other one take 1.3 together, reads it half as often and joins
+    // segments into one item (see below); but only two of its workgroups are resident, so that calls of
+    // short items and calls that stream are slower with it.  It takes the plans whose row-parallel
+    // tiles (counted at 64 query rows; about 3.3 ns of the whole chip each) are at least eight for each of
+    // its resident workgroups and fill at least three tenths of the time the unique bytes take.  Calls
+    // of 60 drawn trees and the performance cases, the other kernel's time over this one's: beyond both
+    // lines 1.00 to 1.40, median 1.10 (16 searches of 256 leaves, 64 query heads, 2 002 -> 1 822 us; one,
+    // 137 -> 130; 475 leaves, head_dim 64, 116 -> 84); tiles enough but 0.09 to 0.26 of the bytes' time
+    // 0.92 to 0.99; fewer tiles 0.83 to 1.26, median 0.95.
+    const int64_t hbm_ns = st.unique_kv_bytes * (esz < 2 ? 2 : 1) / 5500;
+    int64_t tiles64 = 0;
+    for (const Seg& sg : segs)
+        if (sg.cascade && sg.cnt * G > 16)
+            tiles64 += ceil_div(sg.tokens, kTile) * ceil_div(sg.cnt * G, kTreeAttnRowsPerItem) * shape.n_kv_heads;
+    p.groups = cascade_ok && !any_wide && opt.cascade_rows == 0 && opt.fuse_merge != 1 &&
+               tiles64 > kGroupMinTiles && tiles64 * 11 > hbm_ns;
+    const int64_t ent_per_item =
+        std::max<int64_t>(1, (p.groups ? kGroupRowsPerItem : opt.cascade_rows > 0 ? opt.cascade_rows : kTreeAttnRowsPerItem) / G);
+    // cost model in nanoseconds: a resident workgroup needs about t_tile per tile of 64
+    // tokens whether it waits on memory (few rows) or computes (many rows), and t_item to
+    // start and to store its partial results; kResident workgroups are resident (three per
+    // compute unit, two of the group kernel with head_dim 128).  Measured: 2.1-2.7 us per tile, 6.5-8.5
+    // us per item; the sum predicts the attention launch of the configurations within 5 %.  Group
+    // kernel: 1.5 us per tile of up to 64 query rows, 2.0-2.7 of more, 5-8 us per item.
+    const int64_t t_tile = p.groups ? 2000 : 2500, t_mem = t_tile, t_item = 7000;
+    const int64_t kResident = p.groups && shape.head_dim == 128 ? 512 : 768;
+    auto tile_cost = [&](int64_t) { return t_tile; };
+    // The shared lists.  A segment by itself would cost every leaf query beneath it a partial result,
+    // and an item for every ent_per_item of them.  So the leaf queries are grouped, and within a
+    // group the segments that the same leaf queries of it read are walked as one list: the path down
+    // to a group's last common node is one item, and so is every stretch of a branch below it.
+    std::vector<Shared> shared;
+    std::vector<int32_t> last_shared(L, -1);  // by entry: the shared list nearest to its leaf
+    std::vector<std::pair<int32_t, int32_t>> group_of;  // by entry, if grouped: its group's entries
+    // It pays where partial results are a good part of the traffic, and costs L2 hits where they are not:
+    // groups walk the same rows at different times, the row groups of one segment at the same time.
+    // Joined against by segment, us: 16 searches of 256 leaves with 64 query heads (31 % of the KV bytes in
+    // partial results, 7.1 -> 3.9 of them for a leaf query) 1 850 against 1 970, 366 leaves of short
+    // steps 76 against 95, 414 leaves (18 %) 239 against 252; 512 leaves with 32 query heads (8 %) 376
+    // against 369, over E4M3 pools 291 against 283.
+    int64_t by_segment = L;
+    for (const Seg& sg : segs)
+        if (sg.cascade) by_segment += sg.cnt;
+    const bool grouped = p.groups && L >= 2 * ent_per_item &&
+                         by_segment * partial_bytes * 8 > st.unique_kv_bytes * (esz < 2 ? 2 : 1);
+    if (!grouped) {
+        std::vector<int32_t> of_seg(segs.size(), -1);  // the nearest shared list at or above
+        for (size_t i = 0; i < segs.size(); ++i) {
+            const Seg& sg = segs[i];
+            const int32_t above = sg.parent_seg >= 0 ? of_seg[sg.parent_seg] : -1;
+            of_seg[i] = above;
+            if (!sg.cascade) continue;
+            of_seg[i] = (int32_t)shared.size();
+            Shared sh;
+            sh.ent_begin = sg.ent_begin;
+            sh.n_ent = (int32_t)sg.cnt;
+            sh.nodes.swap(segs[i].nodes);  // (nobody reads a shared segment by himself)
+            sh.tokens = sg.tokens;
+            sh.above = above;
+            sh.wide = sg.wide;
+            shared.push_back(std::move(sh));
+        }
+        for (int32_t e = 0; e < L; ++e) last_shared[e] = of_seg[seg_of[p.leaf_node[p.ent_order[e]]]];
+    } else {
+        // rows of shared segments above neighbouring entries
+        std::vector<int64_t> above_rows(segs.size(), 0), common(L, 0);
+        std::vector<int32_t> level(segs.size(), 0);
+        for (size_t i = 0; i < segs.size(); ++i) {
+            const Seg& sg = segs[i];
+            if (sg.parent_seg >= 0) {
+                above_rows[i] = above_rows[sg.parent_seg];
+                level[i] = level[sg.parent_seg] + 1;
             }
-        } else {
-            st.stream_tokens += sg.tokens * sg.cnt;
-            own_total += sg.tokens * sg.cnt;
-            work_ns += ceil_div(sg.tokens, kTile) * t_mem * sg.cnt * shape.n_kv_heads;
+            if (sg.cascade) above_rows[i] += sg.tokens;
+        }
+        group_of.resize((size_t)L);
+        std::vector<int32_t> leaf_seg(L);
+        for (int32_t e = 0; e < L; ++e) leaf_seg[e] = seg_of[p.leaf_node[p.ent_order[e]]];
+        for (int32_t e = 1; e < L; ++e) {
+            int32_t x = leaf_seg[e - 1], y = leaf_seg[e];
+            while (x != y && x >= 0 && y >= 0) {
+                if (level[x] >= level[y]) x = segs[x].parent_seg;
+                else y = segs[y].parent_seg;
+            }
+            if (x == y && x >= 0) common[e] = above_rows[x];
+        }
+        const std::vector<int32_t> bounds = group_leaves(common, (int32_t)ent_per_item);
+        std::vector<int32_t> in_group(segs.size(), -1), list_of(segs.size(), -1), members;
+        for (size_t g = 0; g + 1 < bounds.size(); ++g) {
+            const int32_t first = bounds[g], end = bounds[g + 1];
+            members.clear();
+            for (int32_t e = first; e < end; ++e)
+                for (int32_t s = leaf_seg[e]; s >= 0 && in_group[s] != (int32_t)g; s = segs[s].parent_seg) {
+                    in_group[s] = (int32_t)g;
+                    members.push_back(s);
+                }
+            std::sort(members.begin(), members.end());  // parents before children
+            for (int32_t s : members) {
+                const Seg& sg = segs[s];
+                const int32_t above = sg.parent_seg >= 0 ? list_of[sg.parent_seg] : -1;
+                list_of[s] = above;
+                const int32_t lo = std::max(first, sg.ent_begin);
+                const int32_t n = std::min(end, sg.ent_begin + (int32_t)sg.cnt) - lo;
+                if (!sg.cascade || n < 2) continue;
+                if (above < 0 || shared[above].n_ent != n) {  // (a subset of the list above it)
+                    list_of[s] = (int32_t)shared.size();
+                    Shared sh;
+                    sh.ent_begin = lo;
+                    sh.n_ent = n;
+                    sh.above = above;
+                    shared.push_back(std::move(sh));
+                }
+                Shared& sh = shared[list_of[s]];
+                sh.nodes.insert(sh.nodes.end(), sg.nodes.begin(), sg.nodes.end());
+                sh.tokens += sg.tokens;
+                sh.sole = sh.sole && sg.cnt == n;
+            }
+            for (int32_t e = first; e < end; ++e) {
+                last_shared[e] = list_of[leaf_seg[e]];
+                group_of[e] = {first, end};
+            }
         }
     }
+    // segments that the leaf query of entry e reads by itself, leaf first
+    auto own_segs = [&](int32_t e, std::vector<int32_t>& out) {
+        out.clear();
+        for (int32_t s = seg_of[p.leaf_node[p.ent_order[e]]]; s >= 0; s = segs[s].parent_seg) {
+            bool own = !segs[s].cascade;
+            if (!own && grouped)
+                own = std::min(group_of[e].second, segs[s].ent_begin + (int32_t)segs[s].cnt) -
+                          std::max(group_of[e].first, segs[s].ent_begin) < 2;
+            if (own) out.push_back(s);
+        }
+    };
+    int64_t own_total = 0, work_ns = 0, wide_work_ns = 0;
+    int64_t items_est = L;  // one item per leaf query for what it reads itself, plus:
+    for (const Shared& sh : shared) {
+        if (sh.wide) {
+            wide_work_ns += ceil_div(sh.tokens, kTile) * ceil_div(sh.n_ent, ent_per_wide) * t_wide *
+                            shape.n_kv_heads;
+            continue;
+        }
+        for (int64_t e0 = 0; e0 < sh.n_ent; e0 += ent_per_item) {
+            work_ns += ceil_div(sh.tokens, kTile) *
+                       tile_cost(std::min(ent_per_item, sh.n_ent - e0) * G) * shape.n_kv_heads;
+            items_est += 1;
+        }
+    }
+    std::vector<int32_t> reads;
+    for (int32_t e = 0; e < L; ++e) {
+        own_segs(e, reads);
+        for (int32_t s : reads) {
+            own_total += segs[s].tokens;
+            work_ns += ceil_div(segs[s].tokens, kTile) * t_mem * shape.n_kv_heads;
+        }
+    }
+    st.stream_tokens = own_total;
     // time the whole call is expected to take: the larger of the HBM time of the
     // unique bytes (at ~5.5 TB/s) and the modelled work spread over the resident
     // workgroups; no single item should take more than half of it: finer items balance no
@@ -344,7 +522,6 @@ ets_status build(const ets_shape& shape, const PlanOptions& opt, const ets_tree&
     // (measured on the configurations: the optimum lies at 45-55 % of the call time)
     // (1-byte pools are budgeted like 2-byte ones: their launch is bound by the number
     // of loads, not by their bytes, and finer items would only add partial results)
-    const int64_t hbm_ns = st.unique_kv_bytes * (esz < 2 ? 2 : 1) / 5500;
     // (plus the start and the end of the items on the critical path, which is what a small
     // call mostly consists of)
     const int64_t call_ns =
@@ -366,24 +543,21 @@ ets_status build(const ets_shape& shape, const PlanOptions& opt, const ets_tree&
         }
     }
 
-    // shared segments: chunk counts first (they fix the slot numbering)
-    std::vector<std::vector<Chunk>> seg_chunks(segs.size());
-    for (size_t s = 0; s < segs.size(); ++s) {
-        Seg& sg = segs[s];
-        sg.prefix =
-            sg.parent_seg < 0 ? 0 : segs[sg.parent_seg].prefix + segs[sg.parent_seg].n_chunks;
-        sg.n_chunks = 0;
-        if (!sg.cascade) continue;
+    // shared lists: chunk counts first (they fix the slot numbering)
+    std::vector<std::vector<Chunk>> shared_chunks(shared.size());
+    for (size_t i = 0; i < shared.size(); ++i) {
+        Shared& sh = shared[i];
+        sh.prefix = sh.above < 0 ? 0 : shared[sh.above].prefix + shared[sh.above].n_chunks;
         int64_t ccap = opt.cascade_chunk;
-        if (ccap <= 0 && sg.wide)
+        if (ccap <= 0 && sh.wide)
             ccap = wide_budget_ns / t_wide * kTile;
         else if (ccap <= 0)
-            ccap = item_budget_ns / tile_cost(std::min(ent_per_item, sg.cnt) * G) * kTile;
+            ccap = item_budget_ns / tile_cost(std::min<int64_t>(ent_per_item, sh.n_ent) * G) * kTile;
         tmp_runs.clear();
-        if (!collect_runs(p, sg.nodes, own, tmp_runs)) p.adv_in_place = false;
-        if (!cut_runs(p, tmp_runs, sg.tokens, ccap, piece, seg_chunks[s]))
+        if (!collect_runs(p, sh.nodes, own, tmp_runs)) p.adv_in_place = false;
+        if (!cut_runs(p, tmp_runs, sh.tokens, ccap, piece, shared_chunks[i]))
             p.adv_in_place = false;
-        sg.n_chunks = (int32_t)seg_chunks[s].size();
+        sh.n_chunks = (int32_t)shared_chunks[i].size();
     }
 
     // per leaf query: the segments of its chain that no shared item reads are read
@@ -391,20 +565,18 @@ ets_status build(const ets_shape& shape, const PlanOptions& opt, const ets_tree&
     std::vector<int32_t> ent_pos(L, 0);
     for (int32_t i = 0; i < L; ++i) ent_pos[p.ent_order[i]] = i;
     {
-        std::vector<int32_t> own_nodes, seg_chain;
+        std::vector<int32_t> own_nodes;
         int64_t slot = 0;
         for (int32_t l = 0; l < L; ++l) {
-            const int32_t s_leaf = seg_of[p.leaf_node[l]];
             p.part_base[l] = (int32_t)slot;
-            const int32_t shared_slots = segs[s_leaf].prefix + segs[s_leaf].n_chunks;
+            const int32_t e = ent_pos[l];
+            const int32_t shared_slots =
+                last_shared[e] < 0 ? 0 : shared[last_shared[e]].prefix + shared[last_shared[e]].n_chunks;
             slot += shared_slots;
-            seg_chain.clear();
-            for (int32_t s = s_leaf; s >= 0; s = segs[s].parent_seg)
-                if (!segs[s].cascade) seg_chain.push_back(s);
             own_nodes.clear();
-            for (size_t i = seg_chain.size(); i-- > 0;)
-                own_nodes.insert(own_nodes.end(), segs[seg_chain[i]].nodes.begin(),
-                                 segs[seg_chain[i]].nodes.end());
+            own_segs(e, reads);
+            for (size_t i = reads.size(); i-- > 0;)
+                own_nodes.insert(own_nodes.end(), segs[reads[i]].nodes.begin(), segs[reads[i]].nodes.end());
             tmp_runs.clear();
             if (!collect_runs(p, own_nodes, own, tmp_runs)) p.adv_in_place = false;
             int64_t tokens = 0;
@@ -432,28 +604,24 @@ ets_status build(const ets_shape& shape, const PlanOptions& opt, const ets_tree&
     }
 
     std::vector<int64_t> wide_cost;
-    for (size_t s = 0; s < segs.size(); ++s) {
-        const Seg& sg = segs[s];
-        for (int32_t c = 0; c < sg.n_chunks; ++c) {
-            const Chunk& ch = seg_chunks[s][c];
-            if (sg.wide) {
-                for (int64_t e0 = 0; e0 < sg.cnt; e0 += ent_per_wide) {
-                    const int32_t ne = (int32_t)std::min<int64_t>(ent_per_wide, sg.cnt - e0);
-                    p.wide_items.push_back(CascadeItem{ch.run_begin, ch.run_end,
-                                                       sg.ent_begin + (int32_t)e0, ne, sg.prefix + c,
-                                                       ch.tokens, sg.cnt <= ent_per_wide ? 1 : 0, 0});
+    for (size_t i = 0; i < shared.size(); ++i) {
+        const Shared& sh = shared[i];
+        for (int32_t c = 0; c < sh.n_chunks; ++c) {
+            const Chunk& ch = shared_chunks[i][c];
+            const int64_t per_item = sh.wide ? ent_per_wide : ent_per_item;
+            const int32_t sole = sh.sole && sh.n_ent <= per_item ? 1 : 0;
+            for (int64_t e0 = 0; e0 < sh.n_ent; e0 += per_item) {
+                const int32_t ne = (int32_t)std::min<int64_t>(per_item, sh.n_ent - e0);
+                const CascadeItem it{ch.run_begin, ch.run_end, sh.ent_begin + (int32_t)e0, ne,
+                                     sh.prefix + c, ch.tokens, sole, 0};
+                if (sh.wide) {
+                    p.wide_items.push_back(it);
                     wide_cost.push_back(ceil_div(ch.tokens, kTile) * ceil_div((int64_t)ne * G, 32));
+                } else {
+                    p.cascade_items.push_back(it);
+                    cascade_cost.push_back(ceil_div(ch.tokens, kTile) * tile_cost((int64_t)ne * G));
+                    p.max_cascade_ent = std::max(p.max_cascade_ent, ne);
                 }
-                continue;
-            }
-            for (int64_t e0 = 0; e0 < sg.cnt; e0 += ent_per_item) {
-                const int32_t ne = (int32_t)std::min<int64_t>(ent_per_item, sg.cnt - e0);
-                p.cascade_items.push_back(CascadeItem{ch.run_begin, ch.run_end,
-                                                      sg.ent_begin + (int32_t)e0, ne,
-                                                      sg.prefix + c, ch.tokens,
-                                                      sg.cnt <= ent_per_item ? 1 : 0, 0});
-                cascade_cost.push_back(ceil_div(ch.tokens, kTile) * tile_cost((int64_t)ne * G));
-                p.max_cascade_ent = std::max(p.max_cascade_ent, ne);
             }
         }
     }
@@ -491,7 +659,8 @@ ets_status build(const ets_shape& shape, const PlanOptions& opt, const ets_tree&
         sorted.reserve(idx.size());
         // A lone wave needs about 2.5 us per 16-token unit; such an item should not
         // last longer than a quarter of the time the whole call is expected to take.
-        const int64_t wave_cap = std::min<int64_t>(opt.wave_items, hbm_ns / 4 / 2500 * 16);
+        const int64_t wave_cap = std::min<int64_t>(
+            opt.wave_items, p.groups ? call_ns * 6 / 10 / 1500 * 16 : hbm_ns / 4 / 2500 * 16);
         auto small = [&](const CascadeItem& it) {
             return (int64_t)it.n_ent * G <= 16 && it.n_tokens <= wave_cap;
         };
@@ -522,13 +691,46 @@ ets_status build(const ets_shape& shape, const PlanOptions& opt, const ets_tree&
         }
         p.wg_map.clear();
         p.wg_map.reserve(heavy.size() + light.size());
-        if (!opt.interleave) {
+        // Units of few rounds (group kernel): longest first, whatever the kind.  With 300 to 1 600
+        // units per kv head's share of the chip the merged sequence is 3 to 15 % slower up to three rounds
+        // over the resident workgroups, and as much faster from there on.
+        const int64_t n_units = ((int64_t)heavy.size() + (int64_t)light.size()) * shape.n_kv_heads;
+        if (opt.interleave && p.groups && n_units < 3 * kResident) {
+            auto duration = [&](const std::pair<int64_t, int32_t>& u) {  // in units of half a tile
+                if (u.second >= 0) {
+                    const CascadeItem& it = p.cascade_items[(size_t)u.second];
+                    const int64_t rows = (int64_t)it.n_ent * G;
+                    return rows > 64 ? ceil_div(u.first, kTile) * 21 : rows > 32 ? ceil_div(u.first, kTile) * 16
+                           : rows > 16 ? ceil_div(u.first, kTile) * 14 : ceil_div(u.first, 2 * kTile) * 16;
+                }
+                // four small items, the longest first
+                return ceil_div(p.cascade_items[(size_t)(p.n_single + 4 * (-(int64_t)u.second - 1))].n_tokens, 32) * 16;
+            };
+            std::vector<std::pair<int64_t, int32_t>> all;
+            for (const auto* kind : {&heavy, &light})
+                for (const auto& u : *kind) all.push_back({duration(u), u.second});
+            std::stable_sort(all.begin(), all.end(), [](const std::pair<int64_t, int32_t>& a, const std::pair<int64_t, int32_t>& b) {
+                return a.first > b.first;
+            });
+            for (const auto& u : all) p.wg_map.push_back(u.second);
+        } else if (!opt.interleave) {
             for (int32_t i = 0; i < p.n_single; ++i) p.wg_map.push_back(i);
             for (int64_t g = 0; g < n_w; ++g) p.wg_map.push_back((int32_t)(-g - 1));
         } else {
             auto by_tokens = [](const std::pair<int64_t, int32_t>& a,
                                 const std::pair<int64_t, int32_t>& b) { return a.first > b.first; };
-            std::stable_sort(heavy.begin(), heavy.end(), by_tokens);
+            // Where there are many of them (group kernel), items of more than 256 tokens come in the order of
+            // their leaf queries, not of their lengths: neighbours walk the same rows from the root, and
+            // what runs at the same time finds them in L2 (16 searches of 256 leaves: 10.8 GB read past L2
+            // and 2 058 us in order of length, 8.9 GB and 1 893 us so).
+            const bool by_place = p.groups && (int64_t)heavy.size() * shape.n_kv_heads > 8 * kResident;
+            auto before = [&](const std::pair<int64_t, int32_t>& a, const std::pair<int64_t, int32_t>& b) {
+                if (!by_place) return a.first > b.first;
+                const bool la = a.first > 256, lb = b.first > 256;
+                if (la != lb) return la;
+                return p.cascade_items[(size_t)a.second].ent_begin < p.cascade_items[(size_t)b.second].ent_begin;
+            };
+            std::stable_sort(heavy.begin(), heavy.end(), before);
             std::stable_sort(light.begin(), light.end(), by_tokens);
             int64_t tot_h = 0, tot_l = 0, done_h = 0, done_l = 0;
             for (const auto& x : heavy) tot_h += std::max<int64_t>(x.first, 1);
@@ -554,7 +756,7 @@ ets_status build(const ets_shape& shape, const PlanOptions& opt, const ets_tree&
     if (p.runs.size() >= (size_t)std::numeric_limits<int32_t>::max() ||
         p.wg_map.size() >= (size_t)std::numeric_limits<int32_t>::max() / 16)
         return ETS_ERR_UNSUPPORTED;
-    build_units(p);
+    build_units(p, G);
     {
         std::vector<int32_t> first(N, -1);
         p.adv_node.clear();
@@ -689,13 +891,12 @@ bool check_plan(const Plan& p, const ets_shape& shape, PlanCheck& out) {
         }
         // the entries: every wave loads 16 consecutive entries from its block's first one
         const int64_t R = (int64_t)it.n_ent * G;
-        bad(it.n_ent < 1 || R > kTreeAttnRowsPerItem || it.ent_begin < 0 ||
+        bad(it.n_ent < 1 || R > (p.groups ? kGroupRowsPerItem : kTreeAttnRowsPerItem) || it.ent_begin < 0 ||
             (int64_t)it.ent_begin + it.n_ent > L);
         if (wave_item) bad(R > 16);
         const bool rowpar = R > 16;
         const int n_blocks = (int)((R + 15) / 16);
-        for (int w = 0; w < 4; ++w) {
-            const int blk = rowpar && w < n_blocks ? w : 0;
+        for (int blk = 0; blk < (rowpar ? n_blocks : 1); ++blk) {
             const int64_t first = (int64_t)it.ent_begin + (16 * blk) / G;
             const int64_t last_loaded = first + 15;
             out.max_entry_index = std::max(out.max_entry_index, last_loaded);
@@ -707,7 +908,6 @@ bool check_plan(const Plan& p, const ets_shape& shape, PlanCheck& out) {
                 const int64_t leaf = entry_leaf(first + k);
                 bad(leaf < 0 || leaf >= std::max<int64_t>(L, 1));
             }
-            if (wave_item) break;  // one wave walks the item
         }
         // the partial rows it writes
         for (int32_t e = 0; e < it.n_ent && (int64_t)it.ent_begin + e < L; ++e) {
@@ -776,7 +976,7 @@ bool check_plan(const Plan& p, const ets_shape& shape, PlanCheck& out) {
             bad(u.item.run_begin != it.run_begin || u.item.run_end != it.run_end ||
                 u.item.ent_begin != it.ent_begin || u.item.n_ent != it.n_ent ||
                 u.item.slot_off != it.slot_off || u.item.sole_reader != it.sole_reader ||
-                u.item.wave_item != (code < 0 ? 1 : 0));
+                u.item.wave_item != unit_kind(p, code, it, G));
             const Run* held[2] = {&u.first, &u.second};
             for (int j = 0; j < 2; ++j) {
                 const int k = unit_step_index(u.item, w, j);

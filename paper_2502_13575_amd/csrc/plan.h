@@ -40,15 +40,17 @@ struct CascadeItem {
     int32_t slot_off;
     int32_t n_tokens;
     int32_t sole_reader;  // 1: no other item reads these rows
-    int32_t wave_item;    // 1: a small item walked by one wavefront (set in the unit table)
+    int32_t wave_item;    // set in the unit table.  1: a small item walked by one wavefront; 2 (group kernel):
+                          // at most 16 query rows, steps dealt to the four wavefronts; 0: others
 };
 
 // What a wavefront of the matrix-core kernel starts from, in launch order: wave w of
 // workgroup y reads units[4 y + w]: its work item (n_ent = 0: nothing to do) and the step
 // it fetches first (n = 0: none), so that the first tile can be requested after a single
 // table read.  Item of a workgroup: four copies, `first` = step w / 2 of the item (the wave
-// fetches half w % 2 of it), `second` unused.  Small item of a wave: `first` = its step 0,
-// `second` = its step 1.  64 bytes.
+// fetches half w % 2 of it), `second` = step 2 + w / 2 (read by the group kernel only).  Small item
+// of a wave: `first` = its step 0, `second` = its step 1.  Group kernel, at most 16 query rows: steps w and
+// 4 + w.  64 bytes.
 struct UnitSlot {
     CascadeItem item;
     Run first;
@@ -61,7 +63,7 @@ struct UnitSlot {
 __host__ __device__
 #endif
 inline int unit_step_index(const CascadeItem& item, int wave, int j) {
-    return item.wave_item ? j : (j == 0 ? wave >> 1 : -1);
+    return item.wave_item == 1 ? j : item.wave_item == 2 ? 4 * j + wave : 2 * j + (wave >> 1);
 }
 
 // Where a growing node's next token goes (decode-step advance): one record per copy of
@@ -77,7 +79,9 @@ struct AdvEntry {
 };
 
 // Geometry of the matrix-core kernel that the planner and the launch code rely on.
-constexpr int kTreeAttnRowsPerItem = 64;  // query rows one work item serves at most
+constexpr int kTreeAttnRowsPerItem = 64;   // query rows one work item serves at most
+constexpr int kGroupRowsPerItem = 128;    // the same of the group kernel
+constexpr int64_t kGroupMinTiles = 4096;  // row-parallel tiles from which a plan is the group kernel's
 constexpr int kTreeAttnMaxSteps = 256;    // steps per work item that takes a workgroup
 constexpr int kWideRowsPerItem = 256;     // query rows per work item of the wide kernel (4 waves x 64)
 // Both per-entry tables (ent_order, ent_base) end in this many zero entries on the device:
@@ -92,7 +96,7 @@ struct PlanOptions {
     int64_t kv_elem_bytes = 0;       // bytes per pool element; 0 = by the shape's dtype
     int64_t stream_chunk = 0;        // 0 = auto
     int64_t cascade_chunk = 0;       // 0 = auto
-    int64_t cascade_rows = 64;       // query rows per shared work item (16, 32 or 64)
+    int64_t cascade_rows = 0;        // query rows per shared work item (16, 32 or 64); 0 = the planner decides
     int64_t wave_items = 512;        // an item of <= 16 rows and at most this many tokens is
                                      // walked by one wave, four such items to a workgroup (0 = off)
     int64_t mfma = 1;                // 0 = never use the matrix-core kernel
@@ -139,6 +143,7 @@ struct Plan {
     int32_t adv_room = 0;             // advances the spare runs still hold
     int32_t advances = 0;             // advances applied in place since the plan was built
     int32_t piece = 0;                // longest run the kernels accept (0 = any)
+    bool groups = false;              // the group kernel takes the items (up to kGroupRowsPerItem rows)
     bool fused = false;               // the matrix-core kernel merges (no merge launch): every
                                       // partial comes from it and every leaf query has one
     ets_stats stats{};

@@ -1,0 +1,86 @@
+"""Plans of the group kernel (many query rows per shared row) on the host: leaf queries cut into
+groups, segments of a group joined into one list.  Indexing against the oracle's walk, the replay of
+the kernel's table reads, and both after decode-step advances, over random forests whose 64 kv heads
+bring them over the planner's line."""
+import numpy as np
+import pytest
+
+import oracle
+import paper_2502_13575_amd as ets
+from workload import random_tree, with_growth_room
+
+SHAPES = [(64, 512, 128), (64, 256, 64), (64, 128, 128), (64, 64, 64)]
+
+
+def _plan(ctx, t):
+    return ctx.plan(t.parent, t.tok_offset, t.n_tokens, t.leaf_node)
+
+
+def _covers(ctx, t, n_tokens):
+    optr, onodes = oracle.paths(t.parent, t.leaf_node)
+    total = 0
+    for l in range(t.n_leaves):
+        rows, n = ctx.leaf_cover(l)
+        nodes = onodes[optr[l]:optr[l + 1]]
+        want = np.concatenate([np.zeros(0, np.int64)] +
+                              [np.arange(t.tok_offset[x], t.tok_offset[x] + n_tokens[x]) for x in nodes])
+        assert np.array_equal(np.sort(rows), np.sort(want)), l
+        total += n
+    assert total == ctx.stats().n_partials
+
+
+@pytest.mark.parametrize("block", range(8))
+def test_group_plans_of_random_forests(block):
+    joined = 0
+    for seed in range(31000 + 30 * block, 31030 + 30 * block):
+        r = np.random.default_rng(seed)
+        t = random_tree(seed, n_nodes=int(r.integers(20, 160)), n_leaves=int(r.integers(40, 300)),
+                        max_tokens=int(r.choice([200, 1000, 3000])), p_root=float(r.choice([0.01, 0.05])),
+                        p_empty=float(r.choice([0.0, 0.15, 0.4])))
+        t = with_growth_room(t, 40)
+        hk, hq, d = SHAPES[seed % len(SHAPES)]
+        with ets.Context(hk, hq, d, ets.ETS_BF16, -1) as ctx, ets.Context(hk, hq, d, ets.ETS_BF16, -1) as by64:
+            ctx.set_option("stream_chunk", int(r.choice([0, 0, 64])))
+            ctx.set_option("cascade_chunk", int(r.choice([0, 0, 96])))
+            ctx.set_option("wave_items", int(r.choice([512, 0, 100000])))
+            ctx.set_option("interleave", int(r.choice([1, 1, 0])))
+            st = _plan(ctx, t)
+            by64.set_option("cascade_rows", 64)
+            _plan(by64, t)
+            assert st.unique_tokens == by64.stats().unique_tokens
+            assert st.cascade_tokens == by64.stats().cascade_tokens
+            joined += st.n_cascade_items < by64.stats().n_cascade_items
+            rep = ctx.check()
+            assert rep.violations == 0 and rep.max_entry_overreach <= 15, (seed, rep.as_dict())
+            _covers(ctx, t, t.n_tokens)
+            n_tokens = t.n_tokens.copy()
+            for step in range(int(r.choice([1, 34]))):
+                ctx.plan_advance()
+                n_tokens[np.unique(t.leaf_node)] += 1
+            assert ctx.check().violations == 0, seed
+            _covers(ctx, t, n_tokens)
+    assert joined >= 6  # the sweep does reach the plans it is about
+
+
+def test_the_leaf_queries_of_one_search_share_one_list_down_to_their_last_common_node():
+    """A chain of 40 nodes of 100 rows with 64 leaf queries at its end: each group of 16 (8 query heads
+    per kv head) reads it as one list, so that a leaf query has as many partials as that list has
+    chunks; with one list per 64 query rows and segment it would be the same here, but not where a leaf
+    query branches off every node: there a group's common part is one list, too."""
+    n = 40
+    chain = np.arange(-1, n - 1, dtype=np.int32)
+    parent = np.concatenate([chain, np.repeat(np.arange(n, dtype=np.int32), 4)])
+    n_tok = np.full(parent.size, 100, np.int32)
+    off = np.arange(parent.size, dtype=np.int64) * 100
+    leaf = np.arange(n, parent.size, dtype=np.int32)
+    stats = []
+    for opts in ({}, {"cascade_rows": 64}):
+        with ets.Context(16, 128, 128, ets.ETS_BF16, -1) as ctx:
+            for k, v in opts.items():
+                ctx.set_option(k, v)
+            ctx.set_option("cascade_chunk", 100000)
+            stats.append(ctx.plan(parent, off, n_tok, leaf))
+    # by segment: a leaf query below node i has i + 1 shared parts and its own
+    assert stats[1].n_partials == 4 * sum(i + 2 for i in range(n))
+    # by group: the parts above the group's first branch are one, those below it stay apart
+    assert stats[0].n_partials == 4 * sum((i % 4) + 2 for i in range(n))
