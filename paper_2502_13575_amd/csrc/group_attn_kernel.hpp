@@ -517,34 +517,44 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(D == 128 ? 
     // (The statements that pin the pieces keep the conversion, and with it the wait for the loads, where it
     // is written; `place` tells the copies apart, which would otherwise be joined ahead of the branch
     // between them.)
-    auto stage_part = [&](u32x4_t* buf, const RawUnit& raw, int k, auto place) {
+    u32x2_t v_even = {0u, 0u}, v_odd = {0u, 0u};  // E4M3: two elements, of tokens 4 b and 4 b + 1 so far
+    auto stage_part = [&](u32x4_t* buf, const RawUnit& raw, int k, auto place) {  // (in order)
         if (k < NKL) {
             raw_t piece = raw.k[k];
             asm volatile("; %1" : "+v"(piece) : "n"(decltype(place)::value));
             buf[(32 * sw + 16 * hw + RPL * k + rb) * KROW + pa] = widen_raw(piece);
         } else {
             const int x = k - NKL;
-            float f[4];
+            u32x2_t* const vs2 = reinterpret_cast<u32x2_t*>(buf + KS_UNITS) + (sw * NX * 64 + lane) * 2 + hw;
+            if constexpr (FP8) {
+                // one conversion yields two elements of a row: two rows of elements x and x + 1, then the
+                // other two and both stores (head_dim 64: codes 4 (a & 1) .. + 3 of the piece)
+                const int r = 2 * (x & 1);
+                uint32_t two[2];
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                if constexpr (FP8) {
-                    // (head_dim 64: codes 4 (a & 1) .. + 3 of the piece)
-                    int dw = D == 128 ? (int)raw.v[i][x >> 2] : (int)((a & 1) ? raw.v[i][1] : raw.v[i][0]);
-                    asm volatile("; %1" : "+v"(dw) : "n"(decltype(place)::value));
-                    const auto two = (x & 2) ? __builtin_amdgcn_cvt_pk_f32_fp8(dw, true)
-                                             : __builtin_amdgcn_cvt_pk_f32_fp8(dw, false);
-                    f[i] = two[x & 1];
-                } else {
+                for (int i = 0; i < 2; ++i) {
+                    uint32_t codes = D == 128 ? raw.v[r + i][x >> 2] : (a & 1) ? raw.v[r + i][1] : raw.v[r + i][0];
+                    asm volatile("; %1" : "+v"(codes) : "n"(decltype(place)::value));
+                    two[i] = (x & 2) ? e4m3x2_to_f16x2<true>(codes) : e4m3x2_to_f16x2<false>(codes);
+                }
+                v_even[x & 1] = low_halves(two[0], two[1]);
+                v_odd[x & 1] = high_halves(two[0], two[1]);
+                if (x & 1) {
+                    vs2[(x - 1) * 128] = v_even;
+                    vs2[x * 128] = v_odd;
+                }
+            } else {
+                float f[4];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
                     uint32_t dw = D == 128 ? raw.v[i][(x >> 1) & 3]
                                            : (a & 1) ? raw.v[i][2 + ((x >> 1) & 1)] : raw.v[i][(x >> 1) & 1];
                     asm volatile("; %1" : "+v"(dw) : "n"(decltype(place)::value));
                     f[i] = (x & 1) ? bf16_hi(dw) : bf16_lo(dw);
                 }
+                vs2[x * 128] = u32x2_t{__builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_pkrtz(f[0], f[1])),
+                                       __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_pkrtz(f[2], f[3]))};
             }
-            u32x2_t* vs2 = reinterpret_cast<u32x2_t*>(buf + KS_UNITS);
-            vs2[((sw * NX + x) * 64 + lane) * 2 + hw] =
-                u32x2_t{__builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_pkrtz(f[0], f[1])),
-                        __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_pkrtz(f[2], f[3]))};
         }
     };
     auto stage = [&](u32x4_t* buf, const RawUnit& raw, auto place) {

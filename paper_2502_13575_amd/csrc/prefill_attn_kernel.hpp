@@ -496,25 +496,25 @@ __device__ __forceinline__ void prefill_item(
     };
     u32x2_t v_even = {0u, 0u}, v_odd = {0u, 0u};  // E4M3: two elements, of rows 0 and 1 so far
     auto stage_v = [&](char* dst, const RawTile& raw, int x) {  // element x = 0..7 of the piece, in order
-        auto halves = [](float lo, float hi) {
-            return __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_pkrtz(lo, hi));
-        };
         if constexpr (FP8) {
             // one conversion yields two elements of a row: two rows of elements x and x + 1, then the
             // other two and both stores
             const int r = 2 * (x & 1);
             const bool high = x & 2;
-            const auto lo = high ? __builtin_amdgcn_cvt_pk_f32_fp8((int)raw.v[r][x >> 2], true)
-                                 : __builtin_amdgcn_cvt_pk_f32_fp8((int)raw.v[r][x >> 2], false);
-            const auto hi = high ? __builtin_amdgcn_cvt_pk_f32_fp8((int)raw.v[r + 1][x >> 2], true)
-                                 : __builtin_amdgcn_cvt_pk_f32_fp8((int)raw.v[r + 1][x >> 2], false);
-            v_even[x & 1] = halves(lo[0], hi[0]);
-            v_odd[x & 1] = halves(lo[1], hi[1]);
+            const uint32_t lo = high ? e4m3x2_to_f16x2<true>(raw.v[r][x >> 2])
+                                     : e4m3x2_to_f16x2<false>(raw.v[r][x >> 2]);
+            const uint32_t hi = high ? e4m3x2_to_f16x2<true>(raw.v[r + 1][x >> 2])
+                                     : e4m3x2_to_f16x2<false>(raw.v[r + 1][x >> 2]);
+            v_even[x & 1] = low_halves(lo, hi);
+            v_odd[x & 1] = high_halves(lo, hi);
             if (x & 1) {
                 *reinterpret_cast<u32x2_t*>(dst + (x - 1) * kVFragX) = v_even;
                 *reinterpret_cast<u32x2_t*>(dst + x * kVFragX) = v_odd;
             }
         } else {
+            auto halves = [](float lo, float hi) {
+                return __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_pkrtz(lo, hi));
+            };
             auto at = [&](int i) { return (x & 1) ? bf16_hi(raw.v[i][x >> 1]) : bf16_lo(raw.v[i][x >> 1]); };
             *reinterpret_cast<u32x2_t*>(dst + x * kVFragX) =
                 u32x2_t{halves(at(0), at(1)), halves(at(2), at(3))};

@@ -75,21 +75,27 @@ __device__ __forceinline__ f16x8_t as_f16x8(u32x4_t v) { return __builtin_bit_ca
 __device__ __forceinline__ u32x4_t load16(const void* p) {
     return *reinterpret_cast<const u32x4_t*>(p);
 }
-// Eight E4M3 codes (two dwords) -> eight bf16 values, element order kept.  Every E4M3
-// value is a bf16 value, so the float -> bf16 conversion (one packed instruction per
-// pair) does not round.
+// Two E4M3 codes (bytes 0 and 1 of a dword, or 2 and 3) as a bf16 or an fp16 pair, in one instruction
+// each.  Every E4M3 value is a bf16 and an fp16 value, subnormal ones included: nothing rounds.
+template <bool HIGH>
+__device__ __forceinline__ uint32_t e4m3x2_to_bf16x2(uint32_t codes) {
+    return __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8((int)codes, 1.0f, HIGH));
+}
+template <bool HIGH>
+__device__ __forceinline__ uint32_t e4m3x2_to_f16x2(uint32_t codes) {
+    return __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_f16_fp8((int)codes, 1.0f, HIGH));
+}
+// Eight codes (two dwords) -> eight bf16 values, element order kept.
 __device__ __forceinline__ u32x4_t e4m3x8_to_bf16x8(u32x2_t r) {
-    typedef float f32x2_t __attribute__((ext_vector_type(2)));
-    typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
-    u32x4_t o;
-#pragma unroll
-    for (int dw = 0; dw < 2; ++dw) {
-        const f32x2_t lo = __builtin_amdgcn_cvt_pk_f32_fp8((int)r[dw], false);  // bytes 0, 1
-        const f32x2_t hi = __builtin_amdgcn_cvt_pk_f32_fp8((int)r[dw], true);   // bytes 2, 3
-        o[2 * dw] = __builtin_bit_cast(uint32_t, __builtin_convertvector(lo, bf16x2_t));
-        o[2 * dw + 1] = __builtin_bit_cast(uint32_t, __builtin_convertvector(hi, bf16x2_t));
-    }
-    return o;
+    return u32x4_t{e4m3x2_to_bf16x2<false>(r[0]), e4m3x2_to_bf16x2<true>(r[0]),
+                   e4m3x2_to_bf16x2<false>(r[1]), e4m3x2_to_bf16x2<true>(r[1])};
+}
+// The low or the high 16 bits of two dwords, as one dword.
+__device__ __forceinline__ uint32_t low_halves(uint32_t first, uint32_t second) {
+    return __builtin_amdgcn_perm(second, first, 0x05040100u);
+}
+__device__ __forceinline__ uint32_t high_halves(uint32_t first, uint32_t second) {
+    return __builtin_amdgcn_perm(second, first, 0x07060302u);
 }
 __device__ __forceinline__ u32x4_t widen_raw(u32x4_t r) { return r; }
 __device__ __forceinline__ u32x4_t widen_raw(u32x2_t r) { return e4m3x8_to_bf16x8(r); }
@@ -670,8 +676,6 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void t
 #pragma unroll
             for (int i = 0; i < NKL; ++i)
                 ks[(32 * sw + 16 * hw + RPL * i + rb) * KROW + pa] = widen_raw(kraw[i]);
-            const u32x4_t vw[4] = {widen_raw(vraw[0]), widen_raw(vraw[1]), widen_raw(vraw[2]),
-                                   widen_raw(vraw[3])};
             // This half's four contraction slots of every V^T fragment (8 of its 16
             // bytes), converted to fp16 for the P V product once for all row blocks:
             // element x of the lane's 16-byte piece (head_dim 64: of the lane's half of
@@ -680,25 +684,36 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void t
             uint32_t dw[4][NX / 2];  // the dwords (two elements each) this lane transposes
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
-                if constexpr (D == 128) {
+                if constexpr (FP8) {  // (fp16 already)
 #pragma unroll
-                    for (int j = 0; j < 4; ++j) dw[i][j] = vw[i][j];
+                    for (int j = 0; j < NX / 4; ++j) {
+                        const uint32_t codes = D == 128 ? vraw[i][j] : (a & 1) ? vraw[i][1] : vraw[i][0];
+                        dw[i][2 * j] = e4m3x2_to_f16x2<false>(codes);
+                        dw[i][2 * j + 1] = e4m3x2_to_f16x2<true>(codes);
+                    }
+                } else if constexpr (D == 128) {
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) dw[i][j] = vraw[i][j];
                 } else {
-                    dw[i][0] = (a & 1) ? vw[i][2] : vw[i][0];
-                    dw[i][1] = (a & 1) ? vw[i][3] : vw[i][1];
+                    dw[i][0] = (a & 1) ? vraw[i][2] : vraw[i][0];
+                    dw[i][1] = (a & 1) ? vraw[i][3] : vraw[i][1];
                 }
             }
+            auto halves = [](float lo, float hi) {
+                return __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_pkrtz(lo, hi));
+            };
 #pragma unroll
             for (int j = 0; j < NX / 2; ++j) {
                 u32x2_t te, to;
-                te[0] = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_pkrtz(
-                                                         bf16_lo(dw[0][j]), bf16_lo(dw[1][j])));
-                te[1] = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_pkrtz(
-                                                         bf16_lo(dw[2][j]), bf16_lo(dw[3][j])));
-                to[0] = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_pkrtz(
-                                                         bf16_hi(dw[0][j]), bf16_hi(dw[1][j])));
-                to[1] = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_pkrtz(
-                                                         bf16_hi(dw[2][j]), bf16_hi(dw[3][j])));
+                if constexpr (FP8) {
+                    te = u32x2_t{low_halves(dw[0][j], dw[1][j]), low_halves(dw[2][j], dw[3][j])};
+                    to = u32x2_t{high_halves(dw[0][j], dw[1][j]), high_halves(dw[2][j], dw[3][j])};
+                } else {
+                    te = u32x2_t{halves(bf16_lo(dw[0][j]), bf16_lo(dw[1][j])),
+                                 halves(bf16_lo(dw[2][j]), bf16_lo(dw[3][j]))};
+                    to = u32x2_t{halves(bf16_hi(dw[0][j]), bf16_hi(dw[1][j])),
+                                 halves(bf16_hi(dw[2][j]), bf16_hi(dw[3][j]))};
+                }
                 vs2[((sw * NX + 2 * j) * 64 + lane) * 2 + hw] = te;
                 vs2[((sw * NX + 2 * j + 1) * 64 + lane) * 2 + hw] = to;
             }
