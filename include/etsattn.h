@@ -255,8 +255,9 @@ ets_status ets_plan_append_rows(const ets_ctx* ctx, int64_t* rows);
  *                    device.  0 or -1 = separate merge launch, the default: it measures
  *                    faster (the device-scope round trips at the end of the last item
  *                    cost more than the launch they replace)
- *   "interleave"     1 (default) = the workgroups that hold small items are spread through
- *                    the launch order; 0 = they follow all the others
+ *   "interleave"     1 (default) = the launch order is the longest work first in calls of few
+ *                    rounds over the chip, and spreads the workgroups that hold small items
+ *                    through the others in longer ones; 0 = they follow all the others
  *   "wave_items"     a work item of at most 16 query rows and at most this many
  *                    tokens is walked by a single wavefront, four such items to
  *                    a workgroup (default 512; 0 = every item gets a workgroup)

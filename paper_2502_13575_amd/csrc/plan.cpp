@@ -691,20 +691,26 @@ ets_status build(const ets_shape& shape, const PlanOptions& opt, const ets_tree&
         }
         p.wg_map.clear();
         p.wg_map.reserve(heavy.size() + light.size());
-        // Units of few rounds (group kernel): longest first, whatever the kind.  With 300 to 1 600
-        // units per kv head's share of the chip the merged sequence is 3 to 15 % slower up to three rounds
-        // over the resident workgroups, and as much faster from there on.
+        // Units of few rounds over the resident workgroups: longest first, whatever the kind, so that the
+        // launch does not end on a long one.  Group kernel: the merged sequence is 3 to 15 % slower up to
+        // three rounds, and as much faster from there on.  The other kernel, 54 drawn trees, merged over
+        // longest first: 0.98 to 1.34 up to eight rounds, median 1.02 (64 diverging leaves 34.4 -> 33.0 us, 100
+        // leaves with head_dim 64 26.0 -> 23.7, 196 leaves of one query head 29.3 -> 24.6); 0.96 to 1.03, median
+        // 0.99, beyond (12 searches of 292 leaves 387 against 405).
         const int64_t n_units = ((int64_t)heavy.size() + (int64_t)light.size()) * shape.n_kv_heads;
-        if (opt.interleave && p.groups && n_units < 3 * kResident) {
+        if (opt.interleave && n_units < (p.groups ? 3 : 8) * kResident) {
             auto duration = [&](const std::pair<int64_t, int32_t>& u) {  // in units of half a tile
                 if (u.second >= 0) {
                     const CascadeItem& it = p.cascade_items[(size_t)u.second];
                     const int64_t rows = (int64_t)it.n_ent * G;
+                    if (!p.groups)  // (tiles of up to 64 rows; four waves that walk 16 tokens each)
+                        return rows > 16 ? ceil_div(u.first, kTile) * 25 : ceil_div(u.first, kTile) * 16;
                     return rows > 64 ? ceil_div(u.first, kTile) * 21 : rows > 32 ? ceil_div(u.first, kTile) * 16
                            : rows > 16 ? ceil_div(u.first, kTile) * 14 : ceil_div(u.first, 2 * kTile) * 16;
                 }
                 // four small items, the longest first
-                return ceil_div(p.cascade_items[(size_t)(p.n_single + 4 * (-(int64_t)u.second - 1))].n_tokens, 32) * 16;
+                const int64_t n = p.cascade_items[(size_t)(p.n_single + 4 * (-(int64_t)u.second - 1))].n_tokens;
+                return p.groups ? ceil_div(n, 32) * 16 : ceil_div(n, 16) * 14;
             };
             std::vector<std::pair<int64_t, int32_t>> all;
             for (const auto* kind : {&heavy, &light})
