@@ -361,18 +361,21 @@ ets_status build(const ets_shape& shape, const PlanOptions& opt, const ets_tree&
     // segments into one item (see below); but only two of its workgroups are resident, so that calls of
     // short items and calls that stream are slower with it.  It takes the plans whose row-parallel
     // tiles (counted at 64 query rows; about 3.3 ns of the whole chip each) are at least eight for each of
-    // its resident workgroups and fill at least three tenths of the time the unique bytes take.  Calls
-    // of 60 drawn trees and the performance cases, the other kernel's time over this one's: beyond both
-    // lines 1.00 to 1.40, median 1.10 (16 searches of 256 leaves, 64 query heads, 2 002 -> 1 822 us; one,
-    // 137 -> 130; 475 leaves, head_dim 64, 116 -> 84); tiles enough but 0.09 to 0.26 of the bytes' time
-    // 0.92 to 0.99; fewer tiles 0.83 to 1.26, median 0.95.
+    // its resident workgroups and fill at least three tenths of the time the unique bytes take; the fewer
+    // they are, the larger the part they have to fill: tiles times that part above 3 500.  The other
+    // kernel's time over this one's, 40 drawn trees beyond the first two lines: below the third 0.90 to
+    // 1.07, median 0.99 (258 leaves of 32 query heads, 31 short steps, 57 us against 51; 146 leaves 73
+    // against 69), above it 0.97 to 1.29, median 1.06 (507 leaves with head_dim 64 71 against 91 us, 414
+    // leaves with 64 query heads 239 against 261).  Tiles enough but 0.09 to 0.26 of the bytes' time 0.92 to
+    // 0.99; fewer tiles 0.83 to 1.26, median 0.95.
     const int64_t hbm_ns = st.unique_kv_bytes * (esz < 2 ? 2 : 1) / 5500;
     int64_t tiles64 = 0;
     for (const Seg& sg : segs)
         if (sg.cascade && sg.cnt * G > 16)
             tiles64 += ceil_div(sg.tokens, kTile) * ceil_div(sg.cnt * G, kTreeAttnRowsPerItem) * shape.n_kv_heads;
     p.groups = cascade_ok && !any_wide && opt.cascade_rows == 0 && opt.fuse_merge != 1 &&
-               tiles64 > kGroupMinTiles && tiles64 * 11 > hbm_ns;
+               tiles64 > kGroupMinTiles && tiles64 * 11 > hbm_ns &&
+               (double)tiles64 * tiles64 * 3.3 > 3500.0 * hbm_ns;
     const int64_t ent_per_item =
         std::max<int64_t>(1, (p.groups ? kGroupRowsPerItem : opt.cascade_rows > 0 ? opt.cascade_rows : kTreeAttnRowsPerItem) / G);
     // cost model in nanoseconds: a resident workgroup needs about t_tile per tile of 64

@@ -67,9 +67,11 @@ def attend(ctx, st, tree, kd, vd, qd):
 
 @pytest.mark.parametrize("fp8", [False, True])
 @pytest.mark.parametrize("hq,d,rows,root", [
-    (64, 128, 512, 4160), (32, 128, 516, 4170), (16, 128, 520, 4160), (8, 128, 510, 4161),   # several groups
-    (64, 128, 192, 11000), (64, 128, 104, 33000), (32, 128, 232, 8300),                       # fewer than two
-    (64, 64, 560, 4160), (32, 64, 600, 4175), (8, 64, 515, 4160)])
+    # several groups (with one or two heads to a kv head more rows of leaf nodes stand beside the root: it has
+    # to be long enough for the planner to choose this kernel)
+    (64, 128, 512, 4160), (32, 128, 516, 4170), (16, 128, 520, 8320), (8, 128, 510, 16321),
+    (64, 128, 192, 11000), (64, 128, 104, 33000), (32, 128, 232, 8300),  # fewer than two
+    (64, 64, 560, 4160), (32, 64, 600, 4175), (8, 64, 515, 12320)])
 def test_parity_over_row_counts_formats_and_head_sizes(hq, d, rows, root, fp8):
     cfg = TreeConfig("group", 8, hq, d, "bf16", 0, 0, 0, 0, 0, None, seed=71 + rows)
     group = hq // 8
