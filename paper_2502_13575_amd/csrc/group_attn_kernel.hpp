@@ -26,7 +26,7 @@
 // behind L2 first: 512 leaves read 2.0 GB past L2 in 370 us.  Whole calls, the other kernel -> this one,
 // us: 16 searches of 256 leaves with 64 query heads 2 002 -> 1 822, one of them 137 -> 130; 475 leaves
 // with 64 query heads of 64 116 -> 84; 512 leaves with 32 query heads 375 -> 370, over E4M3 pools
-// 289 -> 284.  Not faster: segments walked by resident workgroups in lists made by the planner (no slot
+// 289 -> 284 (267 with codes converted straight to fp16).  Not faster: segments walked by resident workgroups in lists made by the planner (no slot
 // idle, but every tile as much longer).
 #pragma once
 
