@@ -39,6 +39,8 @@ struct Shared {
     int32_t above = -1;          // the shared list before it on the way from the root
     bool wide = false;
     bool sole = true;            // nobody else reads these nodes
+    int32_t tail = 0;            // its last leaf queries, which keep an item of their own
+    int32_t slots = -1;          // lists with the same number here end at the same partial slot
 };
 
 struct Chunk {
@@ -183,17 +185,17 @@ void refresh_units(Plan& p) {
 // Cuts the leaf queries (in depth-first order) into groups of at most `room` consecutive ones, with
 // the fewest tokens for the groups to read: the sum over the groups of the shared rows above any of
 // their leaf queries.  What two neighbours have in common is read once if they share a group and
-// twice if a boundary stands between them, so a boundary costs the rows above both (`common[i]`:
-// above leaf queries i - 1 and i).  Returns the first leaf query of every group, and the end.
-std::vector<int32_t> group_leaves(const std::vector<int64_t>& common, int32_t room) {
+// twice if a boundary stands between them, so a boundary costs the rows above both (`costs[i]`:
+// between leaf queries i - 1 and i).  Returns the first leaf query of every group, and the end.
+std::vector<int32_t> group_leaves(const std::vector<int64_t>& costs, int32_t room) {
     constexpr int64_t kGroupTokens = 32;  // and a group of its own costs about the start of an item
-    const int32_t L = (int32_t)common.size();
+    const int32_t L = (int32_t)costs.size();
     std::vector<int64_t> cost((size_t)L + 1, 0);
     std::vector<int32_t> from((size_t)L + 1, 0);
     for (int32_t j = 1; j <= L; ++j) {
         cost[j] = std::numeric_limits<int64_t>::max();
         for (int32_t i = std::max(0, j - room); i < j; ++i) {
-            const int64_t c = cost[i] + common[i] + kGroupTokens;
+            const int64_t c = cost[i] + costs[i] + kGroupTokens;
             if (c < cost[j]) {
                 cost[j] = c;
                 from[j] = i;
@@ -387,13 +389,23 @@ ets_status build(const ets_shape& shape, const PlanOptions& opt, const ets_tree&
     const int64_t t_tile = p.groups ? 2000 : 2500, t_mem = t_tile, t_item = 7000;
     const int64_t kResident = p.groups && shape.head_dim == 128 ? 512 : 768;
     auto tile_cost = [&](int64_t) { return t_tile; };
+    // Items of at most 16 query rows apply weights of 16 bits to V as it is, larger ones weights of 11
+    // bits to V in fp16, which ends at 65 504.  Cut into items of 64 query rows, a segment's last leaf queries
+    // are in an item of the former kind where at most 16 rows are left over; larger items leave these
+    // leaf queries out: nobody gets fewer bits by the larger item.  (16 searches of 256 leaves with
+    // 64 query heads, 6 % of the leaf queries' rows: 1 916 us against 1 831 with them inside; one of
+    // them 133 against 130, 512 leaves with 32 query heads 368 against 366.)
+    auto tail_of = [&](const Seg& sg) {
+        const int64_t per64 = std::max<int64_t>(1, kTreeAttnRowsPerItem / G), rest = sg.cnt % per64;
+        return (int32_t)(p.groups && rest * G <= 16 ? rest : 0);
+    };
     // The shared lists.  A segment by itself would cost every leaf query beneath it a partial result,
     // and an item for every ent_per_item of them.  So the leaf queries are grouped, and within a
     // group the segments that the same leaf queries of it read are walked as one list: the path down
     // to a group's last common node is one item, and so is every stretch of a branch below it.
     std::vector<Shared> shared;
     std::vector<int32_t> last_shared(L, -1);  // by entry: the shared list nearest to its leaf
-    std::vector<std::pair<int32_t, int32_t>> group_of;  // by entry, if grouped: its group's entries
+    std::vector<std::pair<int32_t, int32_t>> own_shared;  // (entry, shared segment) read by that entry alone
     // It pays where partial results are a good part of the traffic, and costs L2 hits where they are not:
     // groups walk the same rows at different times, the row groups of one segment at the same time.
     // Joined against by segment, us: 16 searches of 256 leaves with 64 query heads (31 % of the KV bytes in
@@ -420,6 +432,7 @@ ets_status build(const ets_shape& shape, const PlanOptions& opt, const ets_tree&
             sh.tokens = sg.tokens;
             sh.above = above;
             sh.wide = sg.wide;
+            sh.tail = tail_of(sg);
             shared.push_back(std::move(sh));
         }
         for (int32_t e = 0; e < L; ++e) last_shared[e] = of_seg[seg_of[p.leaf_node[p.ent_order[e]]]];
@@ -435,7 +448,6 @@ ets_status build(const ets_shape& shape, const PlanOptions& opt, const ets_tree&
             }
             if (sg.cascade) above_rows[i] += sg.tokens;
         }
-        group_of.resize((size_t)L);
         std::vector<int32_t> leaf_seg(L);
         for (int32_t e = 0; e < L; ++e) leaf_seg[e] = seg_of[p.leaf_node[p.ent_order[e]]];
         for (int32_t e = 1; e < L; ++e) {
@@ -446,8 +458,14 @@ ets_status build(const ets_shape& shape, const PlanOptions& opt, const ets_tree&
             }
             if (x == y && x >= 0) common[e] = above_rows[x];
         }
-        const std::vector<int32_t> bounds = group_leaves(common, (int32_t)ent_per_item);
-        std::vector<int32_t> in_group(segs.size(), -1), list_of(segs.size(), -1), members;
+        // (a boundary where a tail begins costs less: its segment is read twice there anyway)
+        std::vector<int64_t> costs = common;
+        for (const Seg& sg : segs)
+            if (const int32_t n = tail_of(sg); sg.cascade && n > 0 && n < sg.cnt)
+                costs[sg.ent_begin + sg.cnt - n] -= sg.tokens;
+        const std::vector<int32_t> bounds = group_leaves(costs, (int32_t)ent_per_item);
+        auto slots_of = [&](int32_t e) { return last_shared[e] < 0 ? -1 : shared[last_shared[e]].slots; };
+        std::vector<int32_t> in_group(segs.size(), -1), members;
         for (size_t g = 0; g + 1 < bounds.size(); ++g) {
             const int32_t first = bounds[g], end = bounds[g + 1];
             members.clear();
@@ -459,40 +477,63 @@ ets_status build(const ets_shape& shape, const PlanOptions& opt, const ets_tree&
             std::sort(members.begin(), members.end());  // parents before children
             for (int32_t s : members) {
                 const Seg& sg = segs[s];
-                const int32_t above = sg.parent_seg >= 0 ? list_of[sg.parent_seg] : -1;
-                list_of[s] = above;
-                const int32_t lo = std::max(first, sg.ent_begin);
-                const int32_t n = std::min(end, sg.ent_begin + (int32_t)sg.cnt) - lo;
-                if (!sg.cascade || n < 2) continue;
-                if (above < 0 || shared[above].n_ent != n) {  // (a subset of the list above it)
-                    list_of[s] = (int32_t)shared.size();
-                    Shared sh;
-                    sh.ent_begin = lo;
-                    sh.n_ent = n;
-                    sh.above = above;
-                    shared.push_back(std::move(sh));
+                if (!sg.cascade) continue;
+                const int32_t seg_end = sg.ent_begin + (int32_t)sg.cnt, tail = seg_end - tail_of(sg);
+                const int32_t hi = std::min(end, seg_end);
+                // the group's entries of the segment, cut where its tail begins and where the entries' partial
+                // slots so far differ (a list's slots are numbered alike for all its entries)
+                for (int32_t lo = std::max(first, sg.ent_begin), next; lo < hi; lo = next) {
+                    for (next = lo + 1; next < hi && slots_of(next) == slots_of(lo);) ++next;
+                    const int32_t cut = lo < tail && tail < next ? tail : next;
+                    // Lists of both parts, of a single entry too, keep their slots alike for what the
+                    // entries on both sides read together further down.
+                    const bool pair = cut < next && next - lo > 2 && common[cut] > above_rows[s];
+                    const bool lists[2] = {pair || cut - lo > 1, pair || next - cut > 1};
+                    bool made = true;
+                    for (int k = 0; k < 2; ++k) {
+                        const int32_t from = k ? cut : lo, to = k ? next : cut, n = to - from;
+                        if (n == 0) continue;
+                        if (!lists[k]) {
+                            own_shared.push_back({from, s});
+                            continue;
+                        }
+                        int32_t list = last_shared[from];
+                        if (list < 0 || last_shared[to - 1] != list || shared[list].n_ent != n) {
+                            Shared sh;
+                            sh.ent_begin = from;
+                            sh.n_ent = n;
+                            sh.above = list;
+                            list = (int32_t)shared.size();
+                            sh.slots = k && pair && made ? list - 1 : list;
+                            shared.push_back(std::move(sh));
+                            std::fill(last_shared.begin() + from, last_shared.begin() + to, list);
+                        } else {
+                            made = false;  // (these entries are all that read the list above)
+                        }
+                        Shared& sh = shared[list];
+                        sh.nodes.insert(sh.nodes.end(), sg.nodes.begin(), sg.nodes.end());
+                        sh.tokens += sg.tokens;
+                        sh.sole = sh.sole && sg.cnt == n;
+                    }
                 }
-                Shared& sh = shared[list_of[s]];
-                sh.nodes.insert(sh.nodes.end(), sg.nodes.begin(), sg.nodes.end());
-                sh.tokens += sg.tokens;
-                sh.sole = sh.sole && sg.cnt == n;
-            }
-            for (int32_t e = first; e < end; ++e) {
-                last_shared[e] = list_of[leaf_seg[e]];
-                group_of[e] = {first, end};
             }
         }
+        std::sort(own_shared.begin(), own_shared.end());
     }
     // segments that the leaf query of entry e reads by itself, leaf first
     auto own_segs = [&](int32_t e, std::vector<int32_t>& out) {
         out.clear();
-        for (int32_t s = seg_of[p.leaf_node[p.ent_order[e]]]; s >= 0; s = segs[s].parent_seg) {
-            bool own = !segs[s].cascade;
-            if (!own && grouped)
-                own = std::min(group_of[e].second, segs[s].ent_begin + (int32_t)segs[s].cnt) -
-                          std::max(group_of[e].first, segs[s].ent_begin) < 2;
-            if (own) out.push_back(s);
-        }
+        for (int32_t s = seg_of[p.leaf_node[p.ent_order[e]]]; s >= 0; s = segs[s].parent_seg)
+            if (!segs[s].cascade ||
+                (grouped && std::binary_search(own_shared.begin(), own_shared.end(), std::make_pair(e, s))))
+                out.push_back(s);
+    };
+    // the items of a shared list: f(its first entry, counted in the list, and how many)
+    auto for_items = [&](const Shared& sh, auto f) {
+        const int64_t per_item = sh.wide ? ent_per_wide : ent_per_item;
+        const int64_t body = sh.n_ent - (sh.wide ? 0 : sh.tail);
+        for (int64_t e0 = 0; e0 < body; e0 += per_item) f(e0, std::min(per_item, body - e0));
+        if (body < sh.n_ent) f(body, sh.n_ent - body);
     };
     int64_t own_total = 0, work_ns = 0, wide_work_ns = 0;
     int64_t items_est = L;  // one item per leaf query for what it reads itself, plus:
@@ -502,11 +543,10 @@ ets_status build(const ets_shape& shape, const PlanOptions& opt, const ets_tree&
                             shape.n_kv_heads;
             continue;
         }
-        for (int64_t e0 = 0; e0 < sh.n_ent; e0 += ent_per_item) {
-            work_ns += ceil_div(sh.tokens, kTile) *
-                       tile_cost(std::min(ent_per_item, sh.n_ent - e0) * G) * shape.n_kv_heads;
+        for_items(sh, [&](int64_t, int64_t n) {
+            work_ns += ceil_div(sh.tokens, kTile) * tile_cost(n * G) * shape.n_kv_heads;
             items_est += 1;
-        }
+        });
     }
     std::vector<int32_t> reads;
     for (int32_t e = 0; e < L; ++e) {
@@ -613,8 +653,8 @@ ets_status build(const ets_shape& shape, const PlanOptions& opt, const ets_tree&
             const Chunk& ch = shared_chunks[i][c];
             const int64_t per_item = sh.wide ? ent_per_wide : ent_per_item;
             const int32_t sole = sh.sole && sh.n_ent <= per_item ? 1 : 0;
-            for (int64_t e0 = 0; e0 < sh.n_ent; e0 += per_item) {
-                const int32_t ne = (int32_t)std::min<int64_t>(per_item, sh.n_ent - e0);
+            for_items(sh, [&](int64_t e0, int64_t n) {
+                const int32_t ne = (int32_t)n;
                 const CascadeItem it{ch.run_begin, ch.run_end, sh.ent_begin + (int32_t)e0, ne,
                                      sh.prefix + c, ch.tokens, sole, 0};
                 if (sh.wide) {
@@ -625,7 +665,7 @@ ets_status build(const ets_shape& shape, const PlanOptions& opt, const ets_tree&
                     cascade_cost.push_back(ceil_div(ch.tokens, kTile) * tile_cost((int64_t)ne * G));
                     p.max_cascade_ent = std::max(p.max_cascade_ent, ne);
                 }
-            }
+            });
         }
     }
 

@@ -153,3 +153,29 @@ def test_replayed_from_a_graph():
             torch.cuda.synchronize()
             assert torch.equal(out, want) and torch.equal(lse, want_lse)
             attend(ctx, st, tree, kd, vd, qd)
+
+
+@pytest.mark.parametrize("hq,d,rows,root", [
+    (64, 128, 80, 17000), (64, 128, 208, 11000),  # one list per segment: 80 = 64 + 16, 208 = 3 x 64 + 16
+    (64, 128, 520, 4160), (32, 128, 516, 4170), (16, 128, 520, 8320), (8, 128, 520, 16321), (64, 64, 584, 4160)])
+def test_v_past_fp16_is_cut_off_for_no_more_rows_than_in_items_of_64(hq, d, rows, root):
+    """Items of more than 16 query rows hold V in fp16, others as it is: with V = 99 840 and equal
+    weights the output is the mean of 65 504 and 99 840 over the rows read in the one and in the other kind,
+    exactly up to fp32 sums of at most 40 000 equal terms in steps of 32 (1 300 roundings at 2^-24)."""
+    cfg = TreeConfig("group", 8, hq, d, "bf16", 0, 0, 0, 0, 0, None, seed=79)
+    tree = edge_tree(root, sizes_for(rows, hq // 8, rows + hq), rows + d)
+    k = torch.randn(8, tree.pool_tokens, d, device="cuda:0").to(torch.bfloat16)
+    v = torch.full((8, tree.pool_tokens, d), 99840.0, dtype=torch.bfloat16, device="cuda:0")
+    q = torch.zeros(tree.n_leaves, hq, d, dtype=torch.bfloat16, device="cuda:0")
+    print("case group large v", hq, d, rows, root, flush=True)
+    with make_ctx(cfg) as ctx, make_ctx(cfg, {"cascade_rows": 64}) as by64:
+        st = ctx.plan(tree.parent, tree.tok_offset, tree.n_tokens, tree.leaf_node)
+        assert takes_group_kernel(ctx, cfg, tree) and ctx.check().violations == 0
+        out, lse, _ = attend(ctx, st, tree, k, v, q)
+        st = by64.plan(tree.parent, tree.tok_offset, tree.n_tokens, tree.leaf_node)
+        want, want_lse, _ = attend(by64, st, tree, k, v, q)
+        torch.cuda.synchronize()
+    tol = 1300 * 2.0 ** -24
+    assert bool((want < 99840 * (1 - tol)).any()) and bool((out <= 99840 * (1 + tol)).all())
+    assert bool((out >= want * (1 - 2 * tol)).all())
+    assert torch.allclose(lse, want_lse, atol=2 * tol, rtol=0)
