@@ -10,6 +10,7 @@
 #include <algorithm>
 #include <limits>
 #include <new>
+#include <utility>
 
 namespace ets {
 namespace {
@@ -225,7 +226,7 @@ ets_status validate(const ets_tree& t) {
 }
 
 ets_status build(const ets_shape& shape, const PlanOptions& opt, const ets_tree& tree, int mode,
-                 Plan& p) {
+                 bool may_group, Plan& p) {
     const int32_t N = tree.n_nodes, L = tree.n_leaves;
     const int32_t G = shape.n_q_heads / shape.n_kv_heads;
     const int64_t esz = opt.kv_elem_bytes > 0 ? opt.kv_elem_bytes : shape.dtype == ETS_F32 ? 4 : 2;
@@ -375,7 +376,7 @@ ets_status build(const ets_shape& shape, const PlanOptions& opt, const ets_tree&
     for (const Seg& sg : segs)
         if (sg.cascade && sg.cnt * G > 16)
             tiles64 += ceil_div(sg.tokens, kTile) * ceil_div(sg.cnt * G, kTreeAttnRowsPerItem) * shape.n_kv_heads;
-    p.groups = cascade_ok && !any_wide && opt.cascade_rows == 0 && opt.fuse_merge != 1 &&
+    p.groups = may_group && cascade_ok && !any_wide && opt.cascade_rows == 0 && opt.fuse_merge != 1 &&
                tiles64 > kGroupMinTiles && tiles64 * 11 > hbm_ns &&
                (double)tiles64 * tiles64 * 3.3 > 3500.0 * hbm_ns;
     const int64_t ent_per_item =
@@ -415,6 +416,7 @@ ets_status build(const ets_shape& shape, const PlanOptions& opt, const ets_tree&
     int64_t by_segment = L;
     for (const Seg& sg : segs)
         if (sg.cascade) by_segment += sg.cnt;
+    p.min_workspace_bytes = (by_segment - L) * shape.n_q_heads * ((int64_t)shape.head_dim + 2) * 4;
     const bool grouped = p.groups && L >= 2 * ent_per_item &&
                          by_segment * partial_bytes * 8 > st.unique_kv_bytes * (esz < 2 ? 2 : 1);
     if (!grouped) {
@@ -896,7 +898,18 @@ ets_status build_plan(const ets_shape& shape, const PlanOptions& opt, const ets_
     ets_status s = validate(tree);
     if (s != ETS_OK) return s;
     try {
-        return build(shape, opt, tree, mode, plan);
+        s = build(shape, opt, tree, mode, true, plan);
+        // The group kernel's plans mostly have fewer partial results, but their shared lists can be cut finer: a
+        // plan that fits the static scratch with items of 64 query rows keeps them if it would not fit
+        // otherwise.  (The other plan has at least a partial result for every leaf query of a shared segment.)
+        if (s == ETS_OK && plan.groups && plan.stats.workspace_bytes > ETS_STATIC_SCRATCH_BYTES &&
+            plan.min_workspace_bytes <= ETS_STATIC_SCRATCH_BYTES) {
+            Plan by64;
+            if (build(shape, opt, tree, mode, false, by64) == ETS_OK &&
+                by64.stats.workspace_bytes <= ETS_STATIC_SCRATCH_BYTES)
+                plan = std::move(by64);
+        }
+        return s;
     } catch (const std::bad_alloc&) {
         plan.valid = false;
         return ETS_ERR_NOMEM;

@@ -84,3 +84,21 @@ def test_the_leaf_queries_of_one_search_share_one_list_down_to_their_last_common
     assert stats[1].n_partials == 4 * sum(i + 2 for i in range(n))
     # by group: the parts above the group's first branch are one, those below it stay apart
     assert stats[0].n_partials == 4 * sum((i % 4) + 2 for i in range(n))
+
+
+@pytest.mark.parametrize("hq,d,leaves,root,leaf", [(64, 64, 192, 50000, 16), (64, 64, 256, 8320, 64),
+                                                   (64, 64, 320, 12480, 16), (64, 64, 512, 4160, 16)])
+def test_a_plan_that_fits_the_static_scratch_by_segment_fits_it(hq, d, leaves, root, leaf):
+    """The group kernel's lists can be cut finer than items of 64 query rows: such a plan must not grow
+    out of the buffer of ets_tree_decode_attn_static."""
+    parent = np.concatenate([[-1], np.zeros(leaves, np.int32)]).astype(np.int32)
+    n_tok = np.concatenate([[root], np.full(leaves, leaf)]).astype(np.int32)
+    off = np.cumsum(n_tok.astype(np.int64)) - n_tok
+    size = []
+    for opts in ({}, {"cascade_rows": 64}):
+        with ets.Context(8, hq, d, ets.ETS_BF16, -1) as ctx:
+            for k, v in opts.items():
+                ctx.set_option(k, v)
+            size.append(ctx.plan(parent, off, n_tok, np.arange(1, leaves + 1, dtype=np.int32)).workspace_bytes)
+            assert ctx.check().violations == 0
+    assert size[1] <= ets.ETS_STATIC_SCRATCH_BYTES and size[0] <= ets.ETS_STATIC_SCRATCH_BYTES
