@@ -151,6 +151,11 @@ ets_status ets_plan(ets_ctx* ctx, const ets_tree* tree, int mode /* ets_plan_mod
 
 ets_status ets_plan_stats(const ets_ctx* ctx, ets_stats* out /* host */);
 
+/* Query rows that one work item of the plan's shared-node kernel may hold, in *rows (host):
+ * 128 if the planner gave the call to the kernel of such items (group_attn_kernel), 64 or
+ * the option "cascade_rows" otherwise (tree_attn_kernel), 0 if the plan has no such items. */
+ets_status ets_plan_item_rows(const ets_ctx* ctx, int32_t* rows);
+
 /* Root->leaf node chains of the planned tree in CSR form, for checking the
  * planner's indexing bit for bit: path_ptr[n_leaves + 1], path_nodes[cap]
  * (host).  *n_path_nodes (may be NULL) receives the total; if it exceeds cap

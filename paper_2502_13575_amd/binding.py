@@ -106,6 +106,8 @@ def load_library():
     lib.ets_plan.argtypes = [vp, C.POINTER(_EtsTree), C.c_int]
     lib.ets_plan_stats.restype = C.c_int
     lib.ets_plan_stats.argtypes = [vp, C.POINTER(EtsStats)]
+    lib.ets_plan_item_rows.restype = C.c_int
+    lib.ets_plan_item_rows.argtypes = [vp, i32p]
     lib.ets_plan_paths.restype = C.c_int
     lib.ets_plan_paths.argtypes = [vp, i64p, i32p, C.c_int64, i64p]
     lib.ets_plan_leaf_counts.restype = C.c_int
@@ -269,6 +271,13 @@ def ets_plan_stats(ctx) -> EtsStats:
     st = EtsStats()
     _check(load_library().ets_plan_stats(ctx, C.byref(st)), "ets_plan_stats")
     return st
+
+
+def ets_plan_item_rows(ctx) -> int:
+    """Query rows per work item of the plan's shared-node kernel (128: group_attn_kernel)."""
+    rows = C.c_int32()
+    _check(load_library().ets_plan_item_rows(ctx, C.byref(rows)), "ets_plan_item_rows")
+    return int(rows.value)
 
 
 def ets_plan_paths(ctx):
@@ -449,6 +458,9 @@ class Context:
 
     def stats(self) -> EtsStats:
         return ets_plan_stats(self._ctx)
+
+    def item_rows(self) -> int:
+        return ets_plan_item_rows(self._ctx)
 
     def paths(self):
         return ets_plan_paths(self._ctx)

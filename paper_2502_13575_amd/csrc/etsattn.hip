@@ -734,6 +734,13 @@ ets_status ets_plan_stats(const ets_ctx* ctx, ets_stats* out) {
     return ETS_OK;
 }
 
+ets_status ets_plan_item_rows(const ets_ctx* ctx, int32_t* rows) {
+    if (!ctx || !rows) return ETS_ERR_INVALID_ARG;
+    if (!ctx->plan.valid) return ETS_ERR_NO_PLAN;
+    *rows = ctx->plan.item_rows;
+    return ETS_OK;
+}
+
 ets_status ets_plan_paths(const ets_ctx* ctx, int64_t* path_ptr, int32_t* path_nodes, int64_t cap,
                           int64_t* n_path_nodes) {
     if (!ctx || !path_ptr || cap < 0 || (cap > 0 && !path_nodes)) return ETS_ERR_INVALID_ARG;

@@ -379,8 +379,9 @@ ets_status build(const ets_shape& shape, const PlanOptions& opt, const ets_tree&
     p.groups = may_group && cascade_ok && !any_wide && opt.cascade_rows == 0 && opt.fuse_merge != 1 &&
                tiles64 > kGroupMinTiles && tiles64 * 11 > hbm_ns &&
                (double)tiles64 * tiles64 * 3.3 > 3500.0 * hbm_ns;
-    const int64_t ent_per_item =
-        std::max<int64_t>(1, (p.groups ? kGroupRowsPerItem : opt.cascade_rows > 0 ? opt.cascade_rows : kTreeAttnRowsPerItem) / G);
+    const int64_t rows_per_item =
+        p.groups ? kGroupRowsPerItem : opt.cascade_rows > 0 ? opt.cascade_rows : kTreeAttnRowsPerItem;
+    const int64_t ent_per_item = std::max<int64_t>(1, rows_per_item / G);
     // cost model in nanoseconds: a resident workgroup needs about t_tile per tile of 64
     // tokens whether it waits on memory (few rows) or computes (many rows), and t_item to
     // start and to store its partial results; kResident workgroups are resident (three per
@@ -833,6 +834,7 @@ ets_status build(const ets_shape& shape, const PlanOptions& opt, const ets_tree&
         return ETS_ERR_UNSUPPORTED;
     st.n_stream_items = (int64_t)p.stream_items.size();
     st.n_cascade_items = (int64_t)p.cascade_items.size();
+    p.item_rows = p.cascade_items.empty() ? 0 : (int32_t)rows_per_item;
     st.n_wide_items = (int64_t)p.wide_items.size();
     st.workspace_bytes = st.n_partials * shape.n_q_heads * ((int64_t)shape.head_dim + 2) * 4;
     // The matrix-core kernel can run the merge itself when it writes every partial and every

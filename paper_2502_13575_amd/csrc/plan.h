@@ -144,6 +144,7 @@ struct Plan {
     int32_t advances = 0;             // advances applied in place since the plan was built
     int32_t piece = 0;                // longest run the kernels accept (0 = any)
     bool groups = false;              // the group kernel takes the items (up to kGroupRowsPerItem rows)
+    int32_t item_rows = 0;            // query rows that a cascade item may hold (0: there are none)
     int64_t min_workspace_bytes = 0;  // of any plan whose shared segments are read one by one
     bool fused = false;               // the matrix-core kernel merges (no merge launch): every
                                       // partial comes from it and every leaf query has one

@@ -48,15 +48,6 @@ def sizes_for(rows, group, seed):
     return out
 
 
-def takes_group_kernel(ctx, cfg, tree):
-    """Whether the default plan differs from the one of 64 query rows per item."""
-    with make_ctx(cfg, {"cascade_rows": 64}) as other:
-        if ctx.stats().unique_kv_bytes != ctx.stats().unique_tokens * 4 * cfg.n_kv_heads * cfg.head_dim:
-            other.set_kv_format(ets.ETS_KV_FP8_E4M3, KS, VS)
-        st = other.plan(tree.parent, tree.tok_offset, tree.n_tokens, tree.leaf_node)
-        return st.n_cascade_items > ctx.stats().n_cascade_items
-
-
 def attend(ctx, st, tree, kd, vd, qd):
     out = torch.full((tree.n_leaves, ctx.shape.n_q_heads, ctx.shape.head_dim), float("nan"), device="cuda:0")
     lse = torch.full((tree.n_leaves, ctx.shape.n_q_heads), float("nan"), device="cuda:0")
@@ -85,7 +76,7 @@ def test_parity_over_row_counts_formats_and_head_sizes(hq, d, rows, root, fp8):
         if fp8:
             ctx.set_kv_format(ets.ETS_KV_FP8_E4M3, KS, VS)
         st = ctx.plan(tree.parent, tree.tok_offset, tree.n_tokens, tree.leaf_node)
-        assert takes_group_kernel(ctx, cfg, tree)
+        assert ctx.item_rows() == 128
         assert ctx.check().violations == 0
         kd, vd, qd = pool_to_device(k), pool_to_device(v), to_device(q)
         out, lse, _ = attend(ctx, st, tree, kd, vd, qd)
@@ -113,7 +104,7 @@ def test_growth_between_decode_steps(hq, d):
     print("case group growth", hq, d, flush=True)
     with make_ctx(cfg) as ctx, make_ctx(cfg) as fresh:
         ctx.plan(tree.parent, tree.tok_offset, tree.n_tokens, tree.leaf_node)
-        assert takes_group_kernel(ctx, cfg, tree)
+        assert ctx.item_rows() == 128
         n_tokens = tree.n_tokens.copy()
         for step in range(36):
             ctx.plan_advance()
@@ -139,7 +130,7 @@ def test_replayed_from_a_graph():
     kd, vd, qd = pool_to_device(k), pool_to_device(v), to_device(q)
     with make_ctx(cfg) as ctx:
         st = ctx.plan(tree.parent, tree.tok_offset, tree.n_tokens, tree.leaf_node)
-        assert takes_group_kernel(ctx, cfg, tree)
+        assert ctx.item_rows() == 128
         want, want_lse, ws = attend(ctx, st, tree, kd, vd, qd)
         out, lse = torch.empty_like(want), torch.empty_like(want_lse)
         s = torch.cuda.Stream()
@@ -170,7 +161,7 @@ def test_v_past_fp16_is_cut_off_for_no_more_rows_than_in_items_of_64(hq, d, rows
     print("case group large v", hq, d, rows, root, flush=True)
     with make_ctx(cfg) as ctx, make_ctx(cfg, {"cascade_rows": 64}) as by64:
         st = ctx.plan(tree.parent, tree.tok_offset, tree.n_tokens, tree.leaf_node)
-        assert takes_group_kernel(ctx, cfg, tree) and ctx.check().violations == 0
+        assert ctx.item_rows() == 128 and ctx.check().violations == 0
         out, lse, _ = attend(ctx, st, tree, k, v, q)
         st = by64.plan(tree.parent, tree.tok_offset, tree.n_tokens, tree.leaf_node)
         want, want_lse, _ = attend(by64, st, tree, k, v, q)

@@ -49,7 +49,8 @@ def test_group_plans_of_random_forests(block):
             _plan(by64, t)
             assert st.unique_tokens == by64.stats().unique_tokens
             assert st.cascade_tokens == by64.stats().cascade_tokens
-            joined += st.n_cascade_items < by64.stats().n_cascade_items
+            assert by64.item_rows() == 64
+            joined += ctx.item_rows() == 128
             rep = ctx.check()
             assert rep.violations == 0 and rep.max_entry_overreach <= 15, (seed, rep.as_dict())
             _covers(ctx, t, t.n_tokens)
@@ -102,3 +103,18 @@ def test_a_plan_that_fits_the_static_scratch_by_segment_fits_it(hq, d, leaves, r
             size.append(ctx.plan(parent, off, n_tok, np.arange(1, leaves + 1, dtype=np.int32)).workspace_bytes)
             assert ctx.check().violations == 0
     assert size[1] <= ets.ETS_STATIC_SCRATCH_BYTES and size[0] <= ets.ETS_STATIC_SCRATCH_BYTES
+
+
+def test_the_plan_says_which_kernel_takes_it():
+    one = np.array([-1], np.int32)
+    for n_tok, leaves, options, mode, rows in [
+            (16500, 200, {}, ets.ETS_PLAN_TREE, 128), (16500, 200, {"cascade_rows": 32}, ets.ETS_PLAN_TREE, 32),
+            (100, 200, {}, ets.ETS_PLAN_TREE, 64), (16500, 200, {}, ets.ETS_PLAN_FLAT, 64),
+            (16500, 200, {"mfma": 0}, ets.ETS_PLAN_TREE, 0), (0, 200, {}, ets.ETS_PLAN_TREE, 0)]:
+        with ets.Context(2, 8, 128, ets.ETS_BF16, -1) as ctx:
+            with pytest.raises(ets.EtsError):
+                ctx.item_rows()
+            for k, v in options.items():
+                ctx.set_option(k, v)
+            ctx.plan(one, np.zeros(1, np.int64), np.array([n_tok], np.int32), np.zeros(leaves, np.int32), mode)
+            assert ctx.item_rows() == rows, (n_tok, leaves, options, mode)
