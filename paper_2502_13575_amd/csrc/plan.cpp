@@ -739,12 +739,13 @@ ets_status build(const ets_shape& shape, const PlanOptions& opt, const ets_tree&
         p.wg_map.reserve(heavy.size() + light.size());
         // Units of few rounds over the resident workgroups: longest first, whatever the kind, so that the
         // launch does not end on a long one.  Group kernel: the merged sequence is 3 to 15 % slower up to
-        // three rounds, and as much faster from there on.  The other kernel, 54 drawn trees, merged over
-        // longest first: 0.98 to 1.34 up to eight rounds, median 1.02 (64 diverging leaves 34.4 -> 33.0 us, 100
-        // leaves with head_dim 64 26.0 -> 23.7, 196 leaves of one query head 29.3 -> 24.6); 0.96 to 1.03, median
-        // 0.99, beyond (12 searches of 292 leaves 387 against 405).
+        // three rounds, and as much faster from there on.  The other kernel, 82 drawn trees, merged over
+        // longest first: 0.98 to 1.24 up to five rounds, median 1.02 (64 diverging leaves 34.4 -> 33.0 us, 100
+        // leaves with head_dim 64 26.0 -> 23.7, 196 leaves of one query head 29.3 -> 24.6); 0.95 to 1.03, median
+        // 0.98, from there to eight rounds, 0.96 to 1.03, median 0.99, beyond (12 searches of 292 leaves 387
+        // against 405).
         const int64_t n_units = ((int64_t)heavy.size() + (int64_t)light.size()) * shape.n_kv_heads;
-        if (opt.interleave && n_units < (p.groups ? 3 : 8) * kResident) {
+        if (opt.interleave && n_units < (p.groups ? 3 : 5) * kResident) {
             auto duration = [&](const std::pair<int64_t, int32_t>& u) {  // in units of half a tile
                 if (u.second >= 0) {
                     const CascadeItem& it = p.cascade_items[(size_t)u.second];
