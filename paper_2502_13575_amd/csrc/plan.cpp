@@ -737,15 +737,26 @@ ets_status build(const ets_shape& shape, const PlanOptions& opt, const ets_tree&
         }
         p.wg_map.clear();
         p.wg_map.reserve(heavy.size() + light.size());
-        // Units of few rounds over the resident workgroups: longest first, whatever the kind, so that the
-        // launch does not end on a long one.  Group kernel: the merged sequence is 3 to 15 % slower up to
-        // three rounds, and as much faster from there on.  The other kernel, 82 drawn trees, merged over
-        // longest first: 0.98 to 1.24 up to five rounds, median 1.02 (64 diverging leaves 34.4 -> 33.0 us, 100
-        // leaves with head_dim 64 26.0 -> 23.7, 196 leaves of one query head 29.3 -> 24.6); 0.95 to 1.03, median
-        // 0.98, from there to eight rounds, 0.96 to 1.03, median 0.99, beyond (12 searches of 292 leaves 387
-        // against 405).
+        // Longest first, whatever the kind, where the merged sequence would end the launch on a long item:
+        //  - in units of few rounds over the resident workgroups.  Group kernel: the merged sequence is 3 to
+        //    15 % slower up to three rounds, and as much faster from there on.  The other kernel, 82 drawn trees,
+        //    merged over longest first: 0.98 to 1.24 up to five rounds, median 1.02 (64 diverging leaves 34.4 ->
+        //    33.0 us, 100 leaves with head_dim 64 26.0 -> 23.7, 196 leaves of one query head 29.3 -> 24.6);
+        //    0.95 to 1.03, median 0.98, from there to eight rounds, 0.96 to 1.03, median 0.99, beyond (12
+        //    searches of 292 leaves 387 against 405);
+        //  - where an item with many rows is handed out so late, at the same fraction of the tokens as the others,
+        //    that it lasts a fifth of the call longer than is left of it (8 searches of 45 leaves under prompts of
+        //    3 500 rows and a few short steps 101 us merged, 86 longest first; 4 of 137 120 and 99; 512
+        //    leaves under one root of 33 000 rows 1 037 and 617; up to an eighth of the call 0.97 to 1.02).
         const int64_t n_units = ((int64_t)heavy.size() + (int64_t)light.size()) * shape.n_kv_heads;
-        if (opt.interleave && n_units < (p.groups ? 3 : 5) * kResident) {
+        double overrun = 0;  // parts of the call (the items stand longest first)
+        int64_t total = 0, handed = 0;
+        for (const auto& x : heavy) total += x.first;
+        for (const auto& x : heavy) {
+            handed += x.first;
+            overrun = std::max(overrun, (double)handed / total - 1 + (double)(ceil_div(x.first, kTile) * t_tile) / call_ns);
+        }
+        if (opt.interleave && (n_units < (p.groups ? 3 : 5) * kResident || overrun > 0.2)) {
             auto duration = [&](const std::pair<int64_t, int32_t>& u) {  // in units of half a tile
                 if (u.second >= 0) {
                     const CascadeItem& it = p.cascade_items[(size_t)u.second];
