@@ -359,26 +359,42 @@ ets_status build(const ets_shape& shape, const PlanOptions& opt, const ets_tree&
         if (sg.cascade) st.cascade_tokens += sg.tokens;
         if (sg.wide) st.wide_tokens += sg.tokens;
     }
+    // Items of at most 16 query rows apply weights of 16 bits to V as it is, larger ones weights of 11
+    // bits to V in fp16, which ends at 65 504.  Cut into items of 64 query rows, a segment's last leaf queries
+    // are in an item of the former kind where at most 16 rows are left over; larger items leave these
+    // leaf queries out: nobody gets fewer bits by the larger item.  (16 searches of 256 leaves with
+    // 64 query heads, 6 % of the leaf queries' rows: 1 916 us against 1 831 with them inside; one of
+    // them 133 against 130, 512 leaves with 32 query heads 368 against 366.)
+    auto tail_of = [&](const Seg& sg) {
+        const int64_t per64 = std::max<int64_t>(1, kTreeAttnRowsPerItem / G), rest = sg.cnt % per64;
+        return (int32_t)(rest * G <= 16 ? rest : 0);
+    };
     // Which kernel.  The group kernel applies a tile to 128 query rows in about 1.0 us of a compute unit,
     // where two items of 64 rows of the other one take 1.3 together, reads it half as often and joins
-    // segments into one item (see below); but only two of its workgroups are resident, so that calls of
-    // short items and calls that stream are slower with it.  It takes the plans whose row-parallel
-    // tiles (counted at 64 query rows; about 3.3 ns of the whole chip each) are at least eight for each of
-    // its resident workgroups and fill at least three tenths of the time the unique bytes take; the fewer
-    // they are, the larger the part they have to fill: tiles times that part above 3 500.  The other
-    // kernel's time over this one's, 40 drawn trees beyond the first two lines: below the third 0.90 to
-    // 1.07, median 0.99 (258 leaves of 32 query heads, 31 short steps, 57 us against 51; 146 leaves 73
-    // against 69), above it 0.97 to 1.29, median 1.06 (507 leaves with head_dim 64 71 against 91 us, 414
-    // leaves with 64 query heads 239 against 261).  Tiles enough but 0.09 to 0.26 of the bytes' time 0.92 to
-    // 0.99; fewer tiles 0.83 to 1.26, median 0.95.
+    // segments into one item (see below); but with head_dim 128 only two of its workgroups are resident, so
+    // that calls of short items and calls that stream are slower with it.  It takes the plans whose
+    // row-parallel tiles (counted at 64 query rows; about 3.3 ns of the whole chip each)
+    //  - are more than kGroupMinTiles (fewer: the other kernel's time over this one's is 0.83 to 1.26, median
+    //    0.95) and fill at least three tenths of the time the unique bytes take (0.09 to 0.26 of it: 0.92 to 0.99);
+    //  - have to fill a larger part the fewer they are: tiles times that part above 3 500 (40 drawn trees,
+    //    below 0.90 to 1.07, median 0.99; above 0.97 to 1.29, median 1.06);
+    //  - with head_dim 128 become so many fewer tiles of 128 rows (and of a tail's), at 1 / 0.9 of the price, that
+    //    this saves a tenth of the time of the unique bytes: a segment of 81 to 128 rows halves its tiles, one of
+    //    up to 64 only pays more (108 drawn trees: below 0.86 to 1.14, geometric mean 0.983; above 0.93 to 1.20, 1.045;
+    //    with head_dim 64, 52 trees, 0.91 to 1.51, 1.14).
     const int64_t hbm_ns = st.unique_kv_bytes * (esz < 2 ? 2 : 1) / 5500;
-    int64_t tiles64 = 0;
+    int64_t tiles64 = 0, tiles128 = 0;
     for (const Seg& sg : segs)
-        if (sg.cascade && sg.cnt * G > 16)
+        if (sg.cascade && sg.cnt * G > 16) {
             tiles64 += ceil_div(sg.tokens, kTile) * ceil_div(sg.cnt * G, kTreeAttnRowsPerItem) * shape.n_kv_heads;
+            const int64_t tail = tail_of(sg);
+            tiles128 += ceil_div(sg.tokens, kTile) * shape.n_kv_heads *
+                        (ceil_div((sg.cnt - tail) * G, kGroupRowsPerItem) + (tail > 0 ? 1 : 0));
+        }
     p.groups = may_group && cascade_ok && !any_wide && opt.cascade_rows == 0 && opt.fuse_merge != 1 &&
                tiles64 > kGroupMinTiles && tiles64 * 11 > hbm_ns &&
-               (double)tiles64 * tiles64 * 3.3 > 3500.0 * hbm_ns;
+               (double)tiles64 * tiles64 * 3.3 > 3500.0 * hbm_ns &&
+               (shape.head_dim == 64 || (0.9 * tiles64 - tiles128) * 33 > hbm_ns);
     const int64_t rows_per_item =
         p.groups ? kGroupRowsPerItem : opt.cascade_rows > 0 ? opt.cascade_rows : kTreeAttnRowsPerItem;
     const int64_t ent_per_item = std::max<int64_t>(1, rows_per_item / G);
@@ -391,16 +407,6 @@ ets_status build(const ets_shape& shape, const PlanOptions& opt, const ets_tree&
     const int64_t t_tile = p.groups ? 2000 : 2500, t_mem = t_tile, t_item = 7000;
     const int64_t kResident = p.groups && shape.head_dim == 128 ? 512 : 768;
     auto tile_cost = [&](int64_t) { return t_tile; };
-    // Items of at most 16 query rows apply weights of 16 bits to V as it is, larger ones weights of 11
-    // bits to V in fp16, which ends at 65 504.  Cut into items of 64 query rows, a segment's last leaf queries
-    // are in an item of the former kind where at most 16 rows are left over; larger items leave these
-    // leaf queries out: nobody gets fewer bits by the larger item.  (16 searches of 256 leaves with
-    // 64 query heads, 6 % of the leaf queries' rows: 1 916 us against 1 831 with them inside; one of
-    // them 133 against 130, 512 leaves with 32 query heads 368 against 366.)
-    auto tail_of = [&](const Seg& sg) {
-        const int64_t per64 = std::max<int64_t>(1, kTreeAttnRowsPerItem / G), rest = sg.cnt % per64;
-        return (int32_t)(p.groups && rest * G <= 16 ? rest : 0);
-    };
     // The shared lists.  A segment by itself would cost every leaf query beneath it a partial result,
     // and an item for every ent_per_item of them.  So the leaf queries are grouped, and within a
     // group the segments that the same leaf queries of it read are walked as one list: the path down
@@ -435,7 +441,7 @@ ets_status build(const ets_shape& shape, const PlanOptions& opt, const ets_tree&
             sh.tokens = sg.tokens;
             sh.above = above;
             sh.wide = sg.wide;
-            sh.tail = tail_of(sg);
+            sh.tail = p.groups ? tail_of(sg) : 0;
             shared.push_back(std::move(sh));
         }
         for (int32_t e = 0; e < L; ++e) last_shared[e] = of_seg[seg_of[p.leaf_node[p.ent_order[e]]]];

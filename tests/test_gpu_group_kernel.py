@@ -147,7 +147,7 @@ def test_replayed_from_a_graph():
 
 
 @pytest.mark.parametrize("hq,d,rows,root", [
-    (64, 128, 80, 17000), (64, 128, 208, 11000),  # one list per segment: 80 = 64 + 16, 208 = 3 x 64 + 16
+    (64, 128, 144, 12500), (64, 128, 208, 11000),  # one list per segment: 144 = 128 + 16, 208 = 3 x 64 + 16
     (64, 128, 520, 4160), (32, 128, 516, 4170), (16, 128, 520, 8320), (8, 128, 520, 16321), (64, 64, 584, 4160)])
 def test_v_past_fp16_is_cut_off_for_no_more_rows_than_in_items_of_64(hq, d, rows, root):
     """Items of more than 16 query rows hold V in fp16, others as it is: with V = 99 840 and equal

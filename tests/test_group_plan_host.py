@@ -118,3 +118,18 @@ def test_the_plan_says_which_kernel_takes_it():
                 ctx.set_option(k, v)
             ctx.plan(one, np.zeros(1, np.int64), np.array([n_tok], np.int32), np.zeros(leaves, np.int32), mode)
             assert ctx.item_rows() == rows, (n_tok, leaves, options, mode)
+
+
+@pytest.mark.parametrize("leaves,root,leaf,d,rows", [
+    # (8 query heads per kv head: 56 rows are a tile of 64 and a tile of 128, 72 two and two, because 8 rows stay
+    # apart, 88 two and one, 136 three and two)
+    (7, 60000, 8, 128, 64), (7, 60000, 8, 64, 128), (9, 60000, 8, 128, 64), (9, 60000, 8, 64, 128),
+    (11, 60000, 8, 128, 128), (17, 60000, 8, 128, 128),
+    (17, 60000, 14000, 128, 64), (17, 60000, 14000, 64, 128), (16, 60000, 8000, 128, 128), (16, 8256, 8, 128, 64)])
+def test_rows_that_fill_few_tiles_of_128_stay_with_items_of_64(leaves, root, leaf, d, rows):
+    parent = np.concatenate([[-1], np.zeros(leaves, np.int32)]).astype(np.int32)
+    n_tok = np.concatenate([[root], np.full(leaves, leaf)]).astype(np.int32)
+    off = np.cumsum(n_tok.astype(np.int64)) - n_tok
+    with ets.Context(8, 64, d, ets.ETS_BF16, -1) as ctx:
+        ctx.plan(parent, off, n_tok, np.arange(1, leaves + 1, dtype=np.int32))
+        assert ctx.item_rows() == rows
