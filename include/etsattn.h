@@ -116,8 +116,11 @@ typedef struct {
     int64_t n_cascade_items; /* work items of the shared-node kernel                     */
     int64_t min_pool_tokens; /* pools must hold at least this many rows                  */
     int64_t workspace_bytes; /* device scratch ets_tree_decode_attn needs                */
-    int64_t cascade_tokens;  /* unique tokens read (once) by the shared-node kernel      */
-    int64_t stream_tokens;   /* tokens read by the streaming kernel, repeats included    */
+    int64_t cascade_tokens;  /* unique tokens that a work item reads for several leaf    */
+                             /* queries                                                  */
+    int64_t stream_tokens;   /* tokens that leaf queries read by themselves, repeats     */
+                             /* included; where leaf queries are read in groups, those   */
+                             /* of a shared segment too, if one is alone in its group    */
     int64_t shares_nodes;    /* 1: shared nodes are read once per call (bf16 pools, tree */
                              /* mode); 0: every leaf reads its chain itself              */
     int64_t n_wide_items;    /* work items of the kernel for widely shared segments      */

@@ -356,7 +356,6 @@ ets_status build(const ets_shape& shape, const PlanOptions& opt, const ets_tree&
         // units.  The wide kernel takes 256 rows per item.
         sg.wide = sg.cascade && wide_rows > 0 && sg.cnt * G > wide_rows;
         any_wide = any_wide || sg.wide;
-        if (sg.cascade) st.cascade_tokens += sg.tokens;
         if (sg.wide) st.wide_tokens += sg.tokens;
     }
     // Items of at most 16 query rows apply weights of 16 bits to V as it is, larger ones weights of 11
@@ -442,6 +441,7 @@ ets_status build(const ets_shape& shape, const PlanOptions& opt, const ets_tree&
             sh.above = above;
             sh.wide = sg.wide;
             sh.tail = p.groups ? tail_of(sg) : 0;
+            st.cascade_tokens += sg.tokens;
             shared.push_back(std::move(sh));
         }
         for (int32_t e = 0; e < L; ++e) last_shared[e] = of_seg[seg_of[p.leaf_node[p.ent_order[e]]]];
@@ -475,6 +475,7 @@ ets_status build(const ets_shape& shape, const PlanOptions& opt, const ets_tree&
         const std::vector<int32_t> bounds = group_leaves(costs, (int32_t)ent_per_item);
         auto slots_of = [&](int32_t e) { return last_shared[e] < 0 ? -1 : shared[last_shared[e]].slots; };
         std::vector<int32_t> in_group(segs.size(), -1), members;
+        std::vector<char> counted(segs.size(), 0);  // in cascade_tokens
         for (size_t g = 0; g + 1 < bounds.size(); ++g) {
             const int32_t first = bounds[g], end = bounds[g + 1];
             members.clear();
@@ -522,6 +523,10 @@ ets_status build(const ets_shape& shape, const PlanOptions& opt, const ets_tree&
                         Shared& sh = shared[list];
                         sh.nodes.insert(sh.nodes.end(), sg.nodes.begin(), sg.nodes.end());
                         sh.tokens += sg.tokens;
+                        if (n > 1 && !counted[s]) {
+                            counted[s] = 1;
+                            st.cascade_tokens += sg.tokens;
+                        }
                         sh.sole = sh.sole && sg.cnt == n;
                     }
                 }
@@ -547,6 +552,7 @@ ets_status build(const ets_shape& shape, const PlanOptions& opt, const ets_tree&
     int64_t own_total = 0, work_ns = 0, wide_work_ns = 0;
     int64_t items_est = L;  // one item per leaf query for what it reads itself, plus:
     for (const Shared& sh : shared) {
+        if (sh.n_ent == 1) own_total += sh.tokens;  // (beside a list of others: read by one leaf query)
         if (sh.wide) {
             wide_work_ns += ceil_div(sh.tokens, kTile) * ceil_div(sh.n_ent, ent_per_wide) * t_wide *
                             shape.n_kv_heads;

@@ -31,7 +31,7 @@ def _covers(ctx, t, n_tokens):
 
 @pytest.mark.parametrize("block", range(8))
 def test_group_plans_of_random_forests(block):
-    joined = 0
+    joined = apart = 0
     for seed in range(31000 + 30 * block, 31030 + 30 * block):
         r = np.random.default_rng(seed)
         t = random_tree(seed, n_nodes=int(r.integers(20, 160)), n_leaves=int(r.integers(40, 300)),
@@ -48,7 +48,13 @@ def test_group_plans_of_random_forests(block):
             by64.set_option("cascade_rows", 64)
             _plan(by64, t)
             assert st.unique_tokens == by64.stats().unique_tokens
-            assert st.cascade_tokens == by64.stats().cascade_tokens
+            # a segment whose leaf queries are all in different groups is read by each of them (two at least)
+            by_all = by64.stats()
+            assert st.cascade_tokens <= by_all.cascade_tokens
+            assert st.stream_tokens - by_all.stream_tokens >= 2 * (by_all.cascade_tokens - st.cascade_tokens)
+            if ctx.item_rows() == 64:
+                assert st.stream_tokens == by_all.stream_tokens
+            apart += st.cascade_tokens < by_all.cascade_tokens
             assert by64.item_rows() == 64
             joined += ctx.item_rows() == 128
             rep = ctx.check()
@@ -61,6 +67,7 @@ def test_group_plans_of_random_forests(block):
             assert ctx.check().violations == 0, seed
             _covers(ctx, t, n_tokens)
     assert joined >= 6  # the sweep does reach the plans it is about
+    assert apart > 0 or block not in (2, 4, 6)
 
 
 def test_the_leaf_queries_of_one_search_share_one_list_down_to_their_last_common_node():
@@ -133,3 +140,18 @@ def test_rows_that_fill_few_tiles_of_128_stay_with_items_of_64(leaves, root, lea
     with ets.Context(8, 64, d, ets.ETS_BF16, -1) as ctx:
         ctx.plan(parent, off, n_tok, np.arange(1, leaves + 1, dtype=np.int32))
         assert ctx.item_rows() == rows
+
+
+def test_rows_that_a_leaf_query_reads_by_itself_are_counted_as_such():
+    """33 leaf queries under a root, the last four under a longer branch of it, the others under short
+    ones: with 8 query heads per kv head the last one's rows stay out of the root's larger items, in a
+    list of its own."""
+    root, branch, short, leaf = 8320, 9000, 100, 40
+    parent = np.array([-1, 0, 1, 2, 3, 0] + [1, 2] + [3] * 5 + [4] * 22 + [5] * 4, np.int32)
+    n_tok = np.array([root] + [short] * 4 + [branch] + [leaf] * 33, np.int32)
+    off = np.cumsum(n_tok.astype(np.int64)) - n_tok
+    with ets.Context(8, 64, 128, ets.ETS_BF16, -1) as ctx:
+        st = ctx.plan(parent, off, n_tok, np.arange(6, 39, dtype=np.int32))
+        assert ctx.item_rows() == 128
+        assert st.cascade_tokens == root + branch + 4 * short and st.stream_tokens == 33 * leaf + root
+        assert ctx.check().violations == 0
