@@ -296,7 +296,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(D == 128 ? 
     // exact.  Returns the rows there are.
     auto issue = [&](const Run& sd, int from, auto& raw, auto halves, auto aux_tag) {
         constexpr int HALVES = decltype(halves)::value;
-        // cache policy of the loads: 2 = non-temporal, for rows that no other item reads
+        // cache policy of the loads: 2 = non-temporal, in items of at most 16 query rows, whose rows are mostly
+        // one leaf query's own; rows of larger items are mostly read by further ones
         // (uniform, and said to be so: carried round a loop a step may sit in vector registers)
         const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)sd.tok);
         const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)((uint64_t)sd.tok >> 32));

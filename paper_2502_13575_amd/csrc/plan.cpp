@@ -39,7 +39,6 @@ struct Shared {
     int32_t prefix = 0, n_chunks = 0;
     int32_t above = -1;          // the shared list before it on the way from the root
     bool wide = false;
-    bool sole = true;            // nobody else reads these nodes
     int32_t tail = 0;            // its last leaf queries, which keep an item of their own
     int32_t slots = -1;          // lists with the same number here end at the same partial slot
 };
@@ -527,7 +526,6 @@ ets_status build(const ets_shape& shape, const PlanOptions& opt, const ets_tree&
                             counted[s] = 1;
                             st.cascade_tokens += sg.tokens;
                         }
-                        sh.sole = sh.sole && sg.cnt == n;
                     }
                 }
             }
@@ -645,7 +643,7 @@ ets_status build(const ets_shape& shape, const PlanOptions& opt, const ets_tree&
                 if (slot >= std::numeric_limits<int32_t>::max()) return ETS_ERR_UNSUPPORTED;
                 if (use_mfma) {
                     p.cascade_items.push_back(CascadeItem{c.run_begin, c.run_end, ent_pos[l], 1,
-                                                          shared_slots + c_idx, c.tokens, 1, 0});
+                                                          shared_slots + c_idx, c.tokens, p.groups ? 0 : 1, 0});
                     cascade_cost.push_back(ceil_div(c.tokens, kTile) * t_mem);
                     p.max_cascade_ent = std::max(p.max_cascade_ent, 1);
                 } else {
@@ -667,7 +665,7 @@ ets_status build(const ets_shape& shape, const PlanOptions& opt, const ets_tree&
         for (int32_t c = 0; c < sh.n_chunks; ++c) {
             const Chunk& ch = shared_chunks[i][c];
             const int64_t per_item = sh.wide ? ent_per_wide : ent_per_item;
-            const int32_t sole = sh.sole && sh.n_ent <= per_item ? 1 : 0;
+            const int32_t sole = !p.groups && sh.n_ent <= per_item ? 1 : 0;
             for_items(sh, [&](int64_t e0, int64_t n) {
                 const int32_t ne = (int32_t)n;
                 const CascadeItem it{ch.run_begin, ch.run_end, sh.ent_begin + (int32_t)e0, ne,

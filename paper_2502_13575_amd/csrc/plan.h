@@ -39,7 +39,8 @@ struct CascadeItem {
     int32_t n_ent;
     int32_t slot_off;
     int32_t n_tokens;
-    int32_t sole_reader;  // 1: no other item reads these rows
+    int32_t sole_reader;  // 1: no other item reads these rows (tree_attn_kernel; 0 in the group kernel's plans,
+                          // which chooses its loads by the number of query rows)
     int32_t wave_item;    // set in the unit table.  1: a small item walked by one wavefront; 2 (group kernel):
                           // at most 16 query rows, steps dealt to the four wavefronts; 0: others
 };
