@@ -151,12 +151,13 @@ bool fill_unit_steps(const Plan& p, UnitSlot& u, int wave, const std::vector<cha
     return may_grow;
 }
 
-// The table the matrix-core kernel starts from (see UnitSlot), and the slots whose copies
-// of steps an advance has to refresh.
+// CascadeItem::wave_item of an item that stands in the launch order as `code`.
 int32_t unit_kind(const Plan& p, int32_t code, const CascadeItem& it, int64_t G) {
-    return code < 0 ? 1 : p.groups && it.n_ent * G <= 16 ? 2 : 0;
+    return code < 0 ? 1 : !p.groups ? 0 : it.n_ent * G <= 16 ? 2 : 3;
 }
 
+// The table the matrix-core kernel starts from (see UnitSlot), and the slots whose copies
+// of steps an advance has to refresh.
 void build_units(Plan& p, int64_t G) {
     const size_t n_units = p.wg_map.size();
     p.units.assign(4 * n_units, UnitSlot{});  // zero: n_ent = 0, nothing to do

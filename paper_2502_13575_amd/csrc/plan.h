@@ -41,17 +41,17 @@ struct CascadeItem {
     int32_t n_tokens;
     int32_t sole_reader;  // 1: no other item reads these rows (tree_attn_kernel; 0 in the group kernel's plans,
                           // which chooses its loads by the number of query rows)
-    int32_t wave_item;    // set in the unit table.  1: a small item walked by one wavefront; 2 (group kernel):
-                          // at most 16 query rows, steps dealt to the four wavefronts; 0: others
+    int32_t wave_item;    // set in the unit table.  1: a small item walked by one wavefront; group kernel: 2 = at
+                          // most 16 query rows, steps dealt to the four wavefronts, 3 = more; 0: others
 };
 
 // What a wavefront of the matrix-core kernel starts from, in launch order: wave w of
 // workgroup y reads units[4 y + w]: its work item (n_ent = 0: nothing to do) and the step
 // it fetches first (n = 0: none), so that the first tile can be requested after a single
 // table read.  Item of a workgroup: four copies, `first` = step w / 2 of the item (the wave
-// fetches half w % 2 of it), `second` = step 2 + w / 2 (read by the group kernel only).  Small item
-// of a wave: `first` = its step 0, `second` = its step 1.  Group kernel, at most 16 query rows: steps w and
-// 4 + w.  64 bytes.
+// fetches half w % 2 of it), `second` = step 2 + w / 2 for the group kernel and unused otherwise.
+// Small item of a wave: `first` = its step 0, `second` = its step 1.  Group kernel, at most 16 query rows:
+// steps w and 4 + w.  64 bytes.
 struct UnitSlot {
     CascadeItem item;
     Run first;
@@ -64,7 +64,12 @@ struct UnitSlot {
 __host__ __device__
 #endif
 inline int unit_step_index(const CascadeItem& item, int wave, int j) {
-    return item.wave_item == 1 ? j : item.wave_item == 2 ? 4 * j + wave : 2 * j + (wave >> 1);
+    switch (item.wave_item) {
+        case 1: return j;
+        case 2: return 4 * j + wave;
+        case 3: return 2 * j + (wave >> 1);
+        default: return j == 0 ? wave >> 1 : -1;
+    }
 }
 
 // Where a growing node's next token goes (decode-step advance): one record per copy of
