@@ -170,3 +170,53 @@ def test_v_past_fp16_is_cut_off_for_no_more_rows_than_in_items_of_64(hq, d, rows
     assert bool((want < 99840 * (1 - tol)).any()) and bool((out <= 99840 * (1 + tol)).all())
     assert bool((out >= want * (1 - 2 * tol)).all())
     assert torch.allclose(lse, want_lse, atol=2 * tol, rtol=0)
+
+
+def long_list_tree():
+    """Step lists at the kernel's limit of 256: a root of 256 steps under 21 leaf queries, below it nodes of
+    255 steps under 4 of them, of 258 (two lists) under 6 and of 256 with a short last one under 11; one
+    leaf query of the first two ends a path of 100 and of 300 nodes of 1 to 3 rows that do not touch."""
+    parent, n_tok, leaves = [-1], [8192], []
+    for length, count, chain in ((8160, 4, 100), (8225, 6, 300), (8191, 11, 0)):
+        parent.append(0)
+        n_tok.append(length)
+        top = len(parent) - 1
+        for j in range(count):
+            parent.append(top)
+            n_tok.append(5 + 7 * j)
+            for i in range(chain if j == 1 else 0):
+                parent.append(len(parent) - 1)
+                n_tok.append(1 + i % 3)
+            leaves.append(len(parent) - 1)
+    parent, n_tok = np.array(parent, np.int32), np.array(n_tok, np.int32)
+    off = np.cumsum(n_tok.astype(np.int64) + 1) - n_tok - 1  # a free row behind every node
+    return Tree(parent, off, n_tok, np.array(leaves, np.int32), int(n_tok.sum()) + n_tok.size,
+                np.zeros(parent.size, np.int32))
+
+
+@pytest.mark.parametrize("wave_items", [100000, 0])  # the paths' items: one wave's, a workgroup's
+@pytest.mark.parametrize("fp8", [False, True])
+@pytest.mark.parametrize("d", [128, 64])
+def test_step_lists_of_up_to_256_steps(d, fp8, wave_items):
+    cfg = TreeConfig("group", 8, 64, d, "bf16", 0, 0, 0, 0, 0, None, seed=83)
+    tree = long_list_tree()
+    print("case group long lists", d, fp8, wave_items, flush=True)
+    k, v, q = make_values_fp8_host(cfg, tree, KS, VS) if fp8 else make_values_host(cfg, tree)
+    with make_ctx(cfg, {"cascade_chunk": 100000, "stream_chunk": 100000, "wave_items": wave_items}) as ctx:
+        if fp8:
+            ctx.set_kv_format(ets.ETS_KV_FP8_E4M3, KS, VS)
+        st = ctx.plan(tree.parent, tree.tok_offset, tree.n_tokens, tree.leaf_node)
+        assert ctx.item_rows() == 128 and ctx.check().violations == 0
+        # partials of a leaf query: the root's list, its node's one or two, its own one, the longer path's two
+        assert st.n_partials == 4 * 3 + 6 * 4 + 1 + 11 * 3
+        assert st.n_cascade_items == 2 + 1 + 2 + 1 + 22
+        kd, vd, qd = pool_to_device(k), pool_to_device(v), to_device(q)
+        out, lse, _ = attend(ctx, st, tree, kd, vd, qd)
+        torch.cuda.synchronize()
+    pick = (np.repeat(np.arange(21), 8), np.tile(np.arange(0, 64, 8), 21) + np.repeat(np.arange(21), 8) % 8)
+    if fp8:
+        oo, ol = oracle.tree_decode_attn_fp8kv(tree.parent, tree.tok_offset, tree.n_tokens, tree.leaf_node,
+                                               k, v, KS, VS, q, 8, 64, d, rows=pick)
+    else:
+        oo, ol = oracle_rows(cfg, tree, k, v, q, *pick)
+    compare(out.cpu().numpy()[pick], lse.cpu().numpy()[pick], oo, ol, "bf16", "long lists")

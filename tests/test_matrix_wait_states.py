@@ -170,3 +170,21 @@ def test_wait_states_of_the_built_prefill_kernels(tmp_path):
         assert sum(c[1].startswith("v_mfma") for c in code) >= 32, name
         faults = _check(code)
         assert not faults, (name, len(faults), sorted(faults)[:10])
+
+
+def test_wait_states_of_the_built_group_kernels(tmp_path, monkeypatch):
+    """There the matrix instructions are the compiler's and only the maximum of their results is inline
+    assembly, which brings its own wait.  A result of a 16x16x32 instruction (issued 4 slots after the one
+    before it at the earliest) has to be 8 slots old, which is what the compiler keeps where both sides are
+    its own (the kernel of 64 rows, built alike)."""
+    functions = {n: c for n, c in _functions(_disassembly(tmp_path)).items() if "group_attn_kernel" in n}
+    assert len(functions) == 4
+    for constant, value in (("WRITE_TO_MATRIX", 0), ("MATRIX_TO_USE", 8), ("MATRIX_ISSUE", 4)):
+        monkeypatch.setattr("%s.%s" % (__name__, constant), value)
+    planted = _parse(["v_mfma_f32_16x16x32_bf16 v[0:3], v[4:7], v[8:11], 0", "s_nop 5",
+                      "v_max3_f32 v20, v0, v1, v2", "s_endpgm"])
+    assert _check(planted)
+    for name, code in functions.items():
+        assert sum(c[1].startswith("v_max3_f32") for c in code) >= 3, name
+        faults = [f for f in _check(code) if "v_mfma" not in f]
+        assert not faults, (name, len(faults), sorted(faults)[:10])
