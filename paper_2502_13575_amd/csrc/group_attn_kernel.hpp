@@ -24,10 +24,10 @@
 // which the matrix pipe is busy 1 024: 1.0 us of a compute unit per 128 x 64, against 1.27 for two
 // tiles of 64 rows with three workgroups of the other kernel.  Calls that also stream meet the bandwidth
 // behind L2 first: 512 leaves read 2.0 GB past L2 in 370 us.  Whole calls, the other kernel -> this one,
-// us: 16 searches of 256 leaves with 64 query heads 2 002 -> 1 822, one of them 137 -> 130; 475 leaves
-// with 64 query heads of 64 116 -> 84; 512 leaves with 32 query heads 375 -> 370, over E4M3 pools
-// 289 -> 284 (267 with codes converted straight to fp16).  Not faster: segments walked by resident workgroups in lists made by the planner (no slot
-// idle, but every tile as much longer).
+// us: 16 searches of 256 leaves with 64 query heads 2 061 -> 1 957, one of them 145 -> 132; 512 leaves
+// with 32 query heads 368 -> 369, over E4M3 pools 272 -> 264; drawn trees beyond the planner's lines 0.93 to
+// 1.20, 1.045 in the mean, with head_dim 64 0.91 to 1.51, 1.14.  Not faster: segments walked by resident
+// workgroups in lists made by the planner (no slot idle, but every tile as much longer).
 #pragma once
 
 #include "tree_attn_kernel.hpp"

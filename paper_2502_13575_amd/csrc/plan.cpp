@@ -402,10 +402,10 @@ ets_status build(const ets_shape& shape, const PlanOptions& opt, const ets_tree&
     // start and to store its partial results; kResident workgroups are resident (three per
     // compute unit, two of the group kernel with head_dim 128).  Measured: 2.1-2.7 us per tile, 6.5-8.5
     // us per item; the sum predicts the attention launch of the configurations within 5 %.  Group
-    // kernel: 1.5 us per tile of up to 64 query rows, 2.0-2.7 of more, 5-8 us per item.
-    const int64_t t_tile = p.groups ? 2000 : 2500, t_mem = t_tile, t_item = 7000;
+    // kernel: 1.5 us per tile of up to 64 query rows, 2.0-2.7 of more, 5-8 us per item, of which the
+    // model takes one time for all.
+    const int64_t t_tile = p.groups ? 2000 : 2500, t_item = 7000;
     const int64_t kResident = p.groups && shape.head_dim == 128 ? 512 : 768;
-    auto tile_cost = [&](int64_t) { return t_tile; };
     // The shared lists.  A segment by itself would cost every leaf query beneath it a partial result,
     // and an item for every ent_per_item of them.  So the leaf queries are grouped, and within a
     // group the segments that the same leaf queries of it read are walked as one list: the path down
@@ -416,9 +416,9 @@ ets_status build(const ets_shape& shape, const PlanOptions& opt, const ets_tree&
     // It pays where partial results are a good part of the traffic, and costs L2 hits where they are not:
     // groups walk the same rows at different times, the row groups of one segment at the same time.
     // Joined against by segment, us: 16 searches of 256 leaves with 64 query heads (31 % of the KV bytes in
-    // partial results, 7.1 -> 3.9 of them for a leaf query) 1 850 against 1 970, 366 leaves of short
-    // steps 76 against 95, 414 leaves (18 %) 239 against 252; 512 leaves with 32 query heads (8 %) 376
-    // against 369, over E4M3 pools 291 against 283.
+    // partial results, 7.1 -> 4.1 of them for a leaf query) 1 953 against 1 998, one of them 132 against 142,
+    // 58 drawn trees 0.94 to 1.15, geometric mean 1.02; 512 leaves with 32 query heads (8 %) 376 against
+    // 369, over E4M3 pools 291 against 283.
     int64_t by_segment = L;
     for (const Seg& sg : segs)
         if (sg.cascade) by_segment += sg.cnt;
@@ -558,7 +558,7 @@ ets_status build(const ets_shape& shape, const PlanOptions& opt, const ets_tree&
             continue;
         }
         for_items(sh, [&](int64_t, int64_t n) {
-            work_ns += ceil_div(sh.tokens, kTile) * tile_cost(n * G) * shape.n_kv_heads;
+            work_ns += ceil_div(sh.tokens, kTile) * t_tile * shape.n_kv_heads;
             items_est += 1;
         });
     }
@@ -567,7 +567,7 @@ ets_status build(const ets_shape& shape, const PlanOptions& opt, const ets_tree&
         own_segs(e, reads);
         for (int32_t s : reads) {
             own_total += segs[s].tokens;
-            work_ns += ceil_div(segs[s].tokens, kTile) * t_mem * shape.n_kv_heads;
+            work_ns += ceil_div(segs[s].tokens, kTile) * t_tile * shape.n_kv_heads;
         }
     }
     st.stream_tokens = own_total;
@@ -584,7 +584,7 @@ ets_status build(const ets_shape& shape, const PlanOptions& opt, const ets_tree&
     const int64_t call_ns =
         std::max(hbm_ns, (work_ns + items_est * t_item * shape.n_kv_heads) / kResident) +
         2 * t_item;
-    const int64_t item_budget_ns = std::max<int64_t>(call_ns / 2, 4 * t_mem);
+    const int64_t item_budget_ns = std::max<int64_t>(call_ns / 2, 4 * t_tile);
 
     // wide items: no longer than a quarter of the time their launch is expected to take on
     // 256 compute units, and not so short that start-up dominates
@@ -593,7 +593,7 @@ ets_status build(const ets_shape& shape, const PlanOptions& opt, const ets_tree&
     int64_t scap = opt.stream_chunk;
     if (scap <= 0) {
         if (use_mfma) {
-            scap = item_budget_ns / t_mem * kTile;
+            scap = item_budget_ns / t_tile * kTile;
         } else {
             scap = round_up(ceil_div(own_total * shape.n_kv_heads, 2048), 32);
             scap = std::min<int64_t>(std::max<int64_t>(scap, 64), 2048);
@@ -609,7 +609,7 @@ ets_status build(const ets_shape& shape, const PlanOptions& opt, const ets_tree&
         if (ccap <= 0 && sh.wide)
             ccap = wide_budget_ns / t_wide * kTile;
         else if (ccap <= 0)
-            ccap = item_budget_ns / tile_cost(std::min<int64_t>(ent_per_item, sh.n_ent) * G) * kTile;
+            ccap = item_budget_ns / t_tile * kTile;
         tmp_runs.clear();
         if (!collect_runs(p, sh.nodes, own, tmp_runs)) p.adv_in_place = false;
         if (!cut_runs(p, tmp_runs, sh.tokens, ccap, piece, shared_chunks[i]))
@@ -645,7 +645,7 @@ ets_status build(const ets_shape& shape, const PlanOptions& opt, const ets_tree&
                 if (use_mfma) {
                     p.cascade_items.push_back(CascadeItem{c.run_begin, c.run_end, ent_pos[l], 1,
                                                           shared_slots + c_idx, c.tokens, p.groups ? 0 : 1, 0});
-                    cascade_cost.push_back(ceil_div(c.tokens, kTile) * t_mem);
+                    cascade_cost.push_back(ceil_div(c.tokens, kTile) * t_tile);
                     p.max_cascade_ent = std::max(p.max_cascade_ent, 1);
                 } else {
                     p.stream_items.push_back(
@@ -676,7 +676,7 @@ ets_status build(const ets_shape& shape, const PlanOptions& opt, const ets_tree&
                     wide_cost.push_back(ceil_div(ch.tokens, kTile) * ceil_div((int64_t)ne * G, 32));
                 } else {
                     p.cascade_items.push_back(it);
-                    cascade_cost.push_back(ceil_div(ch.tokens, kTile) * tile_cost((int64_t)ne * G));
+                    cascade_cost.push_back(ceil_div(ch.tokens, kTile) * t_tile);
                     p.max_cascade_ent = std::max(p.max_cascade_ent, ne);
                 }
             });
@@ -715,7 +715,9 @@ ets_status build(const ets_shape& shape, const PlanOptions& opt, const ets_tree&
         std::vector<CascadeItem> sorted;
         sorted.reserve(idx.size());
         // A lone wave needs about 2.5 us per 16-token unit; such an item should not
-        // last longer than a quarter of the time the whole call is expected to take.
+        // last longer than a quarter of the time the whole call is expected to take.  Group kernel: 1.5 us and
+        // six tenths; at most 256 tokens instead, 65 drawn trees, 0.95 to 1.16 times as long, geometric
+        // mean 1.01, 128 tokens 0.97 to 1.29, 1.05, no such items 0.98 to 1.68, 1.18.
         const int64_t wave_cap = std::min<int64_t>(
             opt.wave_items, p.groups ? call_ns * 6 / 10 / 1500 * 16 : hbm_ns / 4 / 2500 * 16);
         auto small = [&](const CascadeItem& it) {
@@ -768,7 +770,7 @@ ets_status build(const ets_shape& shape, const PlanOptions& opt, const ets_tree&
             overrun = std::max(overrun, (double)handed / total - 1 + (double)(ceil_div(x.first, kTile) * t_tile) / call_ns);
         }
         if (opt.interleave && (n_units < (p.groups ? 3 : 5) * kResident || overrun > 0.2)) {
-            auto duration = [&](const std::pair<int64_t, int32_t>& u) {  // in units of half a tile
+            auto duration = [&](const std::pair<int64_t, int32_t>& u) {  // tenths of a microsecond
                 if (u.second >= 0) {
                     const CascadeItem& it = p.cascade_items[(size_t)u.second];
                     const int64_t rows = (int64_t)it.n_ent * G;
@@ -777,8 +779,11 @@ ets_status build(const ets_shape& shape, const PlanOptions& opt, const ets_tree&
                     return rows > 64 ? ceil_div(u.first, kTile) * 21 : rows > 32 ? ceil_div(u.first, kTile) * 16
                            : rows > 16 ? ceil_div(u.first, kTile) * 14 : ceil_div(u.first, 2 * kTile) * 16;
                 }
-                // four small items, the longest first
-                const int64_t n = p.cascade_items[(size_t)(p.n_single + 4 * (-(int64_t)u.second - 1))].n_tokens;
+                // four small items
+                const size_t first = (size_t)(p.n_single + 4 * (-(int64_t)u.second - 1));
+                int64_t n = 0;
+                for (size_t k = first; k < std::min(first + 4, p.cascade_items.size()); ++k)
+                    n = std::max<int64_t>(n, p.cascade_items[k].n_tokens);
                 return p.groups ? ceil_div(n, 32) * 16 : ceil_div(n, 16) * 14;
             };
             std::vector<std::pair<int64_t, int32_t>> all;
