@@ -22,8 +22,10 @@ MFMA_PEAK_TFLOPS = 2500.0       # MI355X dense bf16 / fp16 matrix-core peak, pub
 
 
 # sources whose change invalidates a stored counter reading, per kernel
-TRAFFIC_SOURCES = {"tree_attn": ("group_attn_kernel.hpp", "tree_attn_kernel.hpp", "plan.cpp"),
-                   "tree_attn_e4m3": ("group_attn_kernel.hpp", "tree_attn_kernel.hpp", "plan.cpp"),
+TRAFFIC_SOURCES = {"tree_attn": ("tree_attn_kernel.hpp", "plan.cpp"),
+                   "tree_attn_e4m3": ("tree_attn_kernel.hpp", "plan.cpp"),
+                   "group_attn": ("group_attn_kernel.hpp", "tree_attn_kernel.hpp", "plan.cpp"),
+                   "group_attn_e4m3": ("group_attn_kernel.hpp", "tree_attn_kernel.hpp", "plan.cpp"),
                    "prefill_attn": ("prefill_attn_kernel.hpp", "prefill_plan.cpp")}
 
 
@@ -56,13 +58,20 @@ def record_traffic(workload, kernel, fetch_kib, write_kib, fetch_scale, write_sc
     and `--pmc WRITE_SIZE` readings (KiB per launch) of this script, scaled by what the
     same counters read for the plain 1 GiB copy of --calibrate-copy."""
     path, digest = _traffic_file(kernel, workload)
-    rec = {"kernel": kernel + "_kernel", "workload": workload, "source_sha256_16": digest,
+    name = kernel[:-5] + "_kernel<E4M3>" if kernel.endswith("_e4m3") else kernel + "_kernel"
+    rec = {"kernel": name, "workload": workload, "source_sha256_16": digest,
            "fetch_size_kib_per_launch": fetch_kib, "fetch_scale": fetch_scale,
            "write_size_kib_per_launch": write_kib, "write_scale": write_scale,
            "hbm_bytes_per_launch": int(round((fetch_kib * fetch_scale + write_kib * write_scale) * 1024))}
     with open(path, "w") as f:
         json.dump(rec, f, indent=1)
     print(path, rec)
+
+
+def shared_node_kernel(ctx):
+    """Which kernel reads the shared nodes of the context's plan: group_attn (items of 128 query
+    rows) or tree_attn."""
+    return "group_attn" if ctx.item_rows() > 64 else "tree_attn"
 
 
 def log(*a):
@@ -339,10 +348,11 @@ def main():
     dom = max(kern, key=lambda k: kern[k][0])
     dom_ms = kern[dom][0] / max(prof.calls, 1)
     achieved = kern[dom][1] / (dom_ms * 1e-3) / 1e9 if dom_ms > 0 else 0.0
-    kernel_name = {"cascade": "tree_attn_kernel", "stream": "stream_attn_kernel"}
+    shared_kernel = shared_node_kernel(ctx)
+    kernel_name = {"cascade": shared_kernel + "_kernel", "stream": "stream_attn_kernel"}
     roofline = {"bound": "hbm", "kernel": kernel_name[dom], "achieved": round(achieved, 1),
                 "peak": HBM_PEAK_GBPS, "unit": "GB/s", "frac": round(achieved / HBM_PEAK_GBPS, 4),
-                "traffic": measured_traffic(cfg.name) if dom == "cascade" else None,
+                "traffic": measured_traffic(cfg.name, shared_kernel) if dom == "cascade" else None,
                 "avg_launch_us": round(dom_ms * 1e3, 2),
                 "algorithmic_bytes_per_launch": int(kern[dom][1])}
     # (without streaming items no such kernel is launched; the event pair then only
@@ -409,6 +419,7 @@ def main():
         torch.cuda.synchronize()
         pr8 = ctx.profile_read()
         ctx.set_option("profile", 0)
+        kernel8 = shared_node_kernel(ctx)
         us8 = pr8.cascade_ms / max(pr8.calls, 1) * 1e3
         variants = {"fp8_kv": {
             "format": "E4M3 codes, one scale per pool", "pools_rotated": n8,
@@ -418,14 +429,14 @@ def main():
             "speedup_vs_bf16_pools": round(ms_per_step / cfg.layers * 1e-3 / el8, 3),
             "tree_attn_us": round(us8, 2),
             "merge_us": round(pr8.merge_ms / max(pr8.calls, 1) * 1e3, 2),
-            "roofline": {"bound": "hbm", "kernel": "tree_attn_kernel<E4M3>",
+            "roofline": {"bound": "hbm", "kernel": kernel8 + "_kernel<E4M3>",
                          "achieved": round(st8.unique_kv_bytes / (us8 * 1e-6) / 1e9, 1),
                          "peak": HBM_PEAK_GBPS, "unit": "GB/s",
                          "frac": round(st8.unique_kv_bytes / (us8 * 1e-6) / 1e9 / HBM_PEAK_GBPS, 4),
-                         "traffic": measured_traffic(cfg.name, "tree_attn_e4m3"),
+                         "traffic": measured_traffic(cfg.name, kernel8 + "_e4m3"),
                          "avg_launch_us": round(us8, 2),
                          "algorithmic_bytes_per_launch": int(st8.unique_kv_bytes)}}}
-        log("E4M3 pools: %.1f us per layer (%.2fx the bf16 pools' rate), tree_attn %.1f us = "
+        log("E4M3 pools: %.1f us per layer (%.2fx the bf16 pools' rate), attention %.1f us = "
             "%.0f GB/s of unique KV (%.1f%% of peak)" %
             (el8 * 1e6, variants["fp8_kv"]["speedup_vs_bf16_pools"], us8,
              variants["fp8_kv"]["roofline"]["achieved"],
