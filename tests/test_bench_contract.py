@@ -36,3 +36,16 @@ def test_stored_traffic_records_are_consistent_and_expire_with_the_sources():
         else:
             assert got is None          # counters predate the sources: not reported
     assert bench.measured_traffic("no_such_workload") is None
+
+
+def test_the_roofline_names_the_kernel_of_the_plan():
+    sys.path.insert(0, ROOT)
+    import bench
+    import numpy as np
+    import paper_2502_13575_amd as ets
+    one, zero = np.array([-1], np.int32), np.zeros(1, np.int64)
+    with ets.Context(2, 8, 128, ets.ETS_BF16, -1) as ctx:
+        for rows, name in ((16500, "group_attn"), (100, "tree_attn")):
+            ctx.plan(one, zero, np.array([rows], np.int32), np.zeros(200, np.int32))
+            assert bench.shared_node_kernel(ctx) == name
+            assert name in bench.TRAFFIC_SOURCES and name + "_e4m3" in bench.TRAFFIC_SOURCES
