@@ -258,14 +258,17 @@ ets_status ets_plan_append_rows(const ets_ctx* ctx, int64_t* rows);
  *                    that kernel (bf16 or E4M3 pools, no wide items),
  *                    in which every leaf query has a token, and whose workspace is below
  *                    2 GiB; other plans keep the merge launch (ets_stats.merge_fused
- *                    tells).  Same results bit for bit.  The arrival counters belong to
+ *                    tells).  Work items are those of "cascade_rows" (64 if unset, also
+ *                    where the planner would take 128): same results bit for bit as with
+ *                    these and the merge launch.  The arrival counters belong to
  *                    the context: calls of one context must then not overlap on the
  *                    device.  0 or -1 = separate merge launch, the default: it measures
  *                    faster (the device-scope round trips at the end of the last item
  *                    cost more than the launch they replace)
  *   "interleave"     1 (default) = the launch order is the longest work first in calls of few
- *                    rounds over the chip, and spreads the workgroups that hold small items
- *                    through the others in longer ones; 0 = they follow all the others
+ *                    rounds over the chip and where a long item would end the call, and spreads
+ *                    the workgroups that hold small items through the others in other calls;
+ *                    0 = they follow all the others
  *   "wave_items"     a work item of at most 16 query rows and at most this many
  *                    tokens is walked by a single wavefront, four such items to
  *                    a workgroup (default 512; 0 = every item gets a workgroup)

@@ -19,7 +19,8 @@
 // pinned there: hoisted ahead of them, as the compiler did, it waits for loads a tile too early.
 // 252 registers and 72.5 KB of LDS with head_dim 128: two workgroups per compute unit (three with 64).
 //
-// Bound: the issue of one wave's chain.  A tile takes a wave of 32 query rows 4 200 cycles alone and 4 500
+// Bound of a tile: the issue of one wave's chain.  (Of a call, items of more than 64 rows take half of the
+// slot time or less, e.g. 48 of 117 us on 256 leaves with 64 query heads.)  A tile takes a wave of 32 query rows 4 200 cycles alone and 4 500
 // with a second workgroup beside it (issue of the loads 450, a step of 32 tokens 1 750, barrier 170), of
 // which the matrix pipe is busy 1 024: 1.0 us of a compute unit per 128 x 64, against 1.27 for two
 // tiles of 64 rows with three workgroups of the other kernel.  Calls that also stream meet the bandwidth
