@@ -11,10 +11,13 @@ struct bf16_t {
     uint16_t bits;
 };
 
-// One factor per kv head, passed to kernels by value (kernel argument memory).
+// One factor per kv head, passed to kernels by value (kernel argument memory).  A context may have more kv
+// heads than entries: all entries are alike then (ets_set_kv_head_scales refuses such a context), and the last
+// one stands for the heads beyond.
 constexpr int kMaxScaledHeads = 64;
 struct HeadScales {
     float s[kMaxScaledHeads];
+    __host__ __device__ float of(int h) const { return s[h < kMaxScaledHeads ? h : kMaxScaledHeads - 1]; }
 };
 
 __device__ __forceinline__ float bf16_lo(uint32_t packed) { return __uint_as_float(packed << 16); }

@@ -252,7 +252,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(D == 128 ? 
     const int hw = w & 1;   // which 16-token half of that step
     const int h = blockIdx.x;  // kv head; consecutive workgroups share an item
     // E4M3 pools: the K scale of this kv head is part of the score scale
-    const float scale_log2e = FP8 ? scale_log2e_base * k_scales.s[h] : scale_log2e_base;
+    const float scale_log2e = FP8 ? scale_log2e_base * k_scales.of(h) : scale_log2e_base;
     const int G = 1 << g_shift;
     const int n_q_heads = n_kv_heads << g_shift;
     const float raise_margin = 8.0f / scale_log2e;  // raw-score distance of 2^8 in weight

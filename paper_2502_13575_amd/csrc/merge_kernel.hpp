@@ -237,7 +237,7 @@ __global__ __launch_bounds__(256) void merge_kernel(const int32_t* __restrict__ 
     const int leaf = (int)(blockIdx.x / (unsigned)n_kv_heads) * 4 + wave;
     if (leaf >= n_leaves) return;
     merge_leaf_heads<D, G, UNROLL>(lane, leaf, h, part_base[leaf], part_base[leaf + 1], n_kv_heads * G, ws_o,
-                           ws_ml, 0, out, out_bf16 != 0, lse, v_scales.s[h]);
+                           ws_ml, 0, out, out_bf16 != 0, lse, v_scales.of(h));
 }
 
 }  // namespace ets

@@ -435,7 +435,7 @@ __device__ __forceinline__ void prefill_item(
     const int n = lane & 31;  // in the matrix layouts: query row / run row / d
     const int g = lane >> 5;
     const int h = blockIdx.x;
-    const float scale_log2e = FP8 ? scale_log2e_base * k_scales.s[h] : scale_log2e_base;
+    const float scale_log2e = FP8 ? scale_log2e_base * k_scales.of(h) : scale_log2e_base;
     const int run_begin = it.run_begin, run_end = it.run_end, n_grp = it.n_grp, tok0 = it.tok0;
     const int ent_begin = it.ent_begin, slot_off = it.slot_off;
     const int64_t q_row0 = it.q_row0;
@@ -851,7 +851,7 @@ __device__ __forceinline__ void prefill_item(
         float inv = 1.0f;
         if constexpr (!DECODE) {
             inv = 1.0f / l;
-            if constexpr (FP8) inv *= v_scales.s[h];
+            if constexpr (FP8) inv *= v_scales.of(h);
         }
         if (g == 0 && (r_lane >> g_shift) < n_grp) {
             if constexpr (DECODE)

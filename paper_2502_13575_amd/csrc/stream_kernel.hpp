@@ -219,7 +219,7 @@ __global__ __launch_bounds__(64 * kDirectWaves) void direct_attn_kernel(
             l += ml.y * f;
             acc = fmaf(sm_o[k][e], f, acc);
         }
-        const float r = acc * (n_items == 0 ? 0.f : 1.f / l) * v_scales.s[h];
+        const float r = acc * (n_items == 0 ? 0.f : 1.f / l) * v_scales.of(h);
         if (out_bf16) static_cast<uint16_t*>(out)[row0 * D + e] = f32_to_bf16_rne(r);
         else static_cast<float*>(out)[row0 * D + e] = r;
         if (e % D == 0)

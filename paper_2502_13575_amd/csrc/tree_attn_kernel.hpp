@@ -319,7 +319,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(D == 64 && 
     const int b = lane >> 4;  // token sub-index when loading; MFMA contraction group kg
     const int h = blockIdx.x;  // kv head; consecutive workgroups share an item
     // E4M3 pools: the K scale of this kv head is part of the score scale
-    const float scale_log2e = FP8 ? scale_log2e_base * k_scales.s[h] : scale_log2e_base;
+    const float scale_log2e = FP8 ? scale_log2e_base * k_scales.of(h) : scale_log2e_base;
     // A workgroup takes one item, or four small items, one per wave, which then works alone
     // (no barrier below this point on that path); the planner's launch order says which.
     // One table read (uniform per wave: scalar loads) brings the item and the step this wave
@@ -524,7 +524,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(D == 64 && 
             uint64_t todo = __ballot(arriver && seen + 1 == np);
             if (todo != 0) {
                 __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
-                const float out_scale = tail.v_scales.s[h];
+                const float out_scale = tail.v_scales.of(h);
                 while (todo != 0) {
                     const int src = __builtin_ctzll(todo);
                     todo &= todo - 1;
