@@ -182,7 +182,8 @@ __global__ __launch_bounds__(64 * kDirectWaves) void direct_attn_kernel(
     const T* __restrict__ q, const Run* __restrict__ runs, const StreamItem* __restrict__ items,
     const int32_t* __restrict__ part_base, int n_kv_heads, float scale_log2e, HeadScales v_scales,
     void* __restrict__ out, int out_bf16, float* __restrict__ lse) {
-    __shared__ float sm_o[kDirectWaves][G * D];
+    __shared__ __align__(16) float sm_o[kDirectWaves][G * D];
+    static_assert(__alignof__(sm_o) >= alignof(float4) && D % 4 == 0, "rows are written 16 bytes at a time");
     __shared__ float2 sm_ml[kDirectWaves][G];
     const int h = blockIdx.x % n_kv_heads;
     const int leaf = blockIdx.x / n_kv_heads;
