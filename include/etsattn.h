@@ -67,7 +67,18 @@ typedef enum { ETS_F32 = 0, ETS_BF16 = 1 } ets_dtype;
  * itself (shared rows come out of the caches, not out of the plan), at the cost of the
  * flat baseline.  ets_stats.shares_nodes says which of the two a plan is, and with the
  * option "require_sharing" ets_plan refuses (ETS_ERR_UNSUPPORTED) a tree-mode plan that
- * would not share.  The wide kernel and step prefill are built for head_dim 128 only. */
+ * would not share.  The wide kernel and step prefill are built for head_dim 128 only.
+ *
+ * Small calls over fp32 pools (paths of up to 512 rows, up to 50 million multiply-adds per
+ * contraction, "stream_chunk" unset) are one launch: a workgroup merges a leaf query's
+ * partial results in its own memory and writes the result.  For such a plan n_partials,
+ * workspace_bytes and the report of ets_plan_check count the partial results as if they
+ * went through the workspace, and ets_tree_decode_attn asks for it by the same rule as for
+ * any other plan, though nothing is written there; there is no merge launch, while
+ * merge_fused (which is about the shared-node kernel) is 0; and ets_profile gives the whole
+ * call as stream_ms.  The paths are cut finer than for two launches, into items of 16 or 32
+ * rows instead of 64 or more, so workspace_bytes is up to four times as large, but never
+ * above ETS_STATIC_SCRATCH_BYTES. */
 typedef struct {
     int32_t n_kv_heads;
     int32_t n_q_heads;
@@ -112,10 +123,12 @@ typedef struct {
     int64_t flat_kv_bytes;
     int64_t n_segments;      /* chains of live nodes with identical leaf sets            */
     int64_t n_partials;      /* partial results per query head, summed over the leaves   */
+                             /* (one-launch plans: merged in the workgroup, see above)   */
     int64_t n_stream_items;  /* work items of the per-leaf streaming kernel              */
     int64_t n_cascade_items; /* work items of the shared-node kernel                     */
     int64_t min_pool_tokens; /* pools must hold at least this many rows                  */
-    int64_t workspace_bytes; /* device scratch ets_tree_decode_attn needs                */
+    int64_t workspace_bytes; /* device scratch ets_tree_decode_attn asks for: room for   */
+                             /* n_partials results of every query head                   */
     int64_t cascade_tokens;  /* unique tokens that a work item reads for several leaf    */
                              /* queries                                                  */
     int64_t stream_tokens;   /* tokens that leaf queries read by themselves, repeats     */
@@ -126,7 +139,8 @@ typedef struct {
     int64_t n_wide_items;    /* work items of the kernel for widely shared segments      */
     int64_t wide_tokens;     /* unique tokens of those segments (part of cascade_tokens) */
     int64_t merge_fused;     /* 1: the shared-node kernel merges the partials itself (no  */
-                             /* merge launch); see the "fuse_merge" option                */
+                             /* merge launch); see the "fuse_merge" option.  One-launch   */
+                             /* plans of fp32 pools have no merge launch either, with 0   */
 } ets_stats;
 
 typedef enum {
@@ -190,7 +204,8 @@ typedef struct {
     int64_t max_entry_index;      /* highest entry index any wavefront loads                   */
     int64_t max_entry_overreach;  /* entries loaded past an item's own last entry, at most     */
     int64_t max_pool_row;         /* highest pool row any step names                           */
-    int64_t max_partial_row;      /* highest (partial, head) row written                       */
+    int64_t max_partial_row;      /* highest (partial, head) row written, or in one-launch     */
+                                  /* plans merged in the workgroup: inside the workspace       */
     int64_t violations;
 } ets_plan_check_report;
 ets_status ets_plan_check(const ets_ctx* ctx, ets_plan_check_report* report);
@@ -264,7 +279,8 @@ ets_status ets_plan_append_rows(const ets_ctx* ctx, int64_t* rows);
  *                    the context: calls of one context must then not overlap on the
  *                    device.  0 or -1 = separate merge launch, the default: it measures
  *                    faster (the device-scope round trips at the end of the last item
- *                    cost more than the launch they replace)
+ *                    cost more than the launch they replace).  Small calls over fp32 pools
+ *                    merge without counters and have no such launch whatever the option says
  *   "interleave"     1 (default) = the launch order is the longest work first in calls of few
  *                    rounds over the chip and where a long item would end the call, and spreads
  *                    the workgroups that hold small items through the others in other calls;
@@ -365,7 +381,7 @@ ets_status ets_tree_decode_attn_static(ets_ctx* ctx, const void* k_pool, const v
  * returns the summed kernel times since the previous read and clears them. */
 typedef struct {
     int64_t calls;
-    double stream_ms;  /* per-leaf streaming kernel                  */
+    double stream_ms;  /* per-leaf kernel (one-launch plans: the whole call) */
     double cascade_ms; /* shared-node kernel                         */
     double merge_ms;   /* log-sum-exp merge kernel                   */
     double wide_ms;    /* kernel for widely shared segments          */
