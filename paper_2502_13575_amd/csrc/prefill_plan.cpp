@@ -224,7 +224,8 @@ ets_status build(const ets_shape& shape, const ets_tree& tree, PrefillPlan& p, i
     // the time with: up to four rounds 0.97 to 1.00 where less than 7 % of the runs are saved, 1.00 to 1.12
     // where more are; of more rounds 4 % save 1 to 2 % of the time, 6 % save 3.
     const int64_t workgroups = (small ? n_small : n_large);
-    if (saved > 0 && saved * (workgroups <= 4 * kComputeUnits ? 15 : 40) < walked + saved)
+    // (Joins that save no run are such a call too.)
+    if (p.joins && saved * (workgroups <= 4 * kComputeUnits ? 15 : 40) < walked + saved)
         return build(shape, tree, p, kv_elem_bytes, false);
     // items in the depth-first leaf order; item_begin indexes them per leaf query
     std::vector<int32_t> n_items_of(L, 0);

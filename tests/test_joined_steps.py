@@ -3,6 +3,9 @@ pieces behind and in front of one another in the pool, steps that stay short, pi
 far apart to be joined.  On the host the step counts and the rows seen; on the GPU every result
 against the oracle, with pools whose rows outside the tree hold NaN (a row past the end of a joined
 step has to read as zero, not as its neighbour)."""
+import os
+import subprocess
+
 import numpy as np
 import pytest
 import torch
@@ -72,6 +75,54 @@ def test_pieces_too_far_apart_are_not_joined():
                 st = ctx.plan_prefill(np.array([-1, 0, 1], np.int32), np.array(off, np.int64),
                                       np.array([n, 45, 8], np.int32), np.array([2], np.int32))
                 assert st.n_runs == ROOT // 32 + runs + 1 and ctx.check().violations == 0
+
+
+PLAN_MAIN = r"""
+#include <cstdio>
+#include <cstdlib>
+#include <vector>
+#include "prefill_plan.h"
+// A chain of nodes of these many rows with five unused rows between any two, and one leaf step of 40 rows
+// below it; prints whether the plan's runs may be joined, how many are, and how many runs there are.
+int main(int argc, char** argv) {
+    std::vector<int32_t> parent, rows;
+    std::vector<int64_t> off;
+    int64_t at = 0;
+    for (int i = 1; i <= argc; ++i) {
+        parent.push_back(i - 2);
+        rows.push_back(i < argc ? std::atoi(argv[i]) : 40);
+        off.push_back(at);
+        at += rows.back() + 5;
+    }
+    const int32_t leaf = argc - 1;
+    const ets_shape shape{1, 4, 128, ETS_BF16, 0.f};
+    const ets_tree tree{argc, parent.data(), off.data(), rows.data(), 1, &leaf};
+    ets::PrefillPlan p;
+    if (ets::build_prefill_plan(shape, tree, p, 2) != ETS_OK) return 1;
+    int joined = 0;
+    for (const ets::Run& r : p.runs) joined += r.join != 0;
+    std::printf("%d %d %d\n", (int)p.joins, joined, (int)p.runs.size());
+    return 0;
+}
+"""
+
+
+def test_prefill_joins_are_kept_where_they_save_runs(tmp_path):
+    """The kernel's loop that takes joined runs is the longer one: a plan in which no run is saved, or too few,
+    has no joined run and goes to the other loop."""
+    root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+    csrc = os.path.join(root, "paper_2502_13575_amd", "csrc")
+    main, exe = tmp_path / "main.cpp", str(tmp_path / "plan")
+    main.write_text(PLAN_MAIN)
+    subprocess.run(["g++", "-std=c++17", "-O1", "-I" + csrc, "-I" + os.path.join(root, "include"), str(main),
+                    os.path.join(csrc, "prefill_plan.cpp"), os.path.join(csrc, "plan.cpp"), "-o", exe], check=True)
+    for rows, want in [([192, 40, 63], "0 0 12"),           # joined 32, 8 + 24, 32, 7: four runs either way
+                       ([192, 20, 20], "0 0 10"),           # joined 20 + 12, 8: two either way
+                       ([192, 45, 45, 45], "1 2 13"),       # 32, 13 + 19, 26 + 6, 32, 7 instead of six
+                       ([192] + [60] * 32, "0 0 72"),       # every second run 28 + 4: none saved in 64
+                       ([192] + [48] * 8, "1 4 20")]:       # 32, 16 + 16, 32: 12 instead of 16
+        out = subprocess.run([exe] + [str(x) for x in rows], check=True, capture_output=True, text=True).stdout
+        assert out.strip() == want, rows
 
 
 def _poisoned(x, tree):
