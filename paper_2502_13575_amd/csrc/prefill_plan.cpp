@@ -64,18 +64,14 @@ struct Schedule {
     }
 };
 
-// `join`: whether runs may be joined of two pieces.
-ets_status build(const ets_shape& shape, const ets_tree& tree, PrefillPlan& p, int64_t kv_elem_bytes,
-                 bool join) {
+ets_status build(const ets_shape& shape, const ets_tree& tree, PrefillPlan& p, int64_t kv_elem_bytes) {
     const int32_t N = tree.n_nodes, L = tree.n_leaves;
     const int32_t G = shape.n_q_heads / shape.n_kv_heads;
     p.parent.assign(tree.parent, tree.parent + N);
     p.tok_offset.assign(tree.tok_offset, tree.tok_offset + N);
     p.n_tokens.assign(tree.n_tokens, tree.n_tokens + N);
     p.leaf_node.assign(tree.leaf_node, tree.leaf_node + L);
-    p.runs.clear();
     p.items.clear();
-    p.joins = false;
     p.q_ptr.assign((size_t)L + 1, 0);
     p.item_begin.assign((size_t)L, 0);
     for (int32_t l = 0; l < L; ++l) p.q_ptr[l + 1] = p.q_ptr[l] + p.n_tokens[p.leaf_node[l]];
@@ -121,49 +117,58 @@ ets_status build(const ets_shape& shape, const ets_tree& tree, PrefillPlan& p, i
     std::vector<int32_t> run_begin_of(N, -1), anc_runs_of(N, 0);  // per distinct leaf node
     std::vector<int32_t> plain_runs_of(N, 0);  // ancestors' runs if none were joined
     std::vector<int64_t> anc_tokens_of(N, 0);
-    for (int32_t oi = 0; oi < L; ++oi) {
-        const int32_t v = p.leaf_node[order[oi]];
-        const int32_t len = p.n_tokens[v];
-        if (run_begin_of[v] < 0 && len > 0) {
-            chain.clear();
-            for (int32_t x = v; x >= 0; x = p.parent[x]) chain.push_back(x);
-            std::reverse(chain.begin(), chain.end());
-            run_begin_of[v] = (int32_t)p.runs.size();
-            // ancestors: contiguous rows merge, then steps of 32.  A step costs the same however many rows it
-            // has, and every node of some hundred tokens used to end in a half-empty one.
-            int64_t cur_tok = 0, cur_n = 0, anc_tokens = 0;
-            auto flush = [&]() {
-                int64_t off = 0;
-                plain_runs_of[v] += (int32_t)((cur_n + kStepRows - 1) / kStepRows);
-                if (join && cur_n > 0 && (int32_t)p.runs.size() - run_begin_of[v] > kPrefillFirstRuns)
-                    p.joins = (off = join_rows(p.runs.back(), cur_tok, cur_n)) > 0 || p.joins;
-                for (; off < cur_n; off += kStepRows)
-                    p.runs.push_back(Run{cur_tok + off, (int32_t)std::min<int64_t>(kStepRows, cur_n - off), 0});
-                cur_n = 0;
-            };
-            for (size_t c = 0; c + 1 < chain.size(); ++c) {
-                const int32_t n = chain[c];
-                live[n] = 1;
-                if (p.n_tokens[n] <= 0) continue;
-                anc_tokens += p.n_tokens[n];
-                if (cur_n > 0 && cur_tok + cur_n == p.tok_offset[n]) {
-                    cur_n += p.n_tokens[n];
-                } else {
-                    flush();
-                    cur_tok = p.tok_offset[n];
-                    cur_n = p.n_tokens[n];
+    // `join`: whether runs may be joined of two pieces
+    auto make_runs = [&](bool join) {
+        p.runs.clear();
+        p.joins = false;
+        std::fill(run_begin_of.begin(), run_begin_of.end(), -1);
+        std::fill(plain_runs_of.begin(), plain_runs_of.end(), 0);
+        for (int32_t oi = 0; oi < L; ++oi) {
+            const int32_t v = p.leaf_node[order[oi]];
+            const int32_t len = p.n_tokens[v];
+            if (run_begin_of[v] < 0 && len > 0) {
+                chain.clear();
+                for (int32_t x = v; x >= 0; x = p.parent[x]) chain.push_back(x);
+                std::reverse(chain.begin(), chain.end());
+                run_begin_of[v] = (int32_t)p.runs.size();
+                // ancestors: contiguous rows merge, then steps of 32.  A step costs the same however many rows it
+                // has, and every node of some hundred tokens used to end in a half-empty one.
+                int64_t cur_tok = 0, cur_n = 0, anc_tokens = 0;
+                auto flush = [&]() {
+                    int64_t off = 0;
+                    plain_runs_of[v] += (int32_t)((cur_n + kStepRows - 1) / kStepRows);
+                    if (join && cur_n > 0 && (int32_t)p.runs.size() - run_begin_of[v] > kPrefillFirstRuns)
+                        p.joins = (off = join_rows(p.runs.back(), cur_tok, cur_n)) > 0 || p.joins;
+                    for (; off < cur_n; off += kStepRows)
+                        p.runs.push_back(Run{cur_tok + off, (int32_t)std::min<int64_t>(kStepRows, cur_n - off), 0});
+                    cur_n = 0;
+                };
+                for (size_t c = 0; c + 1 < chain.size(); ++c) {
+                    const int32_t n = chain[c];
+                    live[n] = 1;
+                    if (p.n_tokens[n] <= 0) continue;
+                    anc_tokens += p.n_tokens[n];
+                    if (cur_n > 0 && cur_tok + cur_n == p.tok_offset[n]) {
+                        cur_n += p.n_tokens[n];
+                    } else {
+                        flush();
+                        cur_tok = p.tok_offset[n];
+                        cur_n = p.n_tokens[n];
+                    }
                 }
+                flush();
+                live[v] = 1;
+                anc_runs_of[v] = (int32_t)p.runs.size() - run_begin_of[v];
+                anc_tokens_of[v] = anc_tokens;
+                for (int32_t off = 0; off < len; off += 32)
+                    p.runs.push_back(Run{p.tok_offset[v] + off, std::min(32, len - off), 0});
+                if (p.runs.size() > (size_t)std::numeric_limits<int32_t>::max() - 64)
+                    return false;
             }
-            flush();
-            live[v] = 1;
-            anc_runs_of[v] = (int32_t)p.runs.size() - run_begin_of[v];
-            anc_tokens_of[v] = anc_tokens;
-            for (int32_t off = 0; off < len; off += 32)
-                p.runs.push_back(Run{p.tok_offset[v] + off, std::min(32, len - off), 0});
-            if (p.runs.size() > (size_t)std::numeric_limits<int32_t>::max() - 64)
-                return ETS_ERR_UNSUPPORTED;
         }
-    }
+        return true;
+    };
+    if (!make_runs(true)) return ETS_ERR_UNSUPPORTED;
 
     int64_t n_large = 0, n_small = 0;
     for (int32_t l = 0; l < L; ++l) {
@@ -173,29 +178,51 @@ ets_status build(const ets_shape& shape, const ets_tree& tree, PrefillPlan& p, i
     }
     n_large *= shape.n_kv_heads;
     n_small *= shape.n_kv_heads;
-    bool small = rounds_cost(n_small, kPrefillRunSmall) < rounds_cost(n_large, kPrefillRunLarge);
-    if (small && n_small > n_large && n_small > kComputeUnits && n_small <= kScheduledWorkgroups) {
-        auto ends = [&](int32_t rows) {
-            Schedule schedule;
-            for (int32_t oi = 0; oi < L; ++oi) {
-                const int32_t v = p.leaf_node[order[oi]], len = p.n_tokens[v];
-                for (int32_t t0 = 0; t0 < len; t0 += rows / G) {
-                    const int32_t n_tok = std::min(rows / G, len - t0);
-                    const int64_t runs = anc_runs_of[v] + (t0 + n_tok - 1) / 32 + 1;
-                    const int64_t cycles =
-                        runs * (n_tok * G <= kPrefillRowsSmall ? kPrefillRunSmall : kPrefillRunLarge);
-                    for (int32_t h = 0; h < shape.n_kv_heads; ++h) schedule.add(cycles);
+    auto rows_per_item = [&]() {
+        bool small = rounds_cost(n_small, kPrefillRunSmall) < rounds_cost(n_large, kPrefillRunLarge);
+        if (small && n_small > n_large && n_small > kComputeUnits && n_small <= kScheduledWorkgroups) {
+            auto ends = [&](int32_t rows) {
+                Schedule schedule;
+                for (int32_t oi = 0; oi < L; ++oi) {
+                    const int32_t v = p.leaf_node[order[oi]], len = p.n_tokens[v];
+                    for (int32_t t0 = 0; t0 < len; t0 += rows / G) {
+                        const int32_t n_tok = std::min(rows / G, len - t0);
+                        const int64_t runs = anc_runs_of[v] + (t0 + n_tok - 1) / 32 + 1;
+                        const int64_t cycles =
+                            runs * (n_tok * G <= kPrefillRowsSmall ? kPrefillRunSmall : kPrefillRunLarge);
+                        for (int32_t h = 0; h < shape.n_kv_heads; ++h) schedule.add(cycles);
+                    }
                 }
+                return schedule.end;
+            };
+            small = ends(kPrefillRowsSmall) * 100 < ends(kPrefillRowsPerItem) * 105;
+        }
+        return small ? kPrefillRowsSmall : kPrefillRowsPerItem;
+    };
+    int32_t rows = rows_per_item();
+    // The loop that takes joined runs is 1 to 3 % longer, and a launch of few rounds, where a workgroup waits for
+    // its loads more than for anything else, gains less by fewer rows.  14 drawn calls, the time without over
+    // the time with: up to four rounds 0.97 to 1.00 where less than 7 % of the runs are saved, 1.00 to 1.12
+    // where more are; of more rounds 4 % save 1 to 2 % of the time, 6 % save 3.
+    // (Joins that save no run are such a call too.)
+    if (p.joins) {
+        int64_t plain = 0, saved = 0;  // runs walked by all items
+        for (int32_t l = 0; l < L; ++l) {
+            const int32_t v = p.leaf_node[l], len = p.n_tokens[v];
+            for (int32_t t0 = 0; t0 < len; t0 += rows / G) {
+                plain += plain_runs_of[v] + (std::min(t0 + rows / G, len) - 1) / 32 + 1;
+                saved += plain_runs_of[v] - anc_runs_of[v];
             }
-            return schedule.end;
-        };
-        small = ends(kPrefillRowsSmall) * 100 < ends(kPrefillRowsPerItem) * 105;
+        }
+        const int64_t workgroups = rows == kPrefillRowsSmall ? n_small : n_large;
+        if (saved * (workgroups <= 4 * kComputeUnits ? 15 : 40) < plain) {
+            if (!make_runs(false)) return ETS_ERR_UNSUPPORTED;
+            rows = rows_per_item();
+        }
     }
-    const int32_t rows = small ? kPrefillRowsSmall : kPrefillRowsPerItem;
     const int32_t tq = rows / G;  // query tokens per item
     st.rows_per_item = rows;
 
-    int64_t walked = 0, saved = 0;  // runs
     std::vector<std::vector<PrefillItem>> per_leaf((size_t)L);
     for (int32_t oi = 0; oi < L; ++oi) {
         const int32_t l = order[oi];
@@ -210,8 +237,6 @@ ets_status build(const ets_shape& shape, const ets_tree& tree, PrefillPlan& p, i
             it.q_row0 = p.q_ptr[l] + t0;
             it.leaf = l;
             it.n_anc = anc_runs_of[v];
-            walked += it.run_end - it.run_begin;
-            saved += plain_runs_of[v] - anc_runs_of[v];
             per_leaf[l].push_back(it);
             // what the block's queries see: ancestors in full, own rows causally
             const int64_t a = t0, b = t0 + it.n_tok;  // own rows visible: a + 1 .. b
@@ -219,14 +244,6 @@ ets_status build(const ets_shape& shape, const ets_tree& tree, PrefillPlan& p, i
             for (int32_t r = it.run_begin; r < it.run_end; ++r) st.streamed_tokens += p.runs[r].n;
         }
     }
-    // The loop that takes joined runs is 1 to 3 % longer, and a launch of few rounds, where a workgroup waits for
-    // its loads more than for anything else, gains less by fewer rows.  14 drawn calls, the time without over
-    // the time with: up to four rounds 0.97 to 1.00 where less than 7 % of the runs are saved, 1.00 to 1.12
-    // where more are; of more rounds 4 % save 1 to 2 % of the time, 6 % save 3.
-    const int64_t workgroups = (small ? n_small : n_large);
-    // (Joins that save no run are such a call too.)
-    if (p.joins && saved * (workgroups <= 4 * kComputeUnits ? 15 : 40) < walked + saved)
-        return build(shape, tree, p, kv_elem_bytes, false);
     // items in the depth-first leaf order; item_begin indexes them per leaf query
     std::vector<int32_t> n_items_of(L, 0);
     for (int32_t oi = 0; oi < L; ++oi) {
@@ -291,7 +308,7 @@ ets_status build_prefill_plan(const ets_shape& shape, const ets_tree& tree, Pref
     const ets_status s = check(tree);
     if (s != ETS_OK) return s;
     try {
-        return build(shape, tree, plan, kv_elem_bytes, true);
+        return build(shape, tree, plan, kv_elem_bytes);
     } catch (const std::bad_alloc&) {
         plan.valid = false;
         return ETS_ERR_NOMEM;
