@@ -490,16 +490,20 @@ __device__ __forceinline__ void prefill_item(
     // row is on one side of the join: changed for its loads and put back for the next run, out of the way.
     // (Chosen at every load, a compare and a select each, they made every run 5 % longer.  In the
     // prologue even the way round that code shows, 27.4 us against 27.1 for 16 steps of 64 tokens: the
-    // planner keeps joined runs out of it.)
+    // planner keeps joined runs out of it.  Without JOINS the compiler forms them as it likes and no join word is
+    // carried: with both held there too, 16 steps of 64 tokens took 28.27 us instead of 28.05.)
+    auto plain_row = [&](int i) {
+        return i < 4 ? k_lane_off + (uint32_t)(4 * i) * stride_b : v_lane_off + (uint32_t)(i - 4) * stride_b;
+    };
     uint32_t row_off[8];
     auto plain_rows = [&]() {
 #pragma unroll
         for (int i = 0; i < 8; ++i) {
-            row_off[i] = i < 4 ? k_lane_off + (uint32_t)(4 * i) * stride_b : v_lane_off + (uint32_t)(i - 4) * stride_b;
+            row_off[i] = plain_row(i);
             asm volatile("" : "+v"(row_off[i]));
         }
     };
-    plain_rows();
+    if constexpr (JOINS) plain_rows();
     int joins = 0;  // whether row_off is of a joined run
     auto joined_rows = [&](Run& sd) {  // returns the rows that its loads may reach
         joins = __builtin_amdgcn_readfirstlane(sd.join);
@@ -520,8 +524,9 @@ __device__ __forceinline__ void prefill_item(
         return span.size;
     };
     auto issue_load = [&](const RunRsrc& rs, RawTile& raw, int i) {  // i = 0..7
-        if (i < 4) raw.k[i] = load_piece(rs.k, row_off[i]);
-        else raw.v[i - 4] = load_piece(rs.v, row_off[i]);
+        const uint32_t off = JOINS ? row_off[i] : plain_row(i);
+        if (i < 4) raw.k[i] = load_piece(rs.k, off);
+        else raw.v[i - 4] = load_piece(rs.v, off);
     };
     auto issue_loads = [&](const Run& sd, RawTile& raw) {  // a run of consecutive rows
         const RunRsrc rs = rsrc_of(sd, sd.n);
@@ -569,8 +574,9 @@ __device__ __forceinline__ void prefill_item(
         uint32_t lo = __builtin_amdgcn_readfirstlane(d[0]);
         uint32_t hi = __builtin_amdgcn_readfirstlane(d[1]);
         uint32_t rows = __builtin_amdgcn_readfirstlane(d[2]);
-        uint32_t join = __builtin_amdgcn_readfirstlane(d[3]);
-        asm volatile("" : "+s"(lo), "+s"(hi), "+s"(rows), "+s"(join));  // carried round the loop in scalar registers
+        uint32_t join = JOINS ? __builtin_amdgcn_readfirstlane(d[3]) : 0u;
+        asm volatile("" : "+s"(lo), "+s"(hi), "+s"(rows));  // carried round the loop in scalar registers
+        if constexpr (JOINS) asm volatile("" : "+s"(join));
         return Run{(int64_t)(((uint64_t)hi << 32) | lo), (int32_t)rows, (int32_t)join};
     };
     auto run_at = [&](int idx) { return idx < n_runs ? my_runs[idx] : Run{0, 0, 0}; };
@@ -760,7 +766,16 @@ __device__ __forceinline__ void prefill_item(
             };
             auto descs = [&](int i) ETS_INLINE {
                 if (i == 4) d_e = rows_at(2 * tile + 3);
-                if (i == 5) d_run = *desc_at(2 * tile + 8 + sw);
+                // (without JOINS its first twelve bytes, in two reads)
+                if (i == 5) {
+                    if constexpr (JOINS) {
+                        d_run = *desc_at(2 * tile + 8 + sw);
+                    } else {
+                        const u32x2_t tok = *reinterpret_cast<const u32x2_t*>(desc_at(2 * tile + 8 + sw));
+                        d_run = u32x4_t{tok[0], tok[1], 0u, 0u};
+                    }
+                }
+                if (!JOINS && i == 6) d_run[2] = rows_at(2 * tile + 8 + sw);
                 if (i == 13) e_next = extent_of(d_e, 2 * tile + 3);
                 if (i == 14) load_next = run_of(d_run);
             };
