@@ -14,7 +14,8 @@ import oracle
 import paper_2502_13575_amd as ets
 from workload import Tree, TreeConfig, make_prefill_queries_host, make_values_fp8_host, make_values_host
 
-from _gpu_util import compare, make_ctx, oracle_prefill, pool_to_device, to_device
+from _gpu_util import (compare, gpu_attn, gpu_prefill, make_ctx, oracle_full, oracle_prefill, pool_to_device,
+                       to_device)
 
 KS, VS = 0.0123, 0.0217
 OWN = 40
@@ -65,6 +66,30 @@ def test_prefill_steps_and_rows(lengths, order, steps):
             want = oracle.visible_rows(t.parent, t.tok_offset, t.n_tokens, int(t.leaf_node[0]), tok + 1)
             assert np.array_equal(ctx.prefill_cover(0, tok), want)
         assert ctx.check().violations == 0
+
+
+LIMIT = 1 << 22  # rows between the pieces, at most
+
+
+@pytest.mark.parametrize("back", [False, True])
+@pytest.mark.parametrize("beyond", [0, 1])
+def test_the_largest_gap(back, beyond):
+    """205 rows (the seventh step has 13), then 45: joined 13 + 19 up to the limit, both ways, not beyond."""
+    t = _far_tree(back, beyond)
+    with ets.Context(1, 4, 128, ets.ETS_BF16, -1) as ctx:
+        st = ctx.plan_prefill(t.parent, t.tok_offset, t.n_tokens, t.leaf_node)
+        assert st.n_runs == 10 + beyond
+        ctx.plan(t.parent, t.tok_offset, t.n_tokens, t.leaf_node, ets.ETS_PLAN_FLAT)
+        assert ctx.check().violations == 0
+        want = oracle.visible_rows(t.parent, t.tok_offset, t.n_tokens, 2, OWN)
+        assert np.array_equal(ctx.prefill_cover(0, OWN - 1), want) and np.array_equal(ctx.leaf_cover(0)[0], want)
+
+
+def _far_tree(back, beyond=0):
+    first = (LIMIT + beyond - 205) if back else 0
+    second = 0 if back else 205 + LIMIT + beyond
+    return Tree(np.array([-1, 0, 1], np.int32), np.array([first, second, LIMIT + 400], np.int64),
+                np.array([205, 45, OWN], np.int32), np.array([2], np.int32), LIMIT + 400 + OWN)
 
 
 def test_pieces_too_far_apart_are_not_joined():
@@ -220,7 +245,7 @@ def _decode(cfg, tree, kv, options, mode):
 @pytest.mark.parametrize("kv", ["bf16", "e4m3"])
 @pytest.mark.parametrize("d", [64, 128])
 @pytest.mark.parametrize("leaves,mode,options", [
-    (1, "tree", {}),                       # small items, one wave each
+    (1, "tree", {}),                       # one leaf query (small items, one wave each: test_growth_of_joined_tails)
     (3, "flat", {"wave_items": 0}),        # at most 16 query rows, four waves
     (9, "tree", {}), (40, "tree", {"cascade_chunk": 96}),  # row-parallel
     (9, "tree", {"fuse_merge": 1})])
@@ -230,3 +255,107 @@ def test_decode_over_joined_steps(lengths, order, leaves, mode, options, d, kv):
     cfg = TreeConfig("joined", 2, 8, d, "bf16", 0, 0, 0, 0, 0, None, seed=len(lengths) + leaves)
     print("case joined decode", lengths[:4], order, leaves, mode, options, d, kv, flush=True)
     _decode(cfg, tree, kv, options, ets.ETS_PLAN_TREE if mode == "tree" else ets.ETS_PLAN_FLAT)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("back", [False, True])
+def test_the_largest_gap_on_the_device(back):
+    """Decode and step prefill with pieces a GiB apart in the pool; whatever no node holds is NaN."""
+    far = _far_tree(back)
+    n_tok = far.n_tokens
+    near = Tree(far.parent, np.array([0, 205, 250], np.int64), n_tok, far.leaf_node, 250 + OWN)  # the same rows
+    cfg = TreeConfig("far", 1, 4, 128, "bf16", 0, 0, 0, 0, 0, None, seed=4)
+    k, v, q = make_values_host(cfg, near)
+    qs = make_prefill_queries_host(cfg, near)
+    print("case largest gap", back, flush=True)
+    pools = []
+    for x in (k, v):
+        pool = torch.full((1, far.pool_tokens, 128), float("nan"), dtype=torch.bfloat16, device="cuda:0")
+        rows = pool_to_device(x)
+        for node in range(3):
+            at, a, n = int(far.tok_offset[node]), int(near.tok_offset[node]), int(n_tok[node])
+            pool[:, at:at + n] = rows[:, a:a + n]
+        pools.append(pool)
+    with make_ctx(cfg) as ctx:
+        out, lse, _ = gpu_attn(ctx, far, *pools, to_device(q), ets.ETS_PLAN_FLAT)
+        pout, plse, st = gpu_prefill(ctx, far, *pools, to_device(qs))
+        assert st.n_runs == 10 and ctx.check().violations == 0
+    for got, got_lse, want in ((out, lse, oracle_full(cfg, near, k, v, q)),
+                               (pout, plse, oracle_prefill(cfg, near, k, v, qs))):
+        compare(got.cpu().numpy().reshape(-1, 128), got_lse.cpu().numpy().reshape(-1), want[0].reshape(-1, 128),
+                want[1].reshape(-1), "bf16", "largest gap")
+
+
+GROWING = [(205, 10, False), (205, 19, False), (237, 10, False), (205, 19, True)]  # rows above, own, own in front
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("d,kv", [(64, "bf16"), (128, "bf16"), (128, "e4m3")])
+@pytest.mark.parametrize("leaves,mode,options,small", [
+    (3, "flat", {}, False), (3, "flat", {"stream_chunk": 64}, False),  # four waves to an item
+    (9, "tree", {}, False), (9, "tree", {"cascade_chunk": 64, "fuse_merge": 1}, False),  # row-parallel
+    (5, "flat", {}, True), (5, "flat", {"stream_chunk": 64}, True)])   # one wave to an item
+def test_growth_of_joined_tails(leaves, mode, options, small, d, kv):
+    """Leaf queries on a node whose last step is joined with the rows above it: 13 + 10 rows fill up to 32 and
+    go on in the spare step, 13 + 19 are full from the start; with chunks of 64 rows that step is the first of
+    its item (205 rows above) or the second (237), of which the start table holds copies.  After 33 tokens the
+    tree is planned again.  Items of one wave need a call whose bytes take long: another search in the same
+    forest, of as many rows as the planner asks for."""
+    hkv, hq = 2, 8
+    cfg = TreeConfig("growth", hkv, hq, d, "bf16", 0, 0, 0, 0, 0, None, seed=leaves + d)
+    for above, own, front in GROWING:
+        print("case growth", above, own, front, leaves, mode, options, small, d, kv, flush=True)
+        room = own + 40
+        off = np.array([room + 3, 0] if front else [0, above + 3], np.int64)
+        near = Tree(np.array([-1, 0], np.int32), off, np.array([above, own], np.int32), np.ones(leaves, np.int32),
+                    above + 3 + room)
+        k, v, q = make_values_host(cfg, near) if kv == "bf16" else make_values_fp8_host(cfg, near, KS, VS)
+        k, v = _poisoned(k, near), _poisoned(v, near)
+        kd, vd = pool_to_device(k), pool_to_device(v)
+        parent, n_tok, leaf_node = near.parent, near.n_tokens, near.leaf_node
+        qd = to_device(q)
+        if small:
+            other = 550000 * 128 // d * 2
+            parent, n_tok = np.append(parent, np.int32(-1)), np.append(n_tok, np.int32(other))
+            off, leaf_node = np.append(off, near.pool_tokens), np.append(leaf_node, np.int32(2))
+            qd = torch.cat([qd, qd[:1]])
+
+            def wider(x):
+                y = torch.empty((hkv, near.pool_tokens + other + 40, d), dtype=x.dtype, device="cuda:0")
+                y.normal_() if kv == "bf16" else y.random_(0, 120)
+                y[:, :near.pool_tokens] = x
+                return y
+            kd, vd = wider(kd), wider(vd)
+        with make_ctx(cfg, options) as ctx:
+            if kv == "e4m3":
+                ctx.set_kv_format(ets.ETS_KV_FP8_E4M3, KS, VS)
+            st = ctx.plan(parent, off, n_tok, leaf_node, ets.ETS_PLAN_TREE if mode == "tree" else ets.ETS_PLAN_FLAT)
+            if small:  # the longest item that one wave takes
+                ns = st.unique_kv_bytes * (2 if kv == "e4m3" else 1) // 5500
+                assert ns // 4 // 2500 * 16 >= above + own + 40
+            grown, replans = near.n_tokens, 0
+            for step in range(37):
+                if step > 0:
+                    fresh = Tree(near.parent, near.tok_offset, near.n_tokens, leaf_node, leaf_node.size)
+                    kn, vn = (make_values_host(cfg, fresh, step) if kv == "bf16" else
+                              make_values_fp8_host(cfg, fresh, KS, VS, step))[:2]
+                    replans += bool(ctx.plan_advance())
+                    ctx.kv_append(kd, vd, kd.shape[1], to_device(kn), to_device(vn))
+                    grown = oracle.append_kv(near.tok_offset, grown, near.leaf_node, k, v, kn[:leaves], vn[:leaves])
+                if step not in (0, 1, 2, 8, 9, 10, 22, 23, 32, 33, 36):
+                    continue
+                assert ctx.check().violations == 0
+                L = leaf_node.size
+                out = torch.full((L, hq, d), float("nan"), device="cuda:0")
+                lse = torch.full((L, hq), float("nan"), device="cuda:0")
+                ws = torch.empty(ctx.stats().workspace_bytes, dtype=torch.uint8, device="cuda:0")
+                ctx.decode(kd, vd, kd.shape[1], qd, out, lse, ws, ws.numel())
+                torch.cuda.synchronize()
+                args = (near.parent, near.tok_offset, grown, near.leaf_node, k, v)
+                if kv == "bf16":
+                    oo, ol = oracle.tree_decode_attn(*args, q, hkv, hq, d)
+                else:
+                    oo, ol = oracle.tree_decode_attn_fp8kv(*args, KS, VS, q, hkv, hq, d)
+                compare(out[:leaves].cpu().numpy().reshape(-1, d), lse[:leaves].cpu().numpy().reshape(-1),
+                        oo.reshape(-1, d), ol.reshape(-1), "bf16", "growth %d" % step)
+            assert replans == 1
