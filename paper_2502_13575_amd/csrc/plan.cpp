@@ -55,12 +55,19 @@ constexpr int64_t kMaxPiecesPerChunk = kTreeAttnMaxSteps;  // step list the kern
 inline int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 inline int64_t round_up(int64_t a, int64_t m) { return ceil_div(a, m) * m; }
 
-// Appends the (merged) pool runs of a node list to `out`.  A node that holds leaf
-// queries grows by a token per decode step: the run that ends such a node is marked
-// (pad = 1) and nothing is merged behind it.  Returns false if a growing node has no
-// rows yet (there is no run to mark).
-bool collect_runs(const Plan& p, const std::vector<int32_t>& nodes, const std::vector<int64_t>& own,
-                  std::vector<Run>& out) {
+// Consecutive pool rows of a node list, before they are cut into steps.
+struct Piece {
+    int64_t tok;  // first pool row
+    int32_t n;    // rows
+    bool grows;   // ends a node that holds leaf queries
+};
+
+// Appends the (merged) pieces of a node list to `out`.  A node that holds leaf
+// queries grows by a token per decode step: the piece that ends such a node is marked
+// and nothing is merged behind it.  Returns false if a growing node has no
+// rows yet (there is no piece to mark).
+bool collect_pieces(const Plan& p, const std::vector<int32_t>& nodes, const std::vector<int64_t>& own,
+                    std::vector<Piece>& out) {
     bool ok = true;
     bool closed = true;  // the previous run must not be extended
     for (int32_t n : nodes) {
@@ -75,9 +82,9 @@ bool collect_runs(const Plan& p, const std::vector<int32_t>& nodes, const std::v
             (int64_t)out.back().n + len <= std::numeric_limits<int32_t>::max()) {
             out.back().n += len;
         } else {
-            out.push_back(Run{tok, len, 0});
+            out.push_back(Piece{tok, len, false});
         }
-        out.back().join = grows ? 1 : 0;
+        out.back().grows = grows;
         closed = grows;
     }
     return ok;
@@ -86,11 +93,11 @@ bool collect_runs(const Plan& p, const std::vector<int32_t>& nodes, const std::v
 // Cuts `src` (total `tokens` rows) into chunks of at most `cap` rows, sized
 // evenly in multiples of `grain` rows, appending the chunks' runs to plan.runs.  With
 // piece > 0 no emitted run is longer than `piece` rows (the matrix-core kernel
-// walks its run list in steps of at most 32 rows).  Behind the last piece of a marked
-// run (a growing node's tail) an empty spare run is emitted and an AdvEntry recorded;
+// walks its run list in steps of at most 32 rows).  Behind the last run of a marked
+// piece (a growing node's tail) an empty spare run is emitted and an AdvEntry recorded;
 // returns false if a chunk's step list had no room for a spare.  `join`: a step that the end of a
-// run does not fill goes on in the next run (see join_rows).
-bool cut_runs(Plan& p, const std::vector<Run>& src, int64_t tokens, int64_t cap, int64_t piece, bool join,
+// piece does not fill goes on in the next piece (see join_rows).
+bool cut_runs(Plan& p, const std::vector<Piece>& src, int64_t tokens, int64_t cap, int64_t piece, bool join,
               std::vector<Chunk>& chunks, int64_t grain = 32) {
     chunks.clear();
     if (tokens <= 0) return true;
@@ -118,9 +125,9 @@ bool cut_runs(Plan& p, const std::vector<Run>& src, int64_t tokens, int64_t cap,
             used += take;
             want -= take;
             c.tokens += (int32_t)take;
-            open = join && used == src[ri].n && !src[ri].join && p.runs.back().n < kStepRows;
+            open = join && used == src[ri].n && !src[ri].grows && p.runs.back().n < kStepRows;
             if (used == src[ri].n) {
-                if (src[ri].join) {
+                if (src[ri].grows) {
                     if (piece > 0 && pieces >= kMaxPiecesPerChunk) {
                         ok = false;
                     } else {
@@ -304,7 +311,7 @@ ets_status build(const ets_shape& shape, const PlanOptions& opt, const ets_tree&
     p.adv_in_place = true;
     p.advances = 0;
 
-    std::vector<Run> tmp_runs;
+    std::vector<Piece> pieces;
     std::vector<Chunk> chunks;
     std::vector<int32_t> stream_tokens;   // per stream item, for ordering
     std::vector<int64_t> cascade_cost;    // per cascade item, for ordering
@@ -640,9 +647,9 @@ ets_status build(const ets_shape& shape, const PlanOptions& opt, const ets_tree&
             ccap = wide_budget_ns / t_wide * kTile;
         else if (ccap <= 0)
             ccap = item_budget_ns / t_tile * kTile;
-        tmp_runs.clear();
-        if (!collect_runs(p, sh.nodes, own, tmp_runs)) p.adv_in_place = false;
-        if (!cut_runs(p, tmp_runs, sh.tokens, ccap, piece, join, shared_chunks[i]))
+        pieces.clear();
+        if (!collect_pieces(p, sh.nodes, own, pieces)) p.adv_in_place = false;
+        if (!cut_runs(p, pieces, sh.tokens, ccap, piece, join, shared_chunks[i]))
             p.adv_in_place = false;
         sh.n_chunks = (int32_t)shared_chunks[i].size();
     }
@@ -664,11 +671,11 @@ ets_status build(const ets_shape& shape, const PlanOptions& opt, const ets_tree&
             own_segs(e, reads);
             for (size_t i = reads.size(); i-- > 0;)
                 own_nodes.insert(own_nodes.end(), segs[reads[i]].nodes.begin(), segs[reads[i]].nodes.end());
-            tmp_runs.clear();
-            if (!collect_runs(p, own_nodes, own, tmp_runs)) p.adv_in_place = false;
+            pieces.clear();
+            if (!collect_pieces(p, own_nodes, own, pieces)) p.adv_in_place = false;
             int64_t tokens = 0;
-            for (const Run& r : tmp_runs) tokens += r.n;
-            if (!cut_runs(p, tmp_runs, tokens, scap, piece, join, chunks, direct ? kDirectGrain : 32))
+            for (const Piece& x : pieces) tokens += x.n;
+            if (!cut_runs(p, pieces, tokens, scap, piece, join, chunks, direct ? kDirectGrain : 32))
                 p.adv_in_place = false;
             if (direct) p.direct_waves = std::max(p.direct_waves, std::max(1, (int32_t)chunks.size()));
             int32_t c_idx = 0;
