@@ -10,7 +10,7 @@
 #include <functional>
 #include <limits>
 #include <new>
-#include <queue>
+#include <vector>
 
 namespace ets {
 namespace {
@@ -50,17 +50,43 @@ int64_t rounds_cost(int64_t workgroups, int64_t cycles_per_run) {
 // 17 to 42 tokens, 8 heads per kv head, 536 items in 2.1 rounds against 896 in 3.5: 104.6 us with
 // 128 rows, 89.6 with 256; 42 steps of 36 to 44 tokens, 672 against 1 008: 80.4 and 87.5.
 constexpr int64_t kScheduledWorkgroups = 4096;
-struct Schedule {
-    std::priority_queue<int64_t, std::vector<int64_t>, std::greater<int64_t>> free_at;
-    int64_t end = 0;
+// Work items are handed out for all kv heads one after the other; where these divide the units, the units
+// stay in groups of as many with the same times, and one of each group is enough to follow.
+class Schedule {
+    size_t units_;
+    int32_t copies_;
+    std::vector<int64_t> free_at_;  // a heap, earliest on top, once every unit has a workgroup
+    int64_t end_ = 0;
+
+public:
+    explicit Schedule(int32_t n_kv_heads)
+        : units_((size_t)(kComputeUnits % n_kv_heads == 0 ? kComputeUnits / n_kv_heads : kComputeUnits)),
+          copies_(kComputeUnits % n_kv_heads == 0 ? 1 : n_kv_heads) {
+        free_at_.reserve(units_);
+    }
+    int64_t end() const { return end_; }
+    void add_item(int64_t cycles) {
+        for (int32_t c = 0; c < copies_; ++c) add(cycles);
+    }
+
+private:
     void add(int64_t cycles) {
-        int64_t at = cycles;
-        if ((int64_t)free_at.size() == kComputeUnits) {
-            at += free_at.top();
-            free_at.pop();
+        if (free_at_.size() < units_) {
+            free_at_.push_back(cycles);
+            end_ = std::max(end_, cycles);
+            if (free_at_.size() == units_) std::make_heap(free_at_.begin(), free_at_.end(), std::greater<int64_t>());
+            return;
         }
-        free_at.push(at);
-        end = std::max(end, at);
+        const int64_t at = free_at_[0] + cycles;
+        end_ = std::max(end_, at);
+        size_t i = 0;  // the top's new time sinks to its place
+        for (size_t child = 1; child < units_; child = 2 * i + 1) {
+            if (child + 1 < units_ && free_at_[child + 1] < free_at_[child]) ++child;
+            if (free_at_[child] >= at) break;
+            free_at_[i] = free_at_[child];
+            i = child;
+        }
+        free_at_[i] = at;
     }
 };
 
@@ -117,6 +143,13 @@ ets_status build(const ets_shape& shape, const ets_tree& tree, PrefillPlan& p, i
     std::vector<int32_t> run_begin_of(N, -1), anc_runs_of(N, 0);  // per distinct leaf node
     std::vector<int32_t> plain_runs_of(N, 0);  // ancestors' runs if none were joined
     std::vector<int64_t> anc_tokens_of(N, 0);
+    auto steps_of = [](int64_t n) { return (n + kStepRows - 1) / kStepRows; };
+    auto append_steps = [&](int64_t tok, int64_t n) {
+        const size_t at = p.runs.size();
+        p.runs.resize(at + (size_t)steps_of(n));
+        for (Run* out = p.runs.data() + at; n > 0; ++out, tok += kStepRows, n -= kStepRows)
+            *out = Run{tok, (int32_t)std::min<int64_t>(kStepRows, n), 0};
+    };
     // `join`: whether runs may be joined of two pieces
     auto make_runs = [&](bool join) {
         p.runs.clear();
@@ -135,12 +168,12 @@ ets_status build(const ets_shape& shape, const ets_tree& tree, PrefillPlan& p, i
                 // has, and every node of some hundred tokens used to end in a half-empty one.
                 int64_t cur_tok = 0, cur_n = 0, anc_tokens = 0;
                 auto flush = [&]() {
-                    int64_t off = 0;
-                    plain_runs_of[v] += (int32_t)((cur_n + kStepRows - 1) / kStepRows);
+                    int64_t joined = 0;
+                    plain_runs_of[v] += (int32_t)steps_of(cur_n);
                     if (join && cur_n > 0 && (int32_t)p.runs.size() - run_begin_of[v] > kPrefillFirstRuns)
-                        p.joins = (off = join_rows(p.runs.back(), cur_tok, cur_n)) > 0 || p.joins;
-                    for (; off < cur_n; off += kStepRows)
-                        p.runs.push_back(Run{cur_tok + off, (int32_t)std::min<int64_t>(kStepRows, cur_n - off), 0});
+                        joined = join_rows(p.runs.back(), cur_tok, cur_n);
+                    p.joins = p.joins || joined > 0;
+                    append_steps(cur_tok + joined, cur_n - joined);
                     cur_n = 0;
                 };
                 for (size_t c = 0; c + 1 < chain.size(); ++c) {
@@ -160,8 +193,7 @@ ets_status build(const ets_shape& shape, const ets_tree& tree, PrefillPlan& p, i
                 live[v] = 1;
                 anc_runs_of[v] = (int32_t)p.runs.size() - run_begin_of[v];
                 anc_tokens_of[v] = anc_tokens;
-                for (int32_t off = 0; off < len; off += 32)
-                    p.runs.push_back(Run{p.tok_offset[v] + off, std::min(32, len - off), 0});
+                append_steps(p.tok_offset[v], len);
                 if (p.runs.size() > (size_t)std::numeric_limits<int32_t>::max() - 64)
                     return false;
             }
@@ -182,7 +214,7 @@ ets_status build(const ets_shape& shape, const ets_tree& tree, PrefillPlan& p, i
         bool small = rounds_cost(n_small, kPrefillRunSmall) < rounds_cost(n_large, kPrefillRunLarge);
         if (small && n_small > n_large && n_small > kComputeUnits && n_small <= kScheduledWorkgroups) {
             auto ends = [&](int32_t rows) {
-                Schedule schedule;
+                Schedule schedule(shape.n_kv_heads);
                 for (int32_t oi = 0; oi < L; ++oi) {
                     const int32_t v = p.leaf_node[order[oi]], len = p.n_tokens[v];
                     for (int32_t t0 = 0; t0 < len; t0 += rows / G) {
@@ -190,10 +222,10 @@ ets_status build(const ets_shape& shape, const ets_tree& tree, PrefillPlan& p, i
                         const int64_t runs = anc_runs_of[v] + (t0 + n_tok - 1) / 32 + 1;
                         const int64_t cycles =
                             runs * (n_tok * G <= kPrefillRowsSmall ? kPrefillRunSmall : kPrefillRunLarge);
-                        for (int32_t h = 0; h < shape.n_kv_heads; ++h) schedule.add(cycles);
+                        schedule.add_item(cycles);
                     }
                 }
-                return schedule.end;
+                return schedule.end();
             };
             small = ends(kPrefillRowsSmall) * 100 < ends(kPrefillRowsPerItem) * 105;
         }
@@ -274,14 +306,23 @@ ets_status build(const ets_shape& shape, const ets_tree& tree, PrefillPlan& p, i
             return (it.run_end - it.run_begin) * (it.n_tok * G <= kPrefillRowsSmall ? kPrefillRunSmall : kPrefillRunLarge);
         };
         auto end_of = [&](const std::vector<int32_t>& order) {
-            Schedule schedule;
-            for (int32_t i : order)
-                for (int32_t h = 0; h < shape.n_kv_heads; ++h) schedule.add(cycles(i));
-            return schedule.end;
+            Schedule schedule(shape.n_kv_heads);
+            for (int32_t i : order) schedule.add_item(cycles(i));
+            return schedule.end();
         };
-        std::vector<int32_t> longest = p.order;
-        std::stable_sort(longest.begin(), longest.end(), [&](int32_t x, int32_t y) { return cycles(x) > cycles(y); });
-        if (end_of(longest) * 100 < end_of(p.order) * 99) p.order.swap(longest);
+        // (an order cannot end before an even share of the work, nor before its longest item)
+        int64_t work = 0, most = 0;
+        for (int32_t i : p.order) {
+            work += cycles(i);
+            most = std::max<int64_t>(most, cycles(i));
+        }
+        const int64_t even = (work * shape.n_kv_heads + kComputeUnits - 1) / kComputeUnits;
+        const int64_t end = end_of(p.order);
+        if (std::max(even, most) * 100 < end * 99) {
+            std::vector<int32_t> longest = p.order;
+            std::stable_sort(longest.begin(), longest.end(), [&](int32_t x, int32_t y) { return cycles(x) > cycles(y); });
+            if (end_of(longest) * 100 < end * 99) p.order.swap(longest);
+        }
     }
     st.n_items = (int64_t)p.items.size();
     st.n_runs = (int64_t)p.runs.size();
