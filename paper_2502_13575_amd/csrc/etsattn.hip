@@ -236,7 +236,7 @@ void launch_direct_dg(const ets_ctx* c, const LaunchArgs& a) {
     constexpr int U = (G >= 8) ? 2 : 4;
     const unsigned grid = (unsigned)(c->plan.stats.n_leaves * c->shape.n_kv_heads);
     hipLaunchKernelGGL((direct_attn_kernel<float, D, G, U>), dim3(grid), dim3(64u * (unsigned)c->plan.direct_waves),
-                       0, a.stream, static_cast<const float*>(a.k), static_cast<const float*>(a.v), a.pool_tokens,
+                       (unsigned)direct_lds_bytes(c->plan.direct_waves, D, G), a.stream, static_cast<const float*>(a.k), static_cast<const float*>(a.v), a.pool_tokens,
                        static_cast<const float*>(a.q), c->d_runs, c->d_stream, c->d_part_base,
                        c->shape.n_kv_heads, c->scale * 1.4426950408889634f, c->v_scales, a.out,
                        c->out_bf16 ? 1 : 0, a.lse);

@@ -170,21 +170,28 @@ __global__ __launch_bounds__(64) void stream_attn_kernel(
     }
 }
 
+// LDS of direct_attn_kernel with this many waves.
+constexpr int direct_lds_bytes(int waves, int D, int G) { return waves * G * (D * 4 + 8); }
+
 // A small call over fp32 pools in one launch: a workgroup takes a leaf query's whole path for one kv
 // head, a wave each of its items (at most sixteen, in slot order from part_base[leaf] on; waves past the
 // last one idle), and merges their results through LDS as merge_kernel does through the workspace.
 // Bound: the chain of dependent round trips (items -> runs -> rows -> fold -> output) and the launch
 // itself; the merge launch it saves is a second such chain behind the first one's end.  8 leaves of 80 rows
-// 9.2 -> 5.8 us, 10 of 432 rows with 16 query heads of 128 11.5 -> 8.7; the rule stands in plan.cpp.
+// 9.2 -> 5.8 us, 24 of 486 rows with 32 query heads of 64 11.5 -> 8.9; the rule stands in plan.cpp.
+// LDS goes by the waves that there are: with room for sixteen (66 KB with eight query heads of 128) two workgroups
+// fit a compute unit, 179 leaves of 19 rows 4 kv heads x 8 query heads of 128, 20.7 us; so 11.8.
 template <typename T, int D, int G, int U>
 __global__ __launch_bounds__(64 * kDirectWaves) void direct_attn_kernel(
     const T* __restrict__ k_pool, const T* __restrict__ v_pool, int64_t pool_tokens,
     const T* __restrict__ q, const Run* __restrict__ runs, const StreamItem* __restrict__ items,
     const int32_t* __restrict__ part_base, int n_kv_heads, float scale_log2e, HeadScales v_scales,
     void* __restrict__ out, int out_bf16, float* __restrict__ lse) {
-    __shared__ __align__(16) float sm_o[kDirectWaves][G * D];
-    static_assert(__alignof__(sm_o) >= alignof(float4) && D % 4 == 0, "rows are written 16 bytes at a time");
-    __shared__ float2 sm_ml[kDirectWaves][G];
+    // [wave][G * D] weighted V, then [wave][G] (m, l): direct_lds_bytes for the waves that there are
+    extern __shared__ float4 direct_lds[];
+    static_assert(alignof(float4) == 16 && D % 4 == 0, "rows are written 16 bytes at a time");
+    float* const sm_o = reinterpret_cast<float*>(direct_lds);
+    float2* const sm_ml = reinterpret_cast<float2*>(sm_o + (blockDim.x >> 6) * (G * D));
     const int h = blockIdx.x % n_kv_heads;
     const int leaf = blockIdx.x / n_kv_heads;
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -200,11 +207,11 @@ __global__ __launch_bounds__(64 * kDirectWaves) void direct_attn_kernel(
         if (lane == a) {
 #pragma unroll
             for (int g = 0; g < G; ++g) {
-                float4* dst = reinterpret_cast<float4*>(&sm_o[w][g * D + a * EPL]);
+                float4* dst = reinterpret_cast<float4*>(sm_o + w * (G * D) + g * D + a * EPL);
 #pragma unroll
                 for (int i = 0; i < EPL / 4; ++i)
                     dst[i] = make_float4(st.o[g][4 * i], st.o[g][4 * i + 1], st.o[g][4 * i + 2], st.o[g][4 * i + 3]);
-                if (a == 0) sm_ml[w][g] = make_float2(st.m[g], st.l[g]);
+                if (a == 0) sm_ml[w * G + g] = make_float2(st.m[g], st.l[g]);
             }
         }
     }
@@ -213,12 +220,12 @@ __global__ __launch_bounds__(64 * kDirectWaves) void direct_attn_kernel(
     for (int e = threadIdx.x; e < G * D; e += blockDim.x) {
         const int g = e / D;
         float ms = -INFINITY, l = 0.f, acc = 0.f;
-        for (int k = 0; k < n_items; ++k) ms = fmaxf(ms, sm_ml[k][g].x);
+        for (int k = 0; k < n_items; ++k) ms = fmaxf(ms, sm_ml[k * G + g].x);
         for (int k = 0; k < n_items; ++k) {
-            const float2 ml = sm_ml[k][g];
+            const float2 ml = sm_ml[k * G + g];
             const float f = fast_exp2(ml.x - ms);
             l += ml.y * f;
-            acc = fmaf(sm_o[k][e], f, acc);
+            acc = fmaf(sm_o[k * (G * D) + e], f, acc);
         }
         const float r = acc * (n_items == 0 ? 0.f : 1.f / l) * v_scales.of(h);
         if (out_bf16) static_cast<uint16_t*>(out)[row0 * D + e] = f32_to_bf16_rne(r);
