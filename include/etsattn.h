@@ -69,8 +69,8 @@ typedef enum { ETS_F32 = 0, ETS_BF16 = 1 } ets_dtype;
  * option "require_sharing" ets_plan refuses (ETS_ERR_UNSUPPORTED) a tree-mode plan that
  * would not share.  The wide kernel and step prefill are built for head_dim 128 only.
  *
- * Small calls over fp32 pools (paths of up to 512 rows, up to 50 million multiply-adds per
- * contraction, "stream_chunk" unset) are one launch: a workgroup merges a leaf query's
+ * Small calls over fp32 pools (paths of up to 320 to 512 rows, by the head geometry, with up
+ * to 10 000 to 20 000 partial results over all query heads; "stream_chunk" unset) are one launch: a workgroup merges a leaf query's
  * partial results in its own memory and writes the result.  For such a plan n_partials,
  * workspace_bytes and the report of ets_plan_check count the partial results as if they
  * went through the workspace, and ets_tree_decode_attn asks for it by the same rule as for

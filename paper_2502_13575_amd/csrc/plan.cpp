@@ -47,13 +47,33 @@ struct Chunk {
     int32_t run_begin, run_end, tokens;
 };
 
-constexpr int64_t kDirectGrain = 16, kDirectTokens = 32;  // rows per item of a direct plan: multiples, at most
-constexpr int64_t kDirectProducts = 50000000;  // its multiply-adds per contraction, at most
-
 constexpr int64_t kMaxPiecesPerChunk = kTreeAttnMaxSteps;  // step list the kernel keeps in LDS
 
 inline int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 inline int64_t round_up(int64_t a, int64_t m) { return ceil_div(a, m) * m; }
+
+// Small calls over fp32 pools take one launch (direct_attn_kernel): rows per item of such a plan, 0 = two
+// launches.  `longest`: rows of the longest path; items16, items32: items of all leaf queries, at least one each, if
+// they are cut after 16 or 32 rows.  Two limits:
+//  - A compute unit takes a whole path of a kv head, in at most sixteen waves, while two launches spread
+//    it.  Time of two launches over that of one, calls of up to 60 leaves: up to two query heads per kv head 1.3 to
+//    1.6 at 250 to 400 rows, 1.04 to 1.2 at 450 to 512; four heads 1.2 to 1.45 at 250, 1.04 to 1.15 at 400, 0.87
+//    to 1.05 from 430 on; eight heads of 64 0.92 to 1.1 at 300 to 320, 0.83 to 0.95 from 410, of 128 1.02
+//    to 1.15 at 340 to 400, 0.83 to 0.96 from 420.
+//  - With more waves than the chip holds at once the ends of the items count, each a fold of every query head's
+//    sums over the lanes: up to 10 000 partial rows (items times query heads) 16 rows to an item took 0.96 to
+//    2.0, with eight heads up to 20 000; beyond, down to 0.65 (364 leaves of 71 rows, 32 heads), where 32
+//    rows take 1.03.  32 rows up to 15 000 partial rows 0.85 to 1.7; beyond, 0.58 to 1.3.
+// 278 random searches of 8 to 24 leaves: 114 come under the rule, 1.01 to 1.7 times faster, 1.27 in the geometric mean;
+// 900 calls of 1 to 2 000 leaves: 700, 1.31, 17 of them 2 to 19 % slower.  The others would mostly lose.
+constexpr int64_t kDirectGrain = 16;  // rows of an item: a multiple of
+int64_t direct_rows(const ets_shape& shape, int64_t longest, int64_t items16, int64_t items32) {
+    const int32_t G = shape.n_q_heads / shape.n_kv_heads, Hq = shape.n_q_heads;
+    const int64_t most = G <= 2 ? 512 : G == 4 ? 416 : shape.head_dim == 64 ? 320 : 400;
+    if (longest > most) return 0;
+    if (longest <= 16 * kDirectWaves && items16 * Hq <= (G == 8 ? 20000 : 10000)) return 16;
+    return items32 * Hq <= 15000 ? 32 : 0;
+}
 
 // Consecutive pool rows of a node list, before they are cut into steps.
 struct Piece {
@@ -571,6 +591,7 @@ ets_status build(const ets_shape& shape, const PlanOptions& opt, const ets_tree&
         if (body < sh.n_ent) f(body, sh.n_ent - body);
     };
     int64_t own_total = 0, longest_own = 0, work_ns = 0, wide_work_ns = 0;
+    int64_t own_items[2] = {0, 0};  // of what the leaf queries read themselves, cut after 16 and 32 rows
     int64_t items_est = L;  // one item per leaf query for what it reads itself, plus:
     for (const Shared& sh : shared) {
         if (sh.n_ent == 1) own_total += sh.tokens;  // (beside a list of others: read by one leaf query)
@@ -594,18 +615,12 @@ ets_status build(const ets_shape& shape, const PlanOptions& opt, const ets_tree&
         }
         own_total += tokens;
         longest_own = std::max(longest_own, tokens);
+        for (int i = 0; i < 2; ++i) own_items[i] += std::max<int64_t>(ceil_div(tokens, 16 << i), 1);
     }
     st.stream_tokens = own_total;
-    // Small calls over fp32 pools: one launch (direct_attn_kernel) that cuts every path into sixteen items at
-    // most.  A compute unit takes a whole path of a kv head then, of which it reads some 150 KB in a microsecond: of
-    // paths up to 512 rows (32 to an item) 17 calls took 0.57 to 0.96 of the time of two launches, from there
-    // to 670 rows 0.85 to 1.17, of 1 200 1.5.  And it spreads no work: with more than some 50 M multiply-adds
-    // per call (100 leaves of 504 rows, 16 query heads of 64: 18.5 us in two launches, 18.8 in one; 512 of 256 rows, 8
-    // heads: 40.6 and 47.2; 24 leaves of 486 rows, 64 heads: 20.5 and 17.4) the chip is full either way.
-    const int64_t direct_cap = round_up(std::max<int64_t>(ceil_div(longest_own, kDirectWaves), 1), kDirectGrain);
-    const bool direct = shape.dtype == ETS_F32 && opt.stream_chunk <= 0 && L > 0 && direct_cap <= kDirectTokens &&
-                        own_total * shape.n_q_heads * shape.head_dim <= kDirectProducts &&
-                        (int64_t)L * kDirectWaves * partial_bytes / 2 <= ETS_STATIC_SCRATCH_BYTES;
+    const int64_t direct_cap = shape.dtype == ETS_F32 && opt.stream_chunk <= 0 && L > 0
+                                   ? direct_rows(shape, longest_own, own_items[0], own_items[1]) : 0;
+    const bool direct = direct_cap > 0;
     // time the whole call is expected to take: the larger of the HBM time of the
     // unique bytes (at ~5.5 TB/s) and the modelled work spread over the resident
     // workgroups; no single item should take more than half of it: finer items balance no

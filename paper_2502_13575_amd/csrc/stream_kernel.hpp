@@ -178,7 +178,7 @@ constexpr int direct_lds_bytes(int waves, int D, int G) { return waves * G * (D 
 // last one idle), and merges their results through LDS as merge_kernel does through the workspace.
 // Bound: the chain of dependent round trips (items -> runs -> rows -> fold -> output) and the launch
 // itself; the merge launch it saves is a second such chain behind the first one's end.  8 leaves of 80 rows
-// 9.2 -> 5.8 us, 24 of 486 rows with 32 query heads of 64 11.5 -> 8.9; the rule stands in plan.cpp.
+// 9.2 -> 5.8 us, 32 of 300 rows with 16 query heads of 64 9.2 -> 7.9; the rule stands in plan.cpp.
 // LDS goes by the waves that there are: with room for sixteen (66 KB with eight query heads of 128) two workgroups
 // fit a compute unit, 179 leaves of 19 rows 4 kv heads x 8 query heads of 128, 20.7 us; so 11.8.
 template <typename T, int D, int G, int U>

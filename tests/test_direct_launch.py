@@ -8,7 +8,7 @@ import oracle
 import paper_2502_13575_amd as ets
 from workload import Tree, TreeConfig, make_values_host
 
-from _gpu_util import compare, make_ctx, oracle_full, pool_to_device, to_device
+from _gpu_util import compare, gpu_attn, make_ctx, oracle_full, pool_to_device, to_device
 
 
 def _tree(root, lengths, room=0):
@@ -39,6 +39,42 @@ def test_items(root, lengths, most):
             counts.append(n)
         # beyond 512 rows: items of 64 rows and a second launch
         assert max(counts) == (most if most is not None else -(-(root + max(lengths)) // 64))
+
+
+# heads, head_dim, longest path in one launch; with paths of 40 rows the most leaf queries with items of 16 rows
+# (three each) and of 32 (two each) in one launch
+RULE = [((4, 4, 64), 512, 833, 1875), ((4, 8, 128), 512, 416, 937), ((2, 8, 64), 416, 416, 937),
+        ((2, 8, 128), 416, 416, 937), ((1, 8, 64), 320, 833, 937), ((1, 8, 128), 400, 833, 937)]
+
+
+def _items(tree, hkv, hq, d):
+    with ets.Context(hkv, hq, d, ets.ETS_F32, -1) as ctx:
+        st = ctx.plan(tree.parent, tree.tok_offset, tree.n_tokens, tree.leaf_node)
+        assert ctx.check().violations == 0 and st.workspace_bytes <= ets.ETS_STATIC_SCRATCH_BYTES
+        return ctx.leaf_cover(tree.n_leaves - 1)[1]
+
+
+@pytest.mark.parametrize("heads,longest,leaves16,leaves32", RULE)
+def test_where_the_rule_ends(heads, longest, leaves16, leaves32):
+    for rows, items in ((256, 16), (257, 9), (longest, -(-longest // 32)), (longest + 1, -(-(longest + 1) // 64))):
+        assert _items(_tree(rows - 30, (30,)), *heads) == items, rows
+    for leaves, items in ((leaves16, 3), (leaves16 + 1, 2), (leaves32, 2), (leaves32 + 1, 1)):
+        assert _items(_tree(30, (10,) * leaves), *heads) == items, leaves
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("hkv,hq,d,leaves", [(1, 8, 128, 833), (1, 8, 128, 937), (2, 8, 64, 417), (4, 4, 64, 1875)])
+def test_many_leaves_against_the_oracle(hkv, hq, d, leaves):
+    """Calls at the upper end: several workgroups of two or three waves to a compute unit."""
+    tree = _tree(30, (10,) * leaves)
+    cfg = TreeConfig("direct", hkv, hq, d, "f32", 0, 0, 0, 0, 0, None, seed=leaves + hq)
+    print("case direct leaves", hkv, hq, d, leaves, flush=True)
+    k, v, q = make_values_host(cfg, tree)
+    with make_ctx(cfg) as ctx:
+        out, lse, _ = gpu_attn(ctx, tree, pool_to_device(k), pool_to_device(v), to_device(q))
+    oo, ol = oracle_full(cfg, tree, k, v, q)
+    compare(out.cpu().numpy().reshape(-1, d), lse.cpu().numpy().reshape(-1), oo.reshape(-1, d), ol.reshape(-1),
+            "f32", "direct leaves")
 
 
 @pytest.mark.gpu
