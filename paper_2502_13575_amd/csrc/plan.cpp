@@ -442,7 +442,7 @@ ets_status build(const ets_shape& shape, const PlanOptions& opt, const ets_tree&
     // tokens whether it waits on memory (few rows) or computes (many rows), and t_item to
     // start and to store its partial results; kResident workgroups are resident (three per
     // compute unit, two of the group kernel with head_dim 128; with head_dim 64 four are, of which the model knows
-    // three).  Measured: 2.1-2.7 us per tile, 6.5-8.5
+    // three; what four would change in it was not measured).  Measured: 2.1-2.7 us per tile, 6.5-8.5
     // us per item; the sum predicts the attention launch of the configurations within 5 %.  Group
     // kernel: 1.5 us per tile of up to 64 query rows, 2.0-2.7 of more, 5-8 us per item, of which the
     // model takes one time for all.

@@ -47,7 +47,8 @@
 // A run that its node does not fill goes on in the next piece of the path (Run::join): a run costs the same
 // however many rows it has, and with nodes of some hundred tokens 4 to 6 % of the walk, with nodes of 16 to
 // 64 up to 40 %, were rows that are not there.  128 steps of 10 to 14 tokens over 100 such steps, 8 heads:
-// 240 -> 163 us; 64 steps of 100 to 150 tokens over 16, E4M3 pools: 450 -> 443.
+// 240 -> 163 us; 64 steps of 100 to 150 tokens over 16, E4M3 pools: 447 -> 443; 256 ragged steps of 8 heads
+// 7.55 -> 7.25 ms.
 // The run list can be long (a path of thousands of rows), so its descriptors travel through
 // a ring of 256 entries in LDS that is refilled 128 at a time: tile t reads descriptors up to
 // 2 t + 9, and a refill at tile t writes those from 2 t + 128 on, 60 tiles ahead of their use.
@@ -55,8 +56,9 @@
 // Measured against eight waves of 32 rows: 256 workgroups of 256 rows over one path of 16.8 k rows,
 // 526 runs: 529 us = 1.0 us per run (585), of 128 rows: 331 us = 0.63 us per run (355).  38 k query
 // tokens of 8 heads each over 5.4 k rows: 7.7 ms (8.5); 512 steps of up to 512 tokens over 13 k rows:
-// 32.6 ms = 976 TFLOP/s (36.0).  In that launch the matrix pipes are busy 55 % of the cycles; a
+// 32.6 ms (36.0).  In that launch the matrix pipes are busy 55 % of the cycles; a
 // wave issues for 66 % of its time, waits to issue for 12 % and for data or at barriers for 22 %.
+// With joined runs the same launch takes 31.9 ms = 997 TFLOP/s (without, in turn on one box, 32.9).
 //
 // The same kernel serves decode attention for tree segments that MANY leaf queries share
 // (template parameter DECODE): there the 256 query rows of a work item are up to 256 / G

@@ -233,9 +233,11 @@ ets_status build(const ets_shape& shape, const ets_tree& tree, PrefillPlan& p, i
     };
     int32_t rows = rows_per_item();
     // The loop that takes joined runs is 1 to 3 % longer, and a launch of few rounds, where a workgroup waits for
-    // its loads more than for anything else, gains less by fewer rows.  14 drawn calls, the time without over
-    // the time with: up to four rounds 0.97 to 1.00 where less than 7 % of the runs are saved, 1.00 to 1.12
-    // where more are; of more rounds 4 % save 1 to 2 % of the time, 6 % save 3.
+    // its loads more than for anything else, gains less by fewer rows.  The time without over the time with, up
+    // to four rounds: 0.97 to 1.00 where less than 7 % of the runs are saved; 123 drawn calls where more are: up to
+    // 10 % 0.96 to 1.06, geometric mean 1.02, to 15 % 0.98 to 1.08, 1.03, beyond 0.97 to 1.19, 1.07 (5 of
+    // them lose more than a hundredth).  More rounds, 77 calls: 2.5 to 5 % 0.99 to 1.03, 1.01, to 8 % 0.98 to
+    // 1.05, 1.02, to 15 % 1.00 to 1.08, 1.05, beyond 1.02 to 1.21, 1.08.
     // (Joins that save no run are such a call too.)
     if (p.joins) {
         int64_t plain = 0, saved = 0;  // runs walked by all items
@@ -295,7 +297,7 @@ ets_status build(const ets_shape& shape, const ets_tree& tree, PrefillPlan& p, i
     }
     // Launch order.  Depth-first order ends a launch of few rounds on whatever comes last, and the chip waits
     // for its long items: there the longest go first where that ends earlier by a hundredth.  Items of the same
-    // length stay in depth-first order.  (1 280 workgroups of 64 steps of 100 to 150 tokens 449 -> 443 us; the model
+    // length stay in depth-first order.  (1 280 workgroups of 64 steps of 100 to 150 tokens 450 -> 443 us; the model
     // says 7 %, but a workgroup does not always go where a unit is free.  Beyond sixteen rounds it ends less than
     // a hundredth earlier, and what runs together should walk the same ancestors.)
     p.order.resize(p.items.size());

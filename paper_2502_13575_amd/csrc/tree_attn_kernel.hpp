@@ -55,8 +55,9 @@
 // A step that its piece of the list does not fill goes on in the next piece (Run::join): a tile costs the
 // same however many of its rows are there, and with nodes of 16 to 150 rows 10 to 40 % were not.  Its
 // loads, each row by its side of the join, stand behind a uniform branch: 100 leaves of 17 to 150 rows with
-// head_dim 64 23.6 -> 23.1 us, 80 leaves of 36 to 131 rows over E4M3 pools 14.8 -> 13.6, 12 drawn calls
-// 0.99 to 1.13; lists without such steps 0 to 0.3 % longer.
+// head_dim 64 23.6 -> 23.1 us, 80 leaves of 36 to 131 rows over E4M3 pools 14.8 -> 13.6, 217 drawn calls with
+// head_dim 128 0.97 to 1.23 times faster, geometric mean 1.03; lists without such steps 0 to 0.3 % longer (0.1 %
+// of it is the branch: not worth instantiations without it).
 // The result per query row is the unnormalised partial (o, m, l), m in log2
 // units, merged later along each leaf's chain.
 #pragma once
@@ -279,8 +280,9 @@ struct MergeTail {
 // Workgroups per compute unit: three (168 registers), with head_dim 64 four (126 instead of 137 registers of
 // bf16 pools): calls of short items wait for memory most of the time, and one more workgroup per unit shortens
 // their rounds.  100 leaves of 17 to 150 rows 22.9 -> 20.7 us, 12 drawn calls of head_dim 64 1.00 to 1.17 times
-// faster, none slower.  (Four of E4M3 pools with head_dim 128 spill two registers: 1.03 to 1.08 on 120 to 272
-// leaves, 0.98 to 1.00 on up to 64; bf16 pools spill 65.)
+// faster, none slower; 68 with joined steps as well 0.99 to 1.29, geometric mean 1.06.  (Four of E4M3 pools with
+// head_dim 128 spill two registers: 1.03 to 1.08 on 120 to 272 leaves, 0.98 to 1.00 on up to 64; bf16 pools
+// spill 65.)
 template <bool FP8, bool FUSED, int D = 128>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(D == 64 && !FUSED ? 4 : 3))) void tree_attn_kernel(
     const void* __restrict__ k_pool, const void* __restrict__ v_pool, int64_t pool_tokens,
